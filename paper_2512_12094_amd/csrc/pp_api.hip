@@ -845,8 +845,10 @@ void fuse_gates(std::vector<Op>& ops, size_t from, int W);
 // kLayerMaxRot pairwise commuting rotations, a LAYER op carrying them (its
 // rotation table appended to `tab`) is put in front of them and they become
 // its fallback copies.
+// `table_ok`: the gate table holds the set the sub-layer starts from; if not
+// (a LAYER op's unmerged output), the copies start with an OP_COUNT.
 void add_layer_op(std::vector<Op>& ops, size_t from, size_t to_gate_end, int W,
-                  std::vector<double>& tab, TabRefs& refs, bool merge_follows) {
+                  std::vector<double>& tab, TabRefs& refs, bool table_ok) {
   if (!g_layer) return;
   const size_t r = to_gate_end - from;
   if (r < (size_t)kLayerMinRot || r > (size_t)kLayerMaxRot) return;
@@ -864,7 +866,6 @@ void add_layer_op(std::vector<Op>& ops, size_t from, size_t to_gate_end, int W,
   layer.eps = ops[from].eps;
   layer.wmax = ops[from].wmax;
   layer.full_check = ops[from].full_check;
-  layer.gtab = merge_follows ? 0u : 1u;
   layer.fail_test = g_layer == 2 ? 1u : 0u;
   for (int w = 0; w < kMaxW; ++w) {       // the first rotation (for the op's own record)
     layer.px[w] = ops[from].px[w];
@@ -882,6 +883,7 @@ void add_layer_op(std::vector<Op>& ops, size_t from, size_t to_gate_end, int W,
     tab.insert(tab.end(), rec, rec + kLayerRec);
   }
   fuse_gates(ops, from, W);
+  if (!table_ok) ops.insert(ops.begin() + from, make_op(OP_COUNT));
   for (size_t a = from; a < ops.size(); ++a) ops[a].fallback = 1;
   layer.skip = (uint32_t)(ops.size() - from);
   ops.insert(ops.begin() + from, layer);
@@ -1924,6 +1926,7 @@ int pp_program_create(pp_program** out, int n_qubits, size_t n_sub, const size_t
   TabRefs refs;
   std::vector<Op>& ops = p->ops;
   ops.push_back(make_op(OP_COUNT));
+  bool table_ok = true;                    // the merge of the observable's rows made it
   for (size_t j = 0; j < n_sub; ++j) {
     if (!(eps[j] >= 0.0) || !(depol_p[j] >= 0.0 && depol_p[j] <= 1.0))
       return fail(PP_EINVAL, "bad sub-layer parameters");
@@ -1947,9 +1950,17 @@ int pp_program_create(pp_program** out, int n_qubits, size_t n_sub, const size_t
       op.full_check = k == sub_start[j];
       ops.push_back(op);
     }
-    const size_t before = ops.size();
-    add_layer_op(ops, first_gate, ops.size(), W, tab, refs, merge_follows);
-    if (ops.size() == before) fuse_gates(ops, first_gate, W);
+    const size_t gates_end = ops.size();
+    const bool has_gates = gates_end > first_gate;
+    add_layer_op(ops, first_gate, gates_end, W, tab, refs, table_ok);
+    const bool layered = has_gates && ops[first_gate].type == OP_LAYER;
+    if (has_gates && !layered) {
+      fuse_gates(ops, first_gate, W);
+      if (!table_ok) ops.insert(ops.begin() + first_gate, make_op(OP_COUNT));
+    }
+    // merges and gates leave a valid gate table, an unmerged LAYER op does not
+    if (merge_follows) table_ok = true;
+    else if (has_gates) table_ok = !layered;
     const bool trunc = eps[j] > 0.0 || max_weight[j] >= 0;
     if (!merge_after || merge_after[j]) {
       Op merge = make_op(OP_MERGE);

@@ -1864,6 +1864,7 @@ __device__ __forceinline__ void finish_rebuild(const InstBuf& b, InstDyn& d) {
   d.half ^= 1u;
   d.parity = 0;
   d.gen += 1;
+  d.gstale = 0;
   take_acc(d);
   d.count_for = op.next_gate;
   d.nuniq = 0;
@@ -2085,6 +2086,8 @@ struct ScanKind {
         const double term =
             c * op.table[nx] * op.table[(n + 1) + ny] * op.table[2 * (n + 1) + nz];
         acc = fx_add(acc, fx_from_double(term, &range));
+      } else if (type == OP_COUNT && d.gstale) {
+        gt_insert(b.gtab, b.hg_bits, d.gen + 1, i, hash_key(x, z, W, 0));
       }
       ++my_live;
       if (ng.anti(x, z, W)) ++my_cnt;
@@ -2113,6 +2116,10 @@ struct ScanKind {
                  ld_agent(&d.expect_fx[2])};
       d.expect = fx_to_double(f);
       d.expect_fx[0] = d.expect_fx[1] = d.expect_fx[2] = 0;
+    }
+    if (op.type == OP_COUNT && d.gstale) {
+      d.gen += 1;
+      d.gstale = 0;
     }
     take_acc(d);
     d.count_for = op.next_gate;
@@ -2396,6 +2403,7 @@ __global__ __launch_bounds__(kBlock) void k_grow(InstBuf src, InstBuf dst, InstD
     d.half = 0;
     d.parity = 0;
     d.gen = 1;
+    d.gstale = 0;
   }
 }
 

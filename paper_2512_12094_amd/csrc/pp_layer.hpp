@@ -331,7 +331,10 @@ __device__ __forceinline__ bool layer_heavy(const uint64_t* x, const uint64_t* z
 
 // The bucket's survivors (every LDS slot whose string lives; unused slots
 // read as dropped) to the other half of the store (one atomic per block and
-// bucket), with gate-table entries when the op asks for them.
+// bucket).  No gate-table entries: inserting the next generation's entries
+// takes over slots of the current one, which the op's gate copies still need
+// if a bucket elsewhere does not fit.  layer_finish marks the table stale and
+// the OP_COUNT in front of the next gates enters the set.
 template <int WW, int NB, int CAP>
 __device__ __forceinline__ void emit_survivors(const InstBuf& b, InstDyn& d, const Op& op,
                                                const uint64_t (*sx)[CAP], const uint64_t (*sz)[CAP],
@@ -347,7 +350,7 @@ __device__ __forceinline__ void emit_survivors(const InstBuf& b, InstDyn& d, con
   if (threadIdx.x == 0) *s_base = total ? atomicAdd(&d.nuniq, total) : 0u;
   __syncthreads();
   const uint32_t ob = *s_base, cap = b.cap, ho = d.half ^ 1u;
-  const bool has_next = op.next_gate != kNone32, gtab = op.gtab != 0;
+  const bool has_next = op.next_gate != kNone32;
   *out += mine;
   for (uint32_t j = threadIdx.x; j < (uint32_t)CAP; j += NB) {
     if (!alive(j)) continue;
@@ -370,7 +373,6 @@ __device__ __forceinline__ void emit_survivors(const InstBuf& b, InstDyn& d, con
     else
       static_cast<double*>(b.c[ho])[pos] = sc[j];
     b.alive[ho][0][pos] = 1;
-    if (gtab) gt_insert(b.gtab, b.hg_bits, d.gen + 1, pos, hash_key(x, z, WW, 0));
   }
 }
 
@@ -419,7 +421,7 @@ __device__ __forceinline__ void layer_finish(const InstBuf& b, InstDyn& d, const
   if (held > d.peak) d.peak = held < 0xFFFFFFFFull ? (uint32_t)held : 0xFFFFFFFFu;
   d.half ^= 1u;
   d.parity = 0;
-  if (op.gtab) d.gen += 1;
+  d.gstale = 1;
   d.count_for = op.next_gate;
   d.pc += 1 + op.skip;
 }

@@ -46,7 +46,8 @@ enum OpType : uint32_t {
   OP_MERGE = 2,    // symmetry merge by orbit representative
   OP_DAMP = 3,     // c *= (1-p)^weight
   OP_TRUNC = 4,    // drop |c| < eps or weight > wmax
-  OP_COUNT = 5,    // only recount (live, anticommuting with next gate)
+  OP_COUNT = 5,    // recount (live, anticommuting with next gate); enters the
+                   // live terms into the gate table if a LAYER op left it stale
   OP_EXPECT = 6,   // expectation in a symmetric product state
   OP_GATES = 7,    // 2..kMaxFuse mutually commuting rotations in circuit
                    // order, each followed by the exact merge and
@@ -148,8 +149,6 @@ struct Op {
                          // after that op failed
   uint32_t nrot;         // GATE: 1; GATES, LAYER: rotations in the op
   uint32_t skip;         // LAYER: number of fallback ops that follow it
-  uint32_t gtab;         // LAYER: its output gets gate-table entries (no
-                         // merge follows before the next gate)
   uint32_t fail_test;    // LAYER: always reports a failure (tests of the
                          // fallback path)
   uint64_t px[kMaxW];    // GATE(S): the (first) rotation's Pauli string
@@ -267,6 +266,8 @@ struct InstDyn {
   uint32_t lserved;      // batched form: this step's scatter took the instance's layer op
   uint32_t lfail;        // layer op: a bucket overflowed its slots or the LDS
   uint32_t lneed;        // layer op: survivors of an op whose output did not fit
+  uint32_t gstale;       // the gate table does not hold the current set (a LAYER
+                         // op wrote it); cleared by whatever enters the set again
 };
 
 }  // namespace pp

@@ -173,3 +173,16 @@ def test_batched_form_runs_layer_ops(gpu, mode):
             assert st["layer_ops"] == 0 and st["fallbacks"] > 0, (p.name, st)
         s.close()
         d.close()
+
+
+def test_failed_layer_op_keeps_the_gate_table(gpu):
+    """An untruncated Z_11 Ising ring merged once per Trotter layer: layer
+    ops follow each other without a merge, and the large ones do not fit and
+    fall back to their gate launches, which need gate-table entries for the
+    set the failed op started from.  Bitwise the gate launches' results."""
+    prog = W.tilted_ising_ring(11, 6, 0.25, merge="layer")
+    print("[case] failed layer ops between unmerged sub-layers", flush=True)
+    off = run(gpu, prog, 0)
+    forced = run(gpu, prog, 2)
+    same(forced, off, "forced fallbacks vs gate launches")
+    same(run(gpu, prog, 1), off, "layer ops vs gate launches")
