@@ -283,6 +283,14 @@ uint32_t layer_max_bits(uint32_t slots) {
   return bits;
 }
 
+// Staging slots for a store of `cap` entries: small stores use finer buckets
+// (layer_bits), whose sizes vary more, so they get four times the slots (at
+// most 2^19, 17 MB at one word).
+constexpr uint32_t kLayerSmallCap = 1u << 17;
+uint32_t layer_slots(uint32_t cap) {
+  return 1u << (ceil_log2(cap) + (cap <= kLayerSmallCap ? 2 : 0));
+}
+
 int alloc_store(pp_state* s, uint32_t cap, InstBuf* b, std::vector<void*>* allocs,
                 size_t* dry = nullptr) {
   const int W = s->W;
@@ -343,18 +351,16 @@ int alloc_store(pp_state* s, uint32_t cap, InstBuf* b, std::vector<void*>* alloc
   nb.lstx = nb.lstz = nullptr;
   nb.lstc = nullptr;
   nb.lsta = nullptr;
-  nb.lsth = nullptr;
   nb.lcount = nullptr;
   nb.lslots = 0;
   nb.lmaxbits = 0;
   if (s->layer_used) {
-    nb.lslots = 1u << ceil_log2(cap);
+    nb.lslots = layer_slots(cap);
     nb.lmaxbits = layer_max_bits(nb.lslots);
     ok = ok && (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
     ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
     ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
     ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
-    ok = ok && (nb.lsth = (uint32_t*)take(sizeof(uint32_t) * nb.lslots));
     ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
   }
   const bool wide = !nb.narrow;
@@ -474,10 +480,14 @@ SoloFn solo_of(int kind, bool big, uint32_t nrot = 1, int lane_it = 0, int group
   }
 }
 
-SoloFn layer_of(int kind, int W) {
+SoloFn layer_of(int kind, int n, int W) {
   if (kind == PP_K_LAYER_SCATTER) return W == 1 ? &k_layer_scatter<1> : &k_layer_scatter<2>;
-  if (g_tune.layer_block == 256) return W == 1 ? &k_layer_apply<1, 256> : &k_layer_apply<2, 256>;
-  return W == 1 ? &k_layer_apply<1, 512> : &k_layer_apply<2, 512>;
+  const int kw = layer_key_words(n, W);
+  if (g_tune.layer_block == 256)
+    return kw == 1 ? &k_layer_apply<1, 256> : kw == 2 ? &k_layer_apply<2, 256>
+                                                      : &k_layer_apply<4, 256>;
+  return kw == 1 ? &k_layer_apply<1, 512> : kw == 2 ? &k_layer_apply<2, 512>
+                                                    : &k_layer_apply<4, 512>;
 }
 
 // The layer op's staging, allocated when a handle first runs one (and
@@ -487,7 +497,7 @@ int ensure_layer(pp_state* s) {
   s->layer_used = true;
   InstBuf& nb = s->buf;
   const int W = s->W;
-  nb.lslots = 1u << ceil_log2(nb.cap);
+  nb.lslots = layer_slots(nb.cap);
   nb.lmaxbits = layer_max_bits(nb.lslots);
   std::vector<void*> got;
   auto take = [&](size_t bytes) -> void* {
@@ -499,14 +509,12 @@ int ensure_layer(pp_state* s) {
   ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
   ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
   ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
-  ok = ok && (nb.lsth = (uint32_t*)take(sizeof(uint32_t) * nb.lslots));
   ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
   if (!ok) {
     for (void* p : got) dev_free(s, p);
     nb.lstx = nb.lstz = nullptr;
     nb.lstc = nullptr;
     nb.lsta = nullptr;
-    nb.lsth = nullptr;
     nb.lcount = nullptr;
     nb.lslots = nb.lmaxbits = 0;
     return fail(PP_ENOMEM, "allocation of the layer staging failed");
@@ -718,7 +726,7 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
       S.sync = s->d_sync;
       S.k = (uint32_t)k;
       if (layer)
-        hipLaunchKernelGGL(layer_of(kind, s->W), dim3(grid), dim3(block), 0, s->stream, S);
+        hipLaunchKernelGGL(layer_of(kind, s->n, s->W), dim3(grid), dim3(block), 0, s->stream, S);
       else
         hipLaunchKernelGGL(solo_of(kind, big, nrot, lane_it, s->group), dim3(grid), dim3(block),
                            part_lds(s->buf, kind), s->stream, S);
@@ -2047,7 +2055,7 @@ struct BatchCtx {
   InstDyn** h_dynp = nullptr;
   hipGraphExec_t exec = nullptr;
   int exec_steps = 0, exec_blocks = 0, exec_sig = 0;
-  int layer_w = 0;   // bit w-1: some instance runs layer ops with w key words
+  int layer_w = 0;   // key words (1, 2, 4; layer_key_words) the batch's layer ops run with, ored
 };
 
 std::mutex g_batch_mu;
@@ -2083,14 +2091,17 @@ int batch_ctx(hipStream_t stream, BatchCtx** out) {
 // for the instances that reached them (two scans: truncation, then the
 // next layer's damping).
 // Dynamic LDS of the batched layer apply (above the 64 KB default).
-template <int WW>
-void allow_layer_lds() {
+template <int KW>
+void launch_layer_multi(const Ctx& C, dim3 g, hipStream_t stream) {
   static std::once_flag once;
   std::call_once(once, [] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_layer_apply_multi<WW, 512>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_layer_apply_multi<KW, 512>),
                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)sizeof(ApplySh<WW, 512>));
+                              (int)sizeof(ApplySh<KW, 512>));
   });
+  hipLaunchKernelGGL((k_layer_scatter_multi<ApplySh<KW, 512>::WW>), g, dim3(kBlock), 0, stream, C);
+  hipLaunchKernelGGL((k_layer_apply_multi<KW, 512>), g, dim3(512), sizeof(ApplySh<KW, 512>),
+                     stream, C);
 }
 
 void launch_step(BatchCtx* b, int blocks) {
@@ -2100,19 +2111,11 @@ void launch_step(BatchCtx* b, int blocks) {
   C.ninst = b->d_ninst;
   C.sync = b->d_sync;
   const dim3 g(blocks), t(kBlock);
-  // layer ops first: an instance at one finishes it within the step
-  if (b->layer_w & 1) {
-    allow_layer_lds<1>();
-    hipLaunchKernelGGL(k_layer_scatter_multi<1>, g, t, 0, b->stream, C);
-    hipLaunchKernelGGL((k_layer_apply_multi<1, 512>), g, dim3(512), sizeof(ApplySh<1, 512>),
-                       b->stream, C);
-  }
-  if (b->layer_w & 2) {
-    allow_layer_lds<2>();
-    hipLaunchKernelGGL(k_layer_scatter_multi<2>, g, t, 0, b->stream, C);
-    hipLaunchKernelGGL((k_layer_apply_multi<2, 512>), g, dim3(512), sizeof(ApplySh<2, 512>),
-                       b->stream, C);
-  }
+  // layer ops first: an instance at one finishes it within the step (one
+  // launch pair per key width in the batch)
+  if (b->layer_w & 1) launch_layer_multi<1>(C, g, b->stream);
+  if (b->layer_w & 2) launch_layer_multi<2>(C, g, b->stream);
+  if (b->layer_w & 4) launch_layer_multi<4>(C, g, b->stream);
   for (int k = 0; k < std::max(1, g_tune.gates_per_step); ++k)
     hipLaunchKernelGGL(kernel_of(PP_K_GATE), g, t, 0, b->stream, C);
   for (int kind : {PP_K_MERGE_NARROW, PP_K_MERGE_WIDE1, PP_K_MERGE_WIDE2, PP_K_MERGE_COLLECT,
@@ -2407,7 +2410,8 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
   *b->h_ninst = (int)n;
   b->layer_w = 0;
   for (size_t i = 0; i < n; ++i)
-    if (!states[i]->buf.nolayer) b->layer_w |= 1 << (states[i]->W - 1);
+    if (!states[i]->buf.nolayer) b->layer_w |= layer_key_words(states[i]->n, states[i]->W);
+  if ((b->layer_w & 3) == 3) b->layer_w &= ~1;   // one launch pair serves all one-word strings
   HIP_TRY(hipMemcpyAsync(b->d_bufp, b->h_bufp, sizeof(void*) * n, hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(b->d_dynp, b->h_dynp, sizeof(void*) * n, hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(b->d_ninst, b->h_ninst, sizeof(int), hipMemcpyHostToDevice, stream));

@@ -14,18 +14,20 @@
 // each string in it, its partner under every rotation and every child the
 // rotations can make: a block rotates its bucket in LDS with no other block.
 //
-// The same holds for any union of such sets, so within a bucket each wave
-// takes the strings of whole sets (by the key's hash): a wave rotates its
-// strings with no other wave and no barrier, and runs only the rotations one
-// of its strings anticommutes with (a is shared by a set's members).
-//
-// A wave's rotation g runs over its strings live before it, each with its
-// partner P_g Q found in the wave's LDS hash table: both live -> the pair
+// A string runs its own rotations a(Q) in circuit order, each with its
+// partner P_g Q found in the block's LDS hash table: both live -> the pair
 // rotation (the lower index writes both), partner absent or dropped -> cos
 // on Q and a child sin on P_g Q (a dropped partner's slot is reused), then
 // the truncation of what changed, exactly as the one-rotation gate kernel
 // does it, so the results are bitwise those of r gate launches.  Children
-// of rotation g get indices past those it reads.
+// of a step get indices past those it reads.
+//
+// Measured (MI355X, kernel average per launch, before -> after the apply step
+// took its present form: a string's q-th own rotation per step, one
+// select-based path, table probes as DS instead of FLAT loads, finer buckets
+// for small sets, sums without LDS round trips): Z_8 ring untruncated 42 ->
+// 19 us, the Z_32 ring (10^5 strings) 40 -> 25 us, the same circuit unmerged
+// (5x10^5 strings) 124 -> 43 us.
 #pragma once
 #include "pp_kernels.hpp"
 
@@ -33,9 +35,17 @@ namespace pp {
 
 constexpr uint32_t kAlive = 0xFFu;   // died field of a live string (see live_before)
 
-template <int WW> struct LayerCap;
-template <> struct LayerCap<1> { static constexpr int n = 2048; };   // strings per bucket in LDS
-template <> struct LayerCap<2> { static constexpr int n = 1024; };
+// Key words of a string in the apply step's LDS: one (x | z << 32) for n <= 32,
+// else its W x words, then its W z words.
+__host__ __device__ __forceinline__ int layer_key_words(int n, int W) {
+  return n <= 32 ? 1 : 2 * W;
+}
+
+// Strings per bucket in LDS: two blocks of the apply step fit a CU's 160 KB.
+template <int KW> struct LayerCap;
+template <> struct LayerCap<1> { static constexpr int n = 2048; };
+template <> struct LayerCap<2> { static constexpr int n = 1792; };
+template <> struct LayerCap<4> { static constexpr int n = 1024; };
 
 // Bucket bits for a layer op over M entries: about 2^shift strings per
 // bucket, more after failures (boost), at most maxbits.
@@ -43,7 +53,10 @@ __device__ __host__ __forceinline__ uint32_t layer_bits(uint32_t M, int32_t boos
                                                         uint32_t maxbits, uint32_t shift) {
   uint32_t lg = 0;
   while (lg < 32 && (1ull << lg) < (uint64_t)M) ++lg;
-  int bits = (int)lg - (int)shift + boost;   // boost: from earlier failures
+  int bits = (int)lg - (int)shift;
+  const int fine = (int)lg - kLayerFine < kLayerFillBits ? (int)lg - kLayerFine : kLayerFillBits;
+  if (bits < fine) bits = fine;
+  bits += boost;                             // boost: from earlier failures
   if (bits < 0) bits = 0;
   if (bits > (int)maxbits) bits = (int)maxbits;
   return (uint32_t)bits;
@@ -134,7 +147,7 @@ __device__ __forceinline__ bool scatter_round(const InstBuf& b, const InstDyn& d
   __syncthreads();                         // rotations loaded, counts zero
   uint64_t x[kLTile][WW], z[kLTile][WW], a[kLTile];
   double c[kLTile];
-  uint32_t bk[kLTile], rank[kLTile], h32[kLTile];
+  uint32_t bk[kLTile], rank[kLTile];
   bool has[kLTile];
 #pragma unroll
   for (int k = 0; k < kLTile; ++k) {
@@ -148,7 +161,6 @@ __device__ __forceinline__ bool scatter_round(const InstBuf& b, const InstDyn& d
     }
     c[k] = v.getc(i);
     const uint64_t h = layer_key<WW>(x[k], z[k], r, sh.px, sh.pz, &a[k]);
-    h32[k] = (uint32_t)h;
     bk[k] = bits ? (uint32_t)(h >> (64 - bits)) : 0u;
     rank[k] = agg ? atomicAdd(&sh.cnt[bk[k]], 1u) : atomicAdd(&b.lcount[bk[k]], 1u);
   }
@@ -173,7 +185,6 @@ __device__ __forceinline__ bool scatter_round(const InstBuf& b, const InstDyn& d
     }
     b.lstc[pos] = c[k];
     b.lsta[pos] = a[k];
-    b.lsth[pos] = h32[k];
   }
   return over;
 }
@@ -243,14 +254,141 @@ __global__ __launch_bounds__(kBlock) void k_layer_scatter_multi(Ctx C) {
   }
 }
 
-template <int WW>
-__device__ __forceinline__ uint32_t lds_hash(const uint64_t* x, const uint64_t* z) {
-  uint64_t h = x[0] * 0x9e3779b97f4a7c15ull ^ z[0] * 0xc2b2ae3d27d4eb4full;
-  if (WW > 1) h = (h ^ (h >> 29)) * 0xbf58476d1ce4e5b9ull ^ x[WW - 1] * 0x94d049bb133111ebull ^
-                  z[WW - 1] * 0xff51afd7ed558ccdull;
-  return (uint32_t)((h ^ (h >> 31)) >> 32);
+// String arithmetic on KW key words (layer_key_words).
+template <int KW>
+__device__ __forceinline__ void lk_pack(const uint64_t* x, const uint64_t* z, uint64_t* k) {
+  if constexpr (KW == 1) {
+    k[0] = x[0] | (z[0] << 32);
+  } else {
+#pragma unroll
+    for (int w = 0; w < KW / 2; ++w) { k[w] = x[w]; k[KW / 2 + w] = z[w]; }
+  }
 }
 
+template <int KW>
+__device__ __forceinline__ void lk_unpack(const uint64_t* k, uint64_t* x, uint64_t* z) {
+  if constexpr (KW == 1) {
+    x[0] = (uint32_t)k[0];
+    z[0] = k[0] >> 32;
+  } else {
+#pragma unroll
+    for (int w = 0; w < KW / 2; ++w) { x[w] = k[w]; z[w] = k[KW / 2 + w]; }
+  }
+}
+
+// (x, z) swapped: Q anticommutes with P iff popc(Q & swapped(P)) is odd
+template <int KW>
+__device__ __forceinline__ bool lk_anti(const uint64_t* q, const uint64_t* p) {
+  uint32_t par = 0;
+  if constexpr (KW == 1) {
+    par = __popcll(q[0] & ((p[0] << 32) | (p[0] >> 32)));
+  } else {
+#pragma unroll
+    for (int w = 0; w < KW; ++w) par += __popcll(q[w] & p[(w + KW / 2) % KW]);
+  }
+  return par & 1u;
+}
+
+template <int KW>
+__device__ __forceinline__ int lk_sign(const uint64_t* p, const uint64_t* q, const uint64_t* r) {
+  if constexpr (KW == 1) {
+    const uint32_t px = (uint32_t)p[0], pz = (uint32_t)(p[0] >> 32);
+    const uint32_t qx = (uint32_t)q[0], qz = (uint32_t)(q[0] >> 32);
+    const uint32_t rx = (uint32_t)r[0], rz = (uint32_t)(r[0] >> 32);
+    const int phi = __popc(px & pz) + __popc(qx & qz) + 2 * __popc(pz & qx) - __popc(rx & rz);
+    return ((phi & 3) == 3) ? 1 : -1;
+  } else {
+    constexpr int W = KW / 2;
+    return product_sign(p, p + W, q, q + W, r, r + W, W);
+  }
+}
+
+template <int KW>
+__device__ __forceinline__ bool lk_heavy(const uint64_t* k, int wmax) {
+  if (wmax < 0) return false;
+  int n = 0;
+  if constexpr (KW == 1) {
+    n = __popc((uint32_t)k[0] | (uint32_t)(k[0] >> 32));
+  } else {
+#pragma unroll
+    for (int w = 0; w < KW / 2; ++w) n += __popcll(k[w] | k[KW / 2 + w]);
+  }
+  return n > wmax;
+}
+
+// 32-bit hash of a key: one 32-bit product per half word (a 64-bit product
+// takes four).  A hash linear over GF(2), which would give a partner's slot
+// by one xor, maps some closed sets onto few slots: measured up to 20 times
+// slower steps.
+template <int KW>
+__device__ __forceinline__ uint32_t lk_hash(const uint64_t* k) {
+  uint32_t h = 0;
+#pragma unroll
+  for (int w = 0; w < KW; ++w) {
+    h = (h ^ (uint32_t)k[w]) * 0x9e3779b1u;
+    h ^= h >> 16;
+    h = (h ^ (uint32_t)(k[w] >> 32)) * 0x85ebca77u;
+    h ^= h >> 15;
+  }
+  return h;
+}
+
+// The bucket's hash table: open addressing, linear probing, 32-bit entries: a
+// string's index + 1 in the low IB bits (0: empty) and the hash's low bits
+// as a tag above, so that a probe of another string's slot hardly ever costs
+// a key compare.  At most half full.
+template <int CAP>
+struct LdsTab {
+  static constexpr int HB = 33 - __builtin_clz(CAP - 1), HS = 1 << HB;
+  static constexpr int IB = HB;            // CAP < 2^IB
+  static_assert(HS >= 2 * CAP && CAP < (1 << IB), "at most half full");
+  __device__ __forceinline__ static uint32_t slot(uint32_t h) { return h >> (32 - HB); }
+  __device__ __forceinline__ static uint32_t tagged(uint32_t h) { return h << IB; }
+  __device__ __forceinline__ static bool tag_is(uint32_t e, uint32_t tg) {
+    return ((e ^ tg) >> IB) == 0;
+  }
+  __device__ __forceinline__ static uint32_t index(uint32_t e) {
+    return (e & ((1u << IB) - 1)) - 1;
+  }
+  // an atomic load, which stays a DS instruction (a volatile one goes
+  // through a generic pointer as a FLAT load, several times the latency)
+  __device__ __forceinline__ static uint32_t entry(const uint32_t* tab, uint32_t sl) {
+    return __hip_atomic_load(&tab[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  // publishes index j under hash h from slot sl on
+  __device__ __forceinline__ static void insert(uint32_t* tab, uint32_t h, uint32_t j,
+                                                uint32_t sl) {
+    const uint32_t e = tagged(h) | (j + 1);
+#pragma unroll 1
+    for (int probe = 0; probe < HS; ++probe) {
+      if (atomicCAS(&tab[sl], 0u, e) == 0u) return;
+      sl = (sl + 1) & (HS - 1);
+    }
+  }
+};
+
+// Sum over the wave, valid in lane 63 (data-parallel primitives: shifts
+// within rows of 16 lanes, then row broadcasts; no LDS round trips).
+__device__ __forceinline__ uint32_t wave_sum63(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);   // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);   // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);   // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);   // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+
+// Maximum over the wave, valid in lane 63 (as wave_sum63).
+__device__ __forceinline__ uint32_t wave_max63(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+  return v;
+}
 
 // Exclusive scan of one value per thread over a block of NW waves; *total
 // = block sum.  s_tmp needs NW + 1 entries.  Contains __syncthreads.
@@ -276,93 +414,99 @@ __device__ __forceinline__ uint32_t block_scan_n(uint32_t v, uint32_t* s_tmp, ui
   return r;
 }
 
-__device__ __forceinline__ uint16_t lds_load16(const uint16_t* p) {
-  return *reinterpret_cast<const volatile uint16_t*>(p);
-}
+// What the apply step reads of its op.
+struct LayerArgs {
+  const double* table;
+  double eps;
+  uint64_t nx[kMaxW], nz[kMaxW];
+  uint32_t nrot;
+  int wmax;
+  bool full, has_next;
+};
 
-// local index of the string (x, z) in a wave's LDS table (its strings at
-// base + local index), or -1
-template <int WW, int CAP>
-__device__ __forceinline__ int lds_find(const uint16_t* tab, int HS, const uint64_t (*sx)[CAP],
-                                        const uint64_t (*sz)[CAP], uint32_t base,
-                                        const uint64_t* x, const uint64_t* z) {
-  uint32_t sl = lds_hash<WW>(x, z) & (HS - 1);
-  for (int probe = 0; probe < HS; ++probe) {
-    const uint32_t e = lds_load16(&tab[sl]);
-    if (e == 0) return -1;
-    const int j = (int)e - 1;
-    bool eq = true;
+__device__ __forceinline__ LayerArgs layer_args(const Op& op) {
+  LayerArgs a;
+  a.table = op.table;
+  a.eps = op.eps;
 #pragma unroll
-    for (int w = 0; w < WW; ++w) eq = eq && sx[w][base + j] == x[w] && sz[w][base + j] == z[w];
-    if (eq) return j;
-    sl = (sl + 1) & (HS - 1);
-  }
-  return -1;
+  for (int w = 0; w < kMaxW; ++w) { a.nx[w] = op.nx[w]; a.nz[w] = op.nz[w]; }
+  a.nrot = op.nrot;
+  a.wmax = op.wmax;
+  a.full = op.full_check != 0;
+  a.has_next = op.next_gate != kNone32;
+  return a;
 }
 
-// publishes index j (its string already written) under (x, z)
-template <int WW>
-__device__ __forceinline__ void lds_insert(uint16_t* tab, int HS, const uint64_t* x,
-                                           const uint64_t* z, int j) {
-  uint32_t sl = lds_hash<WW>(x, z) & (HS - 1);
-  for (int probe = 0; probe < HS; ++probe) {
-    const uintptr_t a = reinterpret_cast<uintptr_t>(&tab[sl]);
-    uint32_t* wp = reinterpret_cast<uint32_t*>(a & ~uintptr_t(3));
-    const uint32_t shift = (a & 2) ? 16u : 0u;
-    uint32_t old = *reinterpret_cast<volatile uint32_t*>(wp);
-    for (;;) {
-      if ((old >> shift) & 0xFFFFu) break;                        // slot taken
-      const uint32_t got = atomicCAS(wp, old, old | ((uint32_t)(j + 1) << shift));
-      if (got == old) return;
-      old = got;
-    }
-    sl = (sl + 1) & (HS - 1);
+// rotate_pair (pair) or rotate_single with the child as *nr, by selects: the
+// same products, sums and roundings.
+__device__ __forceinline__ void rotate_any(bool f32, double cs, double sn, int sig, bool pair,
+                                           double cq, double cr, double* nq, double* nr) {
+  if (f32) {
+    const float c = (float)cs, s = (float)sn, q = (float)cq, r = (float)cr;
+    const float aq = c * q, bq = s * r, ar = c * r, br = s * q;
+    const float sbq = sig > 0 ? -bq : bq, sbr = sig > 0 ? br : -br;
+    *nq = (double)(pair ? aq + sbq : aq);
+    *nr = (double)(pair ? ar + sbr : sbr);
+  } else {
+    const double aq = cs * cq, bq = sn * cr, ar = cs * cr, br = sn * cq;
+    const double sbq = sig > 0 ? -bq : bq, sbr = sig > 0 ? br : -br;
+    *nq = pair ? aq + sbq : aq;
+    *nr = pair ? ar + sbr : sbr;
   }
 }
 
-template <int WW>
-__device__ __forceinline__ bool layer_heavy(const uint64_t* x, const uint64_t* z, int wmax) {
-  if (wmax < 0) return false;
-  int n = 0;
-#pragma unroll
-  for (int w = 0; w < WW; ++w) n += __popcll(x[w] | z[w]);
-  return n > wmax;
-}
-
-// The bucket's survivors (every LDS slot whose string lives; unused slots
-// read as dropped) to the other half of the store (one atomic per block and
-// bucket).  No gate-table entries: inserting the next generation's entries
-// takes over slots of the current one, which the op's gate copies still need
-// if a bucket elsewhere does not fit.  layer_finish marks the table stale and
-// the OP_COUNT in front of the next gates enters the set.
-template <int WW, int NB, int CAP>
-__device__ __forceinline__ void emit_survivors(const InstBuf& b, InstDyn& d, const Op& op,
-                                               const uint64_t (*sx)[CAP], const uint64_t (*sz)[CAP],
-                                               const double* sc, const uint16_t* life,
-                                               uint32_t* s_tmp,
+// The bucket's survivors (of its ng strings) to the other half of the store
+// (one atomic per block and bucket).  No gate-table entries: inserting the
+// next generation's entries takes over slots of the current one, which the
+// op's gate copies still need if a bucket elsewhere does not fit.
+// layer_finish marks the table stale and the OP_COUNT in front of the next
+// gates enters the set.
+template <int KW, int NB, int CAP>
+__device__ __forceinline__ void emit_survivors(const InstBuf& b, InstDyn& d, const LayerArgs& op,
+                                               const uint64_t (*sk)[CAP], const double* sc,
+                                               const uint16_t* life, uint32_t ng, uint32_t* s_tmp,
                                                uint32_t* s_base, uint32_t* out, uint32_t* next) {
-  constexpr int NW = NB / 64;
-  auto alive = [&](uint32_t j) { return (life[j] & 0xFFu) == kAlive; };   // unused slots: died 0
-  uint32_t mine = 0;
-  for (uint32_t j = threadIdx.x; j < (uint32_t)CAP; j += NB) mine += alive(j) ? 1u : 0u;
-  uint32_t total;
-  uint32_t off = block_scan_n<NW>(mine, s_tmp, &total);
-  if (threadIdx.x == 0) *s_base = total ? atomicAdd(&d.nuniq, total) : 0u;
+  constexpr int NW = NB / 64, WW = KW == 1 ? 1 : KW / 2;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t wsum = 0;                       // the wave's survivors
+#pragma unroll 1
+  for (uint32_t j0 = 0; j0 < ng; j0 += NB) {
+    const uint32_t j = j0 + threadIdx.x;
+    wsum += (uint32_t)__popcll(__ballot(j < ng && (life[j] & 0xFFu) == kAlive));
+  }
+  if (lane == 0) s_tmp[wid] = wsum;
   __syncthreads();
-  const uint32_t ob = *s_base, cap = b.cap, ho = d.half ^ 1u;
-  const bool has_next = op.next_gate != kNone32;
-  *out += mine;
-  for (uint32_t j = threadIdx.x; j < (uint32_t)CAP; j += NB) {
-    if (!alive(j)) continue;
-    const uint32_t pos = ob + off++;
-    uint64_t x[kMaxW] = {}, z[kMaxW] = {};
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
 #pragma unroll
-    for (int w = 0; w < WW; ++w) { x[w] = sx[w][j]; z[w] = sz[w][j]; }
+    for (int w = 0; w < NW; ++w) total += s_tmp[w];
+    *s_base = total ? atomicAdd(&d.nuniq, total) : 0u;
+    *out += total;
+  }
+  uint32_t off = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) off += w < wid ? s_tmp[w] : 0u;
+  __syncthreads();
+  uint32_t next_pos = *s_base + off;
+  const uint32_t cap = b.cap, ho = d.half ^ 1u;
+  const bool has_next = op.has_next;
+#pragma unroll 1
+  for (uint32_t j0 = 0; j0 < ng; j0 += NB) {
+    const uint32_t j = j0 + threadIdx.x;
+    const bool al = j < ng && (life[j] & 0xFFu) == kAlive;
+    const uint64_t m = __ballot(al);
+    const uint32_t pos = next_pos + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+    next_pos += (uint32_t)__popcll(m);
+    if (!al) continue;
+    uint64_t k[KW], x[kMaxW] = {}, z[kMaxW] = {};
+#pragma unroll
+    for (int w = 0; w < KW; ++w) k[w] = sk[w][j];
+    lk_unpack<KW>(k, x, z);
     uint64_t nx[kMaxW] = {}, nz[kMaxW] = {};
 #pragma unroll
     for (int w = 0; w < WW; ++w) { nx[w] = op.nx[w]; nz[w] = op.nz[w]; }
     if (has_next && anticommutes(x, z, nx, nz, WW)) ++*next;
-    if (pos >= cap) { atomicOr(&d.status, ST_OVERFLOW); continue; }
+    if (pos >= cap) { consume(atomicOr(&d.status, ST_OVERFLOW)); continue; }
 #pragma unroll
     for (int w = 0; w < WW; ++w) {
       b.x[ho][(size_t)w * cap + pos] = x[w];
@@ -376,23 +520,20 @@ __device__ __forceinline__ void emit_survivors(const InstBuf& b, InstDyn& d, con
   }
 }
 
-// Last block, one thread: folds the sums; on success the op's counts, the
-// other half becomes current and pc passes the op's fallback copies.
-__device__ __forceinline__ void layer_finish(const InstBuf& b, InstDyn& d, const Op& op, int ns,
-                                             bool batched) {
-  uint64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int sh = 0; sh < kAccShards; ++sh)
-    for (int k = 0; k < ns; ++k)
-      t[k] += atomicExch((unsigned long long*)&b.accs[sh * kLineU64 + 1 + k], 0ull);
-  const uint32_t out = ld_agent(&d.nuniq);
+// Last block, one thread, with the folded sums t (LayerSums order): on
+// success the op's counts, the other half becomes current and pc passes the
+// op's fallback copies.
+__device__ __forceinline__ void layer_finish(const InstBuf& b, InstDyn& d, const Op& op,
+                                             const uint64_t* t, bool batched) {
+  const uint32_t out = ld_agent(&d.nuniq), status = ld_agent(&d.status), why = ld_agent(&d.lfail);
+  consume((uint64_t)out ^ status ^ why);
   d.nuniq = 0;
-  if (ld_agent(&d.status) & ST_OVERFLOW) {  // the survivors did not fit: grow, run again
+  if (status & ST_OVERFLOW) {               // the survivors did not fit: grow, run again
     d.lneed = out;
     d.lfail = 0;
     d.failed_pc = d.pc;
     return;
   }
-  const uint32_t why = ld_agent(&d.lfail);
   if (why) {                                // a bucket did not fit
     d.lfail = 0;
     d.lwhy = why;                           // 1 staging slots, 2 LDS
@@ -402,7 +543,7 @@ __device__ __forceinline__ void layer_finish(const InstBuf& b, InstDyn& d, const
       d.pc += 1;
       return;
     }
-    d.status |= ST_LAYER;                   // the one-instance path: the host decides
+    d.status = status | ST_LAYER;           // the one-instance path: the host decides
     d.failed_pc = d.pc;
     return;
   }
@@ -447,243 +588,295 @@ __device__ __forceinline__ uint16_t life_of(uint32_t born, uint32_t died) {
 // with a block barrier after it; then the survivors go to the other half.
 // Live counts before each rotation follow from the strings entering and the
 // births and drops of the rotations before it.
-template <int WW, int NB>
+template <int KW, int NB>
 struct ApplySh {
-  static constexpr int CAP = LayerCap<WW>::n, HS = 2 * CAP, NW = NB / 64, NS = 7;
-  uint64_t x[WW][CAP], z[WW][CAP];
+  static constexpr int CAP = LayerCap<KW>::n, HS = LdsTab<CAP>::HS, NW = NB / 64, NS = 7;
+  static constexpr int WW = KW == 1 ? 1 : KW / 2;
+  uint64_t k[KW][CAP];
   double c[CAP];
+  uint64_t a[CAP];                         // rotations still to run on the string
+  uint32_t hash[HS];                       // LdsTab entries
   uint16_t life[CAP];
-  uint16_t hash[HS];                       // index + 1, 0 = empty
-  uint64_t px[kLayerMaxRot][WW], pz[kLayerMaxRot][WW];
-  double cs[kLayerMaxRot], sn[kLayerMaxRot];
-  unsigned long long pat;                  // rotations some string anticommutes with
+  struct Rot {
+    uint64_t p[KW];
+    double cs, sn;
+  } rot[kLayerMaxRot];
+  uint32_t steps;                          // most rotations any string of the bucket takes
   uint32_t inc[3], n0, fail, flag, tmp[NW + 1], base;
-  uint64_t red[NW][NS];
+  uint32_t red[NW][NS];
+  uint64_t fold[kAccShards][NS + 1];
 };
 
 // Per-thread sums of one instance: live before each rotation (as r *
 // entering + weighted births - drops), anticommuting, survivors, survivors
 // anticommuting with the next gate, children, strings held at the end,
 // strings entering; bad: a bucket did not fit the LDS.
+constexpr uint32_t kLayerFlush = 128;      // buckets between two flushes of a block's sums
 struct LayerSums {
-  int64_t lw = 0;
+  int32_t lw = 0;
   uint32_t an = 0, out = 0, nx = 0, ch = 0, held = 0, in = 0;
   bool bad = false;
 };
 
-template <int WW, int NB>
-__device__ __forceinline__ void load_rotations(const Op& op, ApplySh<WW, NB>& sh) {
-  load_rot_strings<WW, NB>(op, sh.px, sh.pz);
-  for (uint32_t g = threadIdx.x; g < op.nrot; g += NB) {
-    sh.cs[g] = op.table[g * kLayerRec + 2 * kMaxW];
-    sh.sn[g] = op.table[g * kLayerRec + 2 * kMaxW + 1];
+template <int KW, int NB>
+__device__ __forceinline__ void load_rotations(const double* table, uint32_t nrot,
+                                               ApplySh<KW, NB>& sh) {
+  constexpr int WW = ApplySh<KW, NB>::WW;
+  for (uint32_t g = threadIdx.x; g < nrot; g += NB) {
+    uint64_t x[WW], z[WW], k[KW];
+#pragma unroll
+    for (int w = 0; w < WW; ++w) {
+      x[w] = rot_word(table, g * kLayerRec + w);
+      z[w] = rot_word(table, g * kLayerRec + kMaxW + w);
+    }
+    const double cs = table[g * kLayerRec + 2 * kMaxW], sn = table[g * kLayerRec + 2 * kMaxW + 1];
+    lk_pack<KW>(x, z, k);
+#pragma unroll
+    for (int w = 0; w < KW; ++w) sh.rot[g].p[w] = k[w];
+    sh.rot[g].cs = cs;
+    sh.rot[g].sn = sn;
   }
 }
 
 // Bucket bk of one instance (bits: the op's bucket bits).  Every thread of
 // the block calls it; it starts with a barrier (the LDS of the previous
 // bucket, and the rotations, are then free and loaded).
-template <int WW, int NB>
-__device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const Op& op,
-                                             uint32_t bits, uint32_t bk, ApplySh<WW, NB>& sh,
+//
+// Step q runs every string's q-th own rotation: the strings of one closed set
+// anticommute with the same rotations, so they are at the same one, and sets
+// that differ need no common order.  A bucket takes as many steps as the
+// string with the most rotations, not as many as the union of all.  Pair and
+// single rotation share one path (selects instead of branches): a wave of
+// mixed lanes pays each instruction once, and the path's length is what
+// bounds the kernel (a step of one wave measured about 5 cycles per
+// instruction, LDS round trips included).  The loops over a thread's strings
+// stay rolled: a launch starts with a cold instruction cache.
+template <int KW, int NB>
+__device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const LayerArgs& op,
+                                             uint32_t bits, uint32_t bk, ApplySh<KW, NB>& sh,
                                              LayerSums& sum) {
-  constexpr int CAP = ApplySh<WW, NB>::CAP, HS = ApplySh<WW, NB>::HS;
+  using Sh = ApplySh<KW, NB>;
+  constexpr int CAP = Sh::CAP, HS = Sh::HS, WW = Sh::WW;
+  using T = LdsTab<CAP>;
   const uint32_t r = op.nrot;
   const uint32_t slots = b.lslots >> bits;
+  const uint32_t cnt = b.lcount[bk];       // (zeroed by thread 0 past the barriers)
   __syncthreads();
   if (threadIdx.x == 0) {
-    const uint32_t cnt = b.lcount[bk];
-    b.lcount[bk] = 0;                      // zero for the next layer op
-    sh.n0 = cnt < slots ? cnt : slots;
-    sh.fail = sh.n0 > (uint32_t)CAP ? 1u : 0u;
+    sh.fail = 0;
     sh.inc[0] = sh.inc[1] = sh.inc[2] = 0;
-    sh.pat = 0;
+    sh.steps = 0;
   }
-  for (int t = threadIdx.x; t < HS / 2; t += NB) reinterpret_cast<uint32_t*>(sh.hash)[t] = 0;
-  for (int t = threadIdx.x; t < CAP; t += NB) sh.life[t] = life_of(0xFF, 0);   // unused: never live
+  for (int t = threadIdx.x; t < HS / 4; t += NB)
+    reinterpret_cast<uint4*>(sh.hash)[t] = make_uint4(0, 0, 0, 0);
   __syncthreads();
-  if (sh.fail) { sum.bad = true; return; }   // uniform
-  const uint32_t n0 = sh.n0;
+  if (threadIdx.x == 0) b.lcount[bk] = 0;  // zero for the next layer op
+  const uint32_t n0 = __builtin_amdgcn_readfirstlane(cnt < slots ? cnt : slots);
+  if (n0 > (uint32_t)CAP) { sum.bad = true; return; }   // uniform
+  const double eps = op.eps;
+  const int wmax = op.wmax;
+  const bool full = op.full, f32 = b.f32 != 0;
+  if (threadIdx.x == 0) {
+    sum.in += n0;
+    sum.lw += (int32_t)(r * n0);
+  }
   {
     const size_t base = (size_t)bk * slots, L = b.lslots;
-    if (threadIdx.x == 0) sum.in += n0;
-    sum.lw += threadIdx.x == 0 ? (int64_t)r * n0 : 0;
-    uint64_t pat = 0;
+    uint32_t most = 0;
+#pragma unroll 1
     for (uint32_t j = threadIdx.x; j < n0; j += NB) {
-      uint64_t x[WW], z[WW];
+      uint64_t x[WW], z[WW], k[KW];
 #pragma unroll
       for (int q = 0; q < WW; ++q) {
         x[q] = b.lstx[(size_t)q * L + base + j];
         z[q] = b.lstz[(size_t)q * L + base + j];
-        sh.x[q][j] = x[q];
-        sh.z[q][j] = z[q];
       }
-      sh.c[j] = b.lstc[base + j];
-      pat |= b.lsta[base + j];
-      sh.life[j] = life_of(0, kAlive);
-      __threadfence_block();
-      lds_insert<WW>(sh.hash, HS, x, z, (int)j);
+      const double c = b.lstc[base + j];
+      const uint64_t a = b.lsta[base + j];
+      lk_pack<KW>(x, z, k);
+#pragma unroll
+      for (int w = 0; w < KW; ++w) sh.k[w][j] = k[w];
+      sh.c[j] = c;
+      sh.a[j] = a;
+      // the op's first rotation re-checks every string: one that commutes
+      // with it is checked here and leaves after that rotation
+      const bool drop = full && !(a & 1ull) && !(fabs(c) >= eps && !lk_heavy<KW>(k, wmax));
+      sh.life[j] = life_of(0, drop ? 0u : kAlive);
+      if (drop) sum.lw -= (int32_t)(r - 1);
+      const uint32_t h = lk_hash<KW>(k);
+      T::insert(sh.hash, h, j, T::slot(h));
+      most = max(most, (uint32_t)__popcll(a));
     }
-    for (int o = 32; o > 0; o >>= 1) pat |= __shfl_xor(pat, o, 64);
-    if ((threadIdx.x & 63) == 0 && pat) atomicOr(&sh.pat, (unsigned long long)pat);
+    most = wave_max63(most);
+    if ((threadIdx.x & 63) == 63 && most) atomicMax(&sh.steps, most);
   }
   __syncthreads();
-  const double eps = op.eps;
-  const int wmax = op.wmax;
-  const bool full = op.full_check != 0;
-  const bool f32 = b.f32 != 0;
-  uint64_t todo = sh.pat | (full ? 1ull : 0ull);
-  uint32_t ng = n0, q = 0;                 // strings before the rotation; rotations run
-  while (todo) {
-    const uint32_t g = (uint32_t)__builtin_ctzll(todo);
-    todo &= todo - 1;
+  const uint32_t steps = __builtin_amdgcn_readfirstlane(sh.steps);
+  uint32_t ng = n0;                        // strings before the step
+#pragma unroll 1
+  for (uint32_t q = 0; q < steps; ++q) {
     if (threadIdx.x == 0) sh.inc[(q + 1) % 3] = 0;
-    const bool chk = g == 0 && full;
-    const int wt = (int)(r - 1 - g);       // rotations after g (live-count weight)
-    int born_here = 0, died_here = 0;
-    uint64_t px[WW], pz[WW];               // the rotation, in registers
-#pragma unroll
-    for (int w = 0; w < WW; ++w) { px[w] = sh.px[g][w]; pz[w] = sh.pz[g][w]; }
-    const double cs = sh.cs[g], sn = sh.sn[g];
+#pragma unroll 1
     for (uint32_t j = threadIdx.x; j < ng; j += NB) {
-      // key, stamp and coefficient in one round trip (a coefficient read
-      // here is used only by a string that leads its pair or has none, and
-      // no other thread writes those)
-      uint64_t qx[WW], qz[WW];
-#pragma unroll
-      for (int w = 0; w < WW; ++w) { qx[w] = sh.x[w][j]; qz[w] = sh.z[w][j]; }
+      // (a coefficient read here is used only by a string that leads its
+      // pair or has none, and no other thread writes those)
+      const uint64_t rem = sh.a[j];
       const uint32_t life = sh.life[j];
       const double cq = sh.c[j];
-      uint32_t par = 0;
+      uint64_t qk[KW], rk[KW];
 #pragma unroll
-      for (int w = 0; w < WW; ++w) par += __popcll((qx[w] & pz[w]) ^ (qz[w] & px[w]));
-      const bool anti = par & 1u;
-      if (!anti && !chk) continue;         // untouched (and live or not, unchanged)
+      for (int w = 0; w < KW; ++w) qk[w] = sh.k[w][j];
+      if (rem == 0) continue;
+      const uint32_t g = (uint32_t)__builtin_ctzll(rem);
+      const uint64_t left = rem & (rem - 1);
+      sh.a[j] = left;
       if (!live_before(life, g)) continue;
-      if (!anti) {                         // the sub-layer's first rotation checks all
-        if (!(fabs(cq) >= eps && !layer_heavy<WW>(qx, qz, wmax))) {
-          sh.life[j] = life_of(life >> 8, g);
-          ++died_here;
+      const typename Sh::Rot rot = sh.rot[g];
+#pragma unroll
+      for (int w = 0; w < KW; ++w) rk[w] = qk[w] ^ rot.p[w];
+      const uint32_t rh = lk_hash<KW>(rk);
+      // the partner, its stamp and coefficient (read with the key compare);
+      // strings made by this step (index >= ng) are nobody's partner in it
+      const uint32_t tg = T::tagged(rh);
+      uint32_t sl = T::slot(rh), p = kNone32, plife = 0;
+      double cp = 0.0;
+#pragma unroll 1
+      for (int probe = 0; probe < HS; ++probe) {
+        const uint32_t e = T::entry(sh.hash, sl);
+        if (e == 0) break;
+        if (T::tag_is(e, tg)) {
+          const uint32_t m = T::index(e);
+          bool eq = m < ng;
+#pragma unroll
+          for (int w = 0; w < KW; ++w) eq = eq & (sh.k[w][m] == rk[w]);
+          plife = sh.life[m];
+          cp = sh.c[m];
+          if (eq) { p = m; break; }
         }
-        continue;
+        sl = (sl + 1) & (HS - 1);
       }
       ++sum.an;
-      uint64_t rx[WW], rz[WW];
-#pragma unroll
-      for (int w = 0; w < WW; ++w) { rx[w] = qx[w] ^ px[w]; rz[w] = qz[w] ^ pz[w]; }
-      const int pk = lds_find<WW>(sh.hash, HS, sh.x, sh.z, 0, rx, rz);
-      const uint32_t p = (uint32_t)pk;
-      uint32_t plife = 0;
-      double cp = 0.0;
-      if (pk >= 0) { plife = sh.life[p]; cp = sh.c[p]; }
-      const bool plive = pk >= 0 && p < ng && live_before(plife, g);
+      const bool found = p != kNone32;
+      const bool plive = found && live_before(plife, g);
       if (plive && p < j) continue;        // the partner's thread leads
-      const int sig = product_sign(px, pz, qx, qz, rx, rz, WW);   // i P Q = sig R
-      if (plive) {                         // Q and R = PQ live: a rotation of the pair
-        double nq, nr;
-        rotate_pair(f32, cs, sn, sig, cq, cp, &nq, &nr);
-        sh.c[j] = nq;
-        sh.c[p] = nr;
-        if (!(fabs(nq) >= eps && !(chk && layer_heavy<WW>(qx, qz, wmax)))) {
-          sh.life[j] = life_of(life >> 8, g);
-          ++died_here;
-        }
-        if (!(fabs(nr) >= eps && !(chk && layer_heavy<WW>(rx, rz, wmax)))) {
-          sh.life[p] = life_of(plife >> 8, g);
-          ++died_here;
-        }
-      } else {
-        double nq, child;
-        rotate_single(f32, cs, sn, sig, cq, &nq, &child);
-        sh.c[j] = nq;
-        if (!(fabs(nq) >= eps && !(chk && layer_heavy<WW>(qx, qz, wmax)))) {
-          sh.life[j] = life_of(life >> 8, g);
-          ++died_here;
-        }
-        if (fabs(child) >= eps && !layer_heavy<WW>(rx, rz, wmax)) {
-          ++sum.ch;
-          if (pk >= 0) {                   // a dropped string comes back in its slot
-            sh.c[p] = child;
-            sh.life[p] = life_of(g + 1, kAlive);
-            ++born_here;
-          } else {
-            const uint32_t k = ng + atomicAdd(&sh.inc[q % 3], 1u);
-            if (k >= (uint32_t)CAP) {
-              sh.fail = 1;
-            } else {
+      const bool chk = g == 0 && full;
+      const int sig = lk_sign<KW>(rot.p, qk, rk);   // i P Q = sig R
+      double nq, nr;                       // Q, and R = PQ: the pair's or the child's
+      rotate_any(f32, rot.cs, rot.sn, sig, plive, cq, cp, &nq, &nr);
+      const bool keep_q = fabs(nq) >= eps && !(chk && lk_heavy<KW>(qk, wmax));
+      const bool keep_r = fabs(nr) >= eps && !((chk || !plive) && lk_heavy<KW>(rk, wmax));
+      const bool born = keep_r && !plive;  // a new string, or a dropped one again
+      // live counts before the later rotations of the op (wt of them)
+      sum.lw += (int32_t)(r - 1 - g) *
+                ((born ? 1 : 0) - (keep_q ? 0 : 1) - (plive && !keep_r ? 1 : 0));
+      sum.ch += born ? 1u : 0u;
+      sh.c[j] = nq;
+      if (!keep_q) sh.life[j] = life_of(life >> 8, g);
+      if (!found && born) {
+        p = ng + atomicAdd(&sh.inc[q % 3], 1u);
+        if (p < (uint32_t)CAP) {
 #pragma unroll
-              for (int w = 0; w < WW; ++w) { sh.x[w][k] = rx[w]; sh.z[w][k] = rz[w]; }
-              sh.c[k] = child;
-              sh.life[k] = life_of(g + 1, kAlive);
-              ++born_here;
-              __threadfence_block();
-              lds_insert<WW>(sh.hash, HS, rx, rz, (int)k);
-            }
-          }
+          for (int w = 0; w < KW; ++w) sh.k[w][p] = rk[w];
+          sh.a[p] = left;
+          T::insert(sh.hash, rh, p, sl);
+        } else {
+          sh.fail = 1;
+          p = kNone32;
         }
       }
+      if (p != kNone32 && (plive || born)) {
+        sh.c[p] = nr;
+        if (born)
+          sh.life[p] = life_of(g + 1, kAlive);
+        else if (!keep_r)
+          sh.life[p] = life_of(plife >> 8, g);
+      }
     }
-    sum.lw += (int64_t)wt * (born_here - died_here);
     __syncthreads();
-    const uint32_t add = sh.inc[q % 3];
+    const uint32_t add = __builtin_amdgcn_readfirstlane(sh.inc[q % 3]);
     ng = ng + add < (uint32_t)CAP ? ng + add : (uint32_t)CAP;
-    ++q;
   }
   if (threadIdx.x == 0) sum.held += ng;
   if (sh.fail) { sum.bad = true; return; }  // uniform: read after the last barrier
-  emit_survivors<WW, NB>(b, d, op, sh.x, sh.z, sh.c, sh.life, sh.tmp, &sh.base, &sum.out, &sum.nx);
+  emit_survivors<KW, NB, CAP>(b, d, op, sh.k, sh.c, sh.life, ng, sh.tmp, &sh.base, &sum.out,
+                              &sum.nx);
 }
 
 // The block's sums of one instance to its shard line (entries 1..NS) and
-// its LDS overflow flag; resets the sums.  Every thread calls it.
-template <int WW, int NB>
-__device__ __forceinline__ void flush_sums(const InstBuf& b, InstDyn& d, ApplySh<WW, NB>& sh,
+// its LDS overflow flag; resets the sums.  Every thread calls it.  Per block
+// and instance every sum is below 2^31 (a block sees at most kLayerMaxRot
+// rotations of its buckets' strings).  The atomics have returned when the
+// threads leave, so the last block needs no fence to read their totals.
+template <int KW, int NB>
+__device__ __forceinline__ void flush_sums(const InstBuf& b, InstDyn& d, ApplySh<KW, NB>& sh,
                                            LayerSums& sum) {
-  constexpr int NS = ApplySh<WW, NB>::NS, NW = ApplySh<WW, NB>::NW;
+  constexpr int NS = ApplySh<KW, NB>::NS, NW = ApplySh<KW, NB>::NW;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const uint64_t v[NS] = {(uint64_t)sum.lw, sum.an, sum.out, sum.nx, sum.ch, sum.held, sum.in};
+  const uint32_t v[NS] = {(uint32_t)sum.lw, sum.an, sum.out, sum.nx, sum.ch, sum.held, sum.in};
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
-    uint64_t t = v[k];
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-    if (lane == 0) sh.red[wid][k] = t;
+    const uint32_t t = wave_sum63(v[k]);
+    if (lane == 63) sh.red[wid][k] = t;
   }
   __syncthreads();
   if (threadIdx.x < NS) {
-    uint64_t t = 0;
+    uint32_t t = 0;
     for (int w = 0; w < NW; ++w) t += sh.red[w][threadIdx.x];
     if (t)
-      atomicAdd((unsigned long long*)&b.accs[(blockIdx.x % kAccShards) * kLineU64 + 1 + threadIdx.x],
-                (unsigned long long)t);
+      consume(atomicAdd((unsigned long long*)&b.accs[(blockIdx.x % kAccShards) * kLineU64 + 1 + threadIdx.x],
+                        (unsigned long long)(int64_t)(int32_t)t));
   }
-  if (threadIdx.x == 0 && sum.bad) atomicOr(&d.lfail, 2u);   // a bucket overflowed the LDS
+  if (threadIdx.x == 0 && sum.bad) consume(atomicOr(&d.lfail, 2u));   // the LDS overflowed
   sum = LayerSums();
 }
 
-template <int WW, int NB>
+template <int KW, int NB>
 __global__ __launch_bounds__(NB) void k_layer_apply(Solo S) {
-  __shared__ ApplySh<WW, NB> sh;
+  using Sh = ApplySh<KW, NB>;
+  __shared__ Sh sh;
   const InstBuf& b = S.b;
   InstDyn& d = *S.d;
-  if (d.pc != S.k) return;                 // uniform: pc changes only in the last block
-  const Op& op = b.prog[S.k];
-  load_rotations<WW, NB>(op, sh);
-  const uint32_t bits = layer_bits(d.M, d.lboost, b.lmaxbits, b.lshift);
+  const Op& op = b.prog[S.k];              // S.k < prog_len
   // the scatter's failure (bit 0, set before this launch); bit 1 comes from
-  // blocks of this launch and must not steer a block's control flow
-  const bool failed = (ld_agent(&d.lfail) & 1u) != 0;
+  // blocks of this launch and must not steer a block's control flow.  The
+  // state's and the op's loads are issued together.
+  const uint32_t pc = d.pc, M = d.M, lfail = ld_agent(&d.lfail);
+  const int32_t lboost = d.lboost;
+  const LayerArgs la = layer_args(op);
+  consume((uint64_t)pc ^ M ^ lfail ^ (uint32_t)lboost ^ (uint64_t)(uintptr_t)la.table ^ la.nrot);
+  if (pc != S.k) return;                   // uniform: pc changes only in the last block
+  load_rotations<KW, NB>(la.table, la.nrot, sh);
+  const uint32_t bits = layer_bits(M, lboost, b.lmaxbits, b.lshift);
+  const bool failed = (lfail & 1u) != 0;
   LayerSums sum;
+  uint32_t done = 0;
   for (uint32_t bk = blockIdx.x; bk < (1u << bits); bk += gridDim.x) {
     if (failed) {                          // only zero the counts (uniform)
       if (threadIdx.x == 0) b.lcount[bk] = 0;
       continue;
     }
-    apply_bucket<WW, NB>(b, d, op, bits, bk, sh, sum);
+    apply_bucket<KW, NB>(b, d, la, bits, bk, sh, sum);
+    if (++done % kLayerFlush == 0) flush_sums<KW, NB>(b, d, sh, sum);
   }
-  flush_sums<WW, NB>(b, d, sh, sum);
-  if (!last_block(S.sync, &sh.flag, gridDim.x, true)) return;
-  if (threadIdx.x == 0) layer_finish(b, d, op, ApplySh<WW, NB>::NS, false);
+  flush_sums<KW, NB>(b, d, sh, sum);
+  if (!last_block(S.sync, &sh.flag, gridDim.x, false)) return;
+  // the shard lines, all at once
+  static_assert(NB >= kAccShards * 8, "one thread per shard entry");
+  if (threadIdx.x < kAccShards * 8) {
+    const uint32_t s = threadIdx.x >> 3, k = threadIdx.x & 7;
+    sh.fold[s][k] = k < (uint32_t)Sh::NS
+        ? atomicExch((unsigned long long*)&b.accs[s * kLineU64 + 1 + k], 0ull) : 0ull;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < kAccShards; ++s)
+#pragma unroll
+      for (int k = 0; k < Sh::NS; ++k) t[k] += sh.fold[s][k];
+    layer_finish(b, d, op, t, false);
+  }
 }
 
 // Block scan for NB-thread blocks over instances (as plan_tiles).
@@ -715,14 +908,14 @@ __device__ __forceinline__ uint32_t plan_tiles_n(int ninst, F tiles, uint32_t* s
 // Batched form, step 2: the buckets of every instance whose layer op step 1
 // took, dealt out to the blocks; the last block finishes those instances
 // (a bucket that did not fit sends the instance to the op's gate copies).
-template <int WW, int NB>
+template <int KW, int NB>
 __global__ __launch_bounds__(NB) void k_layer_apply_multi(Ctx C) {
   __shared__ uint32_t s_pref[kMaxInst];
-  extern __shared__ __align__(16) uint64_t s_layer_dyn[];   // sizeof(ApplySh<WW, NB>) bytes
-  ApplySh<WW, NB>& sh = *reinterpret_cast<ApplySh<WW, NB>*>(s_layer_dyn);
+  extern __shared__ __align__(16) uint64_t s_layer_dyn[];   // sizeof(ApplySh<KW, NB>) bytes
+  ApplySh<KW, NB>& sh = *reinterpret_cast<ApplySh<KW, NB>*>(s_layer_dyn);
   const int ninst = *C.ninst;
   auto served = [&](int i) {
-    return C.bufs[i]->W == WW && ld_agent(&C.dyns[i]->lserved) != 0;
+    return C.bufs[i]->W == ApplySh<KW, NB>::WW && ld_agent(&C.dyns[i]->lserved) != 0;
   };
   const uint32_t total = plan_tiles_n<NB>(ninst, [&](int i) -> uint32_t {
     if (!served(i)) return 0u;
@@ -731,6 +924,8 @@ __global__ __launch_bounds__(NB) void k_layer_apply_multi(Ctx C) {
     return 1u << layer_bits(d.M, d.lboost, b.lmaxbits, b.lshift);
   }, s_pref, sh.tmp);
   LayerSums sum;
+  LayerArgs la{};
+  uint32_t done = 0;
   int cur = -1;
   for (uint32_t t = blockIdx.x; t < total; t += gridDim.x) {
     const int i = find_inst(s_pref, ninst, t);
@@ -738,9 +933,10 @@ __global__ __launch_bounds__(NB) void k_layer_apply_multi(Ctx C) {
     InstDyn& d = *C.dyns[i];
     const Op& op = b.prog[d.pc];
     if (i != cur) {
-      if (cur >= 0) flush_sums<WW, NB>(*C.bufs[cur], *C.dyns[cur], sh, sum);
+      if (cur >= 0) flush_sums<KW, NB>(*C.bufs[cur], *C.dyns[cur], sh, sum);
       __syncthreads();                     // the last bucket's rotations are read
-      load_rotations<WW, NB>(op, sh);
+      la = layer_args(op);
+      load_rotations<KW, NB>(la.table, la.nrot, sh);
       cur = i;
     }
     const uint32_t bits = layer_bits(d.M, d.lboost, b.lmaxbits, b.lshift);
@@ -749,16 +945,21 @@ __global__ __launch_bounds__(NB) void k_layer_apply_multi(Ctx C) {
       if (threadIdx.x == 0) b.lcount[bk] = 0;
       continue;
     }
-    apply_bucket<WW, NB>(b, d, op, bits, bk, sh, sum);
+    apply_bucket<KW, NB>(b, d, la, bits, bk, sh, sum);
+    if (++done % kLayerFlush == 0) flush_sums<KW, NB>(b, d, sh, sum);
   }
-  if (cur >= 0) flush_sums<WW, NB>(*C.bufs[cur], *C.dyns[cur], sh, sum);
+  if (cur >= 0) flush_sums<KW, NB>(*C.bufs[cur], *C.dyns[cur], sh, sum);
   if (!last_block(C.sync, &sh.flag, gridDim.x, true)) return;
   for (int i = threadIdx.x; i < ninst; i += NB) {
     if (!served(i)) continue;
     const InstBuf& b = *C.bufs[i];
     InstDyn& d = *C.dyns[i];
     d.lserved = 0;
-    layer_finish(b, d, b.prog[d.pc], ApplySh<WW, NB>::NS, true);
+    uint64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int q = 0; q < kAccShards; ++q)
+      for (int k = 0; k < ApplySh<KW, NB>::NS; ++k)
+        t[k] += atomicExch((unsigned long long*)&b.accs[q * kLineU64 + 1 + k], 0ull);
+    layer_finish(b, d, b.prog[d.pc], t, true);
   }
 }
 

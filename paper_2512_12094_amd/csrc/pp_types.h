@@ -120,15 +120,21 @@ constexpr int kPartProbe = 64;       // probes before the LDS table refuses a ke
 //   2. apply: one block per bucket runs the r rotations with the exact
 //      merge and truncation after each, then writes the survivors to the
 //      other half of the store.
-// Within a bucket each wave takes whole groups (by the key's hash; strings
-// that commute with every rotation anywhere), so a wave rotates its strings
-// with no barrier between rotations and skips the rotations none of them
-// anticommutes with.  A bucket that does not fit its staging slots or a
-// wave's share of the LDS fails the op; the host then retries it with more
-// buckets, then falls back to the op's GATE(S) copies.
+// Within a bucket step q runs every string's q-th own rotation, so a bucket
+// takes as many steps as its string with the most rotations.  A bucket that
+// does not fit its staging slots or the LDS fails the op; the host then
+// retries it with another bucket count, then falls back to the op's GATE(S)
+// copies.
 constexpr int kLayerMaxRot = 64;
 constexpr int kLayerMinRot = 4;
 constexpr int kLayerShift = 8;        // strings per bucket aimed at: 2^8 (default)
+// Sets too small to fill the CUs with such buckets use up to 2^8 buckets (one
+// per CU) of at least 2^5 strings: a bucket's time goes with the strings per
+// thread in it.  2^9 buckets measured 4% slower on the Z_32 ring (each block
+// reserves its output with one atomic on one address), 2^8 of 2^8 strings
+// only (8 blocks on 2048 strings) 40% slower on the Z_8 ring's launches.
+constexpr int kLayerFillBits = 8;
+constexpr int kLayerFine = 5;
 constexpr int kLayerMaxBits = 20;
 constexpr int kLayerMinSlots = 64;    // staging slots per bucket, at least
 constexpr int kLayerMaxBoost = 3;     // bucket bits added or taken after failures
@@ -197,7 +203,6 @@ struct InstBuf {
   uint64_t* lstz;        // [W][lslots] staged z words
   double* lstc;          // [lslots] staged coefficients (exact in FP64)
   uint64_t* lsta;        // [lslots] staged anticommutation patterns (bit g: P_g)
-  uint32_t* lsth;        // [lslots] staged low 32 bits of the bucket key's hash
   uint32_t* lcount;      // [2^lmaxbits] strings per bucket (zero between ops)
   uint32_t lslots;       // staging slots (a power of two)
   uint32_t lmaxbits;     // largest bucket bits (lslots >> lmaxbits >= kLayerMinSlots)

@@ -186,3 +186,23 @@ def test_failed_layer_op_keeps_the_gate_table(gpu):
     forced = run(gpu, prog, 2)
     same(forced, off, "forced fallbacks vs gate launches")
     same(run(gpu, prog, 1), off, "layer ops vs gate launches")
+
+
+# (qubits, rotations, does the closed set of 2^rotations strings fit a block):
+# one, two and four key words, at and past each width's LDS capacity
+@pytest.mark.parametrize("n,k,fits", [(12, 10, True), (12, 11, True), (12, 12, False),
+                                      (40, 10, True), (40, 11, False),
+                                      (80, 10, True), (80, 11, False)])
+def test_closed_set_at_the_block_capacity(gpu, n, k, fits):
+    """X rotations on k qubits of the one string Z...Z make 2^k strings in
+    one closed set; then Z rotations, so every string meets its partners
+    again.  Bitwise the gate launches, through the layer op where the set
+    fits a block, else through the copies."""
+    xs = [W.Gate(1 << q, 0, 0.3 + 0.01 * q) for q in range(k)]
+    zs = [W.Gate(0, 1 << q, 0.2 + 0.02 * q) for q in range(k)]
+    prog = W.Program(f"field{n}_{k}", n, "none", [(0, (1 << k) - 1, 1.0)],
+                     [W.SubLayer(xs), W.SubLayer(xs[::-1]), W.SubLayer(zs)], W.ZERO_STATE, {})
+    print(f"[case] closed set of 2^{k}, n = {n}", flush=True)
+    on = run(gpu, prog, 1)
+    same(on, run(gpu, prog, 0), prog.name)
+    assert (on["stats"]["fallbacks"] == 0) == fits, on["stats"]
