@@ -985,6 +985,7 @@ struct GateArgs {
   double cs[kMaxFuse], sn[kMaxFuse], eps;
   int wmax;
   uint32_t type, nrot;
+  uint32_t idle[kMaxFuse - 1];                         // rotations left out after 1..nrot-1
   bool full, has_next;
 };
 
@@ -1013,6 +1014,8 @@ __device__ __forceinline__ GateArgs gate_args(const Op& op) {
   g.wmax = op.wmax;
   g.type = op.type;
   g.nrot = op.type == OP_GATES ? op.nrot : 1u;
+#pragma unroll
+  for (int r = 0; r < kMaxFuse - 1; ++r) g.idle[r] = op.idle[r];
   g.full = op.full_check != 0;
   g.has_next = op.next_gate != kNone32;
   return g;
@@ -1298,6 +1301,8 @@ __device__ __forceinline__ void gates_tile(const InstBuf& b, InstDyn& d, const G
           v.aln[i] = keep ? 1 : 0;
           if (keep) {
             my_lv += K - 1;
+#pragma unroll
+            for (int g = 0; g < K - 1; ++g) my_lv += ga.idle[g];
             tally(mx[0], mz[0]);
           }
         } else {
@@ -1374,7 +1379,7 @@ __device__ __forceinline__ void gates_tile(const InstBuf& b, InstDyn& d, const G
 #pragma unroll
           for (int m = 0; m < NM; ++m)
             if (pres[m]) {
-              ++my_lv;
+              my_lv += 1 + ga.idle[g < K - 1 ? g : 0];
               if (an[g + 1 < K ? g + 1 : 0]) ++my_an;
             }
       }
@@ -1496,6 +1501,8 @@ __device__ __forceinline__ void gates_lane_tile(const InstBuf& b, InstDyn& d, co
         v.aln[i] = keep ? 1 : 0;
         if (keep) {
           my_lv += K - 1;
+#pragma unroll
+          for (int g = 0; g < K - 1; ++g) my_lv += ga.idle[g];
           tally(qx, qz);
         }
       }
@@ -1550,7 +1557,7 @@ __device__ __forceinline__ void gates_lane_tile(const InstBuf& b, InstDyn& d, co
           }
         }
         if (g < K - 1 && pres) {
-          ++my_lv;
+          my_lv += 1 + ga.idle[g < K - 1 ? g : 0];
           if (an[g + 1 < K ? g + 1 : 0]) ++my_an;
         }
       }
@@ -1699,6 +1706,9 @@ struct GateKindT {
     if (d.M > d.peak) d.peak = d.M;
     d.parity ^= 1u;
     take_acc(d);
+    const uint64_t idle = (uint64_t)op.idle[rotations_of(op) - 1] * d.live;
+    d.propagated += idle;
+    d.merged += idle;
     d.count_for = op.next_gate;
     next_op(b, d);
   }
@@ -2122,6 +2132,11 @@ struct ScanKind {
       d.gstale = 0;
     }
     take_acc(d);
+    if (op.type == OP_COUNT) {
+      const uint64_t idle = (uint64_t)op.idle[0] * d.live;
+      d.propagated += idle;
+      d.merged += idle;
+    }
     d.count_for = op.next_gate;
     next_op(b, d);
   }
@@ -2408,6 +2423,54 @@ __global__ __launch_bounds__(kBlock) void k_grow(InstBuf src, InstBuf dst, InstD
 }
 
 __global__ void k_set_pc(InstDyn* d, uint32_t pc) { d->pc = pc; }
+
+// Which of nrot rotations (LAYER table records) some live term anticommutes
+// with: bit g of mask, which the caller cleared.  A block takes a tile of
+// kBlock terms into LDS and a group of kBlock rotations, one per thread, which
+// looks through the tile until it meets a term (the terms are read by all
+// lanes at once, and a rotation found active by another block is skipped).
+template <int WW>
+__global__ __launch_bounds__(kBlock) void k_active(InstBuf b, const InstDyn* dp,
+                                                   const double* table, uint32_t nrot,
+                                                   unsigned long long* mask) {
+  __shared__ uint64_t sx[WW][kBlock], sz[WW][kBlock];
+  __shared__ uint32_t s_n;
+  const InstDyn& d = *dp;
+  const View v = view_of(b, d);
+  const uint32_t M = d.M, g = blockIdx.y * kBlock + threadIdx.x;
+  uint64_t px[WW], pz[WW];
+#pragma unroll
+  for (int w = 0; w < WW; ++w) {
+    px[w] = g < nrot ? (uint64_t)__double_as_longlong(table[g * kLayerRec + w]) : 0ull;
+    pz[w] = g < nrot ? (uint64_t)__double_as_longlong(table[g * kLayerRec + kMaxW + w]) : 0ull;
+  }
+  bool act = false;
+  for (uint32_t t = blockIdx.x; t * kBlock < M; t += gridDim.x) {
+    act = act || g >= nrot || ((ld_agent((const uint64_t*)&mask[g >> 6]) >> (g & 63)) & 1ull);
+    if (__syncthreads_and(act)) break;           // also: the last tile is read
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const uint32_t i = t * kBlock + threadIdx.x;
+    if (i < M && v.al[i]) {
+      const uint32_t k = atomicAdd(&s_n, 1u);
+#pragma unroll
+      for (int w = 0; w < WW; ++w) {
+        sx[w][k] = v.X[(size_t)w * v.cap + i];
+        sz[w][k] = v.Z[(size_t)w * v.cap + i];
+      }
+    }
+    __syncthreads();
+    const uint32_t n = s_n;
+    for (uint32_t k = 0; k < n && !act; ++k) {
+      uint32_t par = 0;
+#pragma unroll
+      for (int w = 0; w < WW; ++w) par += __popcll((sx[w][k] & pz[w]) ^ (sz[w][k] & px[w]));
+      act = par & 1u;
+    }
+    const uint64_t m = __ballot(act && g < nrot);
+    if ((threadIdx.x & 63) == 0 && m) atomicOr(&mask[g >> 6], (unsigned long long)m);
+  }
+}
 
 // Copies the per-instance dynamic state into one contiguous buffer (host
 // polling of a batch with one transfer).

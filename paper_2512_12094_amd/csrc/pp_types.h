@@ -165,6 +165,9 @@ struct Op {
   double qcs[kMaxFuse - 1], qsn[kMaxFuse - 1];
   uint64_t nx[kMaxW];    // the next gate op's (first) rotation, when next_gate
   uint64_t nz[kMaxW];    // != kNone32 (its anticommutation count is tallied here)
+  uint32_t idle[kMaxFuse];   // GATE(S): rotations left out after each of the op's
+                             // (COUNT: before the first): no live term
+                             // anticommutes with them; they only count as tested
   double eps;            // GATE/TRUNC: coefficient threshold (0: off)
   const double* table;   // DAMP: (1-p)^w for w = 0..n;
                          // EXPECT: bx^k, by^k, bz^k for k = 0..n (3 blocks);

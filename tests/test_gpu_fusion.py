@@ -218,3 +218,51 @@ def test_fusion_needs_independent_strings(gpu):
     assert info["gates"] == 18 and info["gate_launches"] == 9, info
     res = run_program(gpu, prog, 3)
     same(res, run_program(gpu, prog, 1), "s4")
+
+
+def _wide_programs():
+    """Sub-layers of more than 64 commuting rotations: few of them active
+    (all-to-all from one-letter strings), all active (a later torus layer),
+    the first one inactive, two key words, noise before them, a weight limit
+    that the re-check of the first rotation enforces, the merge deferred to a
+    truncation."""
+    deferred = W.heisenberg_all_to_all(13, 1, 0.05, obs=W.sum_single(13, "Z"), eps=1e-4)
+    for s in deferred.sublayers[1:]:
+        s.merge = False
+    pairs = [W.Gate(*W.two_site("X", a, b), 0.2) for a in range(12, -1, -1) for b in range(a)]
+    late = W.Program("late", 13, "none", [(0, 1, 1.0), (0, 0b111, 0.5), (0b11, 0, 0.25)],
+                     [W.SubLayer(pairs, eps=1e-5, wmax=4), W.SubLayer(pairs, eps=1e-3, wmax=2)],
+                     W.ZERO_STATE, {})
+    return {
+        "s12": W.heisenberg_all_to_all(12, 1, 0.05, obs=W.sum_single(12, "Z"), eps=1e-4),
+        "s70_two_words": prefix(W.heisenberg_all_to_all(70, 1, 0.02, p=1e-3,
+                                                        obs=W.sum_single(70, "Z"), eps=1e-3), 2),
+        "torus_4x4": W.power_law_xxz_torus(4, 4, 1, 0.1, delta=-1.8, obs=W.sum_single(16, "Z"),
+                                           eps=1e-3),
+        "late": late,
+        "deferred": deferred,
+    }
+
+
+@pytest.mark.parametrize("name", sorted(_wide_programs()))
+def test_wide_sublayer_runs_its_active_rotations(gpu, name):
+    """The one-instance path leaves out the rotations no term anticommutes
+    with; the batched form launches them all.  Sets, coefficients, expectation
+    and work counters agree bitwise."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    prog = _wide_programs()[name]
+    assert max(len(s.gates) for s in prog.sublayers) > 64
+    print(f"[case] wide sub-layers {name}", flush=True)
+    dp = driver.DeviceProgram(prog)
+    sets = [driver.PauliSet.from_program(prog, None, gpu["handle"], gpu["alloc"])
+            for _ in range(3)]
+    solo = float(L.pp_batch_run([sets[0].h], [dp.h], gpu["handle"])[0])
+    both = L.pp_batch_run([s.h for s in sets[1:]], [dp.h] * 2, gpu["handle"])
+    for s, e in zip(sets[1:], both):
+        assert float(e) == solo
+        assert s.as_dict() == sets[0].as_dict()
+        assert s.counters() == sets[0].counters()
+    for s in sets:
+        s.close()
+    dp.close()
