@@ -484,11 +484,11 @@ int pp_set_gate_fusion(int max_rotations, int lanes);
  * as the gate launches.  Results, expectations and the propagated / merged
  * counters equal those with layer ops off, bitwise.  A bucket that does not
  * fit its staging slots or the block's LDS makes the op run again with
- * twice the buckets, then as its fused gate launches; after eight such
- * fallbacks a handle runs the gate launches throughout.  One-instance
- * programs only (pp_batch_run / pp_batch_step with one instance, and
- * promoted instances); the batched steps run the gate launches.  The store
- * then also carries (16W + 8) bytes of staging per entry.  mode 0: off,
+ * another bucket count, then as its fused gate launches; after three such
+ * fallbacks a handle runs the gate launches throughout.  Programs built from
+ * now on have them, and pp_apply_layer calls made from now on run them.  The
+ * store then also carries (16W + 16) bytes of staging per entry (four times
+ * that in stores of at most 2^17 entries).  mode 0: off,
  * 1: on (default), 2: on, but every layer op reports a failure (tests of the
  * fallback path).  Other modes: PP_EINVAL.
  */

@@ -759,6 +759,8 @@ int launch_ops(pp_state* s, const std::vector<Op>& ops, size_t from) {
 // overflow.
 using TabRefs = std::vector<std::pair<size_t, size_t>>;   // (op index, table offset)
 
+int layer_failed(pp_state* s, const Op* ops, size_t len);
+
 int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
             const TabRefs& refs, bool nosync) {
   if (ops.empty()) return PP_OK;
@@ -768,6 +770,8 @@ int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
   s->buf.prog = s->d_ops;
   s->buf.prog_len = (uint32_t)ops.size();
   s->buf.nopart = 0;
+  s->buf.nolayer = s->layer_off ? 1u : 0u;
+  s->fb_lo = s->fb_hi = 0;
   s->batch_prog = nullptr;
   s->run_ops_list = &ops;
   struct Reset {
@@ -801,7 +805,7 @@ int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
   hipLaunchKernelGGL(k_set_pc, dim3(1), dim3(1), 0, s->stream, s->d_dyn, 0u);
   if ((rc = launch_ops(s, ops, 0))) return rc;
   bool can_overflow = false;
-  for (const auto& op : ops) can_overflow |= op.type == OP_GATE || op.type == OP_GATES || op.type == OP_MERGE;
+  for (const auto& op : ops) can_overflow |= op.type == OP_GATE || op.type == OP_GATES || op.type == OP_LAYER || op.type == OP_MERGE;
   if (nosync && !can_overflow) return PP_OK;
   for (int guard = 0; guard < 1000; ++guard) {
     if ((rc = read_dyn(s))) return rc;
@@ -825,6 +829,9 @@ int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
       s->h_dyn->status &= ~ST_OVERFLOW;
       HIP_TRY(hipMemcpyAsync(&s->d_dyn->status, &s->h_dyn->status, sizeof(uint32_t),
                              hipMemcpyHostToDevice, s->stream));
+    }
+    if (s->h_dyn->status & ST_LAYER) {
+      if ((rc = layer_failed(s, ops.data(), ops.size()))) return rc;
     }
     if ((rc = launch_ops(s, ops, s->h_dyn->pc))) return rc;
   }
@@ -1573,10 +1580,11 @@ int txn_rollback(pp_state* s, int rc) {
 }
 
 // Runs ops as one transaction: on any error the handle is restored.
-int run_ops_txn(pp_state* s, const std::vector<Op>& ops) {
+int run_ops_txn(pp_state* s, const std::vector<Op>& ops, const std::vector<double>& tab = {},
+                const TabRefs& refs = {}) {
   int rc = txn_begin(s);
   if (rc) return rc;
-  rc = run_ops(s, ops, {}, {}, false);
+  rc = run_ops(s, ops, tab, refs, false);
   if (rc) return txn_rollback(s, rc);
   txn_end(s);
   return PP_OK;
@@ -1600,7 +1608,6 @@ int pp_apply_layer(pp_state* s, const uint64_t* gate_x, const uint64_t* gate_z,
   if (rc) return rc;
   std::vector<Op> ops;
   ops.reserve(n_gates + 1);
-  ops.push_back(make_op(OP_COUNT));
   for (size_t k = 0; k < n_gates; ++k) {
     Op op = make_op(OP_GATE);
     for (int w = 0; w < W; ++w) {
@@ -1614,9 +1621,19 @@ int pp_apply_layer(pp_state* s, const uint64_t* gate_x, const uint64_t* gate_z,
     op.full_check = k == 0;
     ops.push_back(op);
   }
-  fuse_gates(ops, 1, W, g_fuse);
+  // a layer op where a program would have one (sub-layers of 32 rotations on
+  // the Z_32 ring: 203 us a call as gate launches, 104 us as a layer op), else
+  // gate launches; both start their gates with a recount, which also enters
+  // the set into a gate table that an earlier layer op left stale
+  std::vector<double> tab;
+  TabRefs refs;
+  if (!s->layer_off) add_layer_op(ops, 0, ops.size(), W, tab, refs, false);
+  if (ops[0].type != OP_LAYER) {
+    fuse_gates(ops, 0, W, g_fuse);
+    ops.insert(ops.begin(), make_op(OP_COUNT));
+  }
   set_next_gates(ops);
-  return run_ops_txn(s, ops);
+  return run_ops_txn(s, ops, tab, refs);
 }
 
 int pp_merge_canonicalize(pp_state* s) {

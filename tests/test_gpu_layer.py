@@ -206,3 +206,34 @@ def test_closed_set_at_the_block_capacity(gpu, n, k, fits):
     on = run(gpu, prog, 1)
     same(on, run(gpu, prog, 0), prog.name)
     assert (on["stats"]["fallbacks"] == 0) == fits, on["stats"]
+
+
+PER_CALL = {k: CASES[k] for k in ("c1_z8", "dn_12", "noise_z16", "wide_z48", "two_words_n80",
+                                  "ising_z10_layer_merge")}
+# closed sets that do not fit: the handle gives layer ops up on the way
+PER_CALL["s10"] = lambda: W.heisenberg_all_to_all(10, 2, 0.3, obs=W.total_spin_squared(10))
+
+
+@pytest.mark.parametrize("name", sorted(PER_CALL))
+def test_per_call_layers_equal_gate_launches(gpu, name):
+    """pp_apply_layer runs a layer op where a program has one: bitwise the
+    gate launches, also when every op falls back to its copies, and with
+    calls that read the set between layers."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    prog = PER_CALL[name]()
+    print(f"[case] per-call layers {name}", flush=True)
+    out = {}
+    for mode in (0, 1, 2):
+        L.pp_set_layer_ops(mode)
+        try:
+            ps = driver.PauliSet.from_program(prog, None, gpu["handle"], gpu["alloc"])
+            sizes = driver.run_layers(ps, driver.heisenberg_layers(prog), record_sizes=True)
+            out[mode] = (sizes, ps.as_dict(), ps.expectation(prog.bloch), ps.counters())
+            st = L.pp_layer_stats(ps.h)
+            ps.close()
+        finally:
+            L.pp_set_layer_ops(1)
+        assert (st["layer_ops"] > 0) == (mode == 1), (mode, st)
+    assert out[1] == out[0]
+    assert out[2] == out[0]
