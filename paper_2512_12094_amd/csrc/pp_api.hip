@@ -440,6 +440,7 @@ using SoloFn = void (*)(Solo);
 // reserves its appended strings with one atomic on the instance's cursor,
 // and those atomics serialise, so fewer, larger tiles run faster there.
 constexpr uint32_t kBigSet = 1u << 19;
+constexpr int kOutBlocks = 512;   // collect and compaction: one output reservation per block
 constexpr int kBigItems = 4;
 
 int gate_items(bool big) { return big ? std::max(g_tune.gate_items, kBigItems) : g_tune.gate_items; }
@@ -482,8 +483,8 @@ SoloFn solo_of(int kind, bool big, uint32_t nrot = 1, int lane_it = 0, int group
     case PP_K_MERGE_NARROW: return PP_PICK(k_merge_narrow_solo, si);
     case PP_K_MERGE_WIDE1: return PP_PICK(k_merge_wide1_solo, si);
     case PP_K_MERGE_WIDE2: return PP_PICK(k_merge_wide2_solo, si);
-    case PP_K_MERGE_COLLECT: return PP_PICK(k_merge_collect_solo, si);
-    case PP_K_COMPACT: return PP_PICK(k_compact_solo, si);
+    case PP_K_MERGE_COLLECT: return &k_merge_collect_solo;
+    case PP_K_COMPACT: return &k_compact_solo;
     case PP_K_PART_HIST: return part_hist_of(group);
     case PP_K_PART_SCAN: return &k_part_scan;
     case PP_K_PART_SCATTER: return &k_part_scatter;
@@ -719,6 +720,8 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
       const uint32_t nrot = ops[k].type == OP_GATES ? ops[k].nrot : 1u;
       const int lane_it = kind == PP_K_GATE && !big ? lane_items(s->m_hint, nrot) : 0;
       int grid = is_part_kind(kind) ? part_grid(s->buf, kind)
+                 : kind == PP_K_MERGE_COLLECT || kind == PP_K_COMPACT
+                     ? std::min(launch_blocks(elems, kOutU), kOutBlocks)
                  : lane_it            ? launch_blocks(elems << nrot, lane_it)
                                       : launch_blocks(elems, items_of(kind, big));
       if (kind == PP_K_LAYER_APPLY) {       // about two blocks per bucket of the last size seen
@@ -842,6 +845,7 @@ Op make_op(uint32_t type) {
   Op op;
   std::memset(&op, 0, sizeof(op));
   op.type = type;
+  op.no_gtab = type == OP_MERGE ? 1u : 0u;
   op.nrot = type == OP_GATE ? 1u : 0u;
   op.next_gate = kNone32;
   op.wmax = -1;
@@ -898,10 +902,10 @@ bool all_commute(const std::vector<Op>& ops, size_t from, size_t to, int W) {
 // kLayerMaxRot pairwise commuting rotations, a LAYER op carrying them (its
 // rotation table appended to `tab`) is put in front of them and they become
 // its fallback copies.
-// `table_ok`: the gate table holds the set the sub-layer starts from; if not
-// (a LAYER op's unmerged output), the copies start with an OP_COUNT.
+// The copies start with an OP_COUNT: what comes before a LAYER op leaves the
+// gate table stale.
 void add_layer_op(std::vector<Op>& ops, size_t from, size_t to_gate_end, int W,
-                  std::vector<double>& tab, TabRefs& refs, bool table_ok) {
+                  std::vector<double>& tab, TabRefs& refs) {
   if (!g_layer) return;
   const size_t r = to_gate_end - from;
   if (r < (size_t)kLayerMinRot || r > (size_t)kLayerMaxRot) return;
@@ -919,7 +923,7 @@ void add_layer_op(std::vector<Op>& ops, size_t from, size_t to_gate_end, int W,
   refs.push_back({from, tab.size()});
   for (size_t a = from; a < to_gate_end; ++a) append_rotation(tab, ops[a]);
   fuse_gates(ops, from, W, g_fuse);
-  if (!table_ok) ops.insert(ops.begin() + from, make_op(OP_COUNT));
+  ops.insert(ops.begin() + from, make_op(OP_COUNT));
   for (size_t a = from; a < ops.size(); ++a) ops[a].fallback = 1;
   layer.skip = (uint32_t)(ops.size() - from);
   ops.insert(ops.begin() + from, layer);
@@ -1627,7 +1631,7 @@ int pp_apply_layer(pp_state* s, const uint64_t* gate_x, const uint64_t* gate_z,
   // the set into a gate table that an earlier layer op left stale
   std::vector<double> tab;
   TabRefs refs;
-  if (!s->layer_off) add_layer_op(ops, 0, ops.size(), W, tab, refs, false);
+  if (!s->layer_off) add_layer_op(ops, 0, ops.size(), W, tab, refs);
   if (ops[0].type != OP_LAYER) {
     fuse_gates(ops, 0, W, g_fuse);
     ops.insert(ops.begin(), make_op(OP_COUNT));
@@ -2012,7 +2016,7 @@ int pp_program_create(pp_program** out, int n_qubits, size_t n_sub, const size_t
       for (const Op& g : wd.gates) append_rotation(tab, g);
       p->wide.push_back(std::move(wd));
     }
-    add_layer_op(ops, first_gate, gates_end, W, tab, refs, table_ok);
+    add_layer_op(ops, first_gate, gates_end, W, tab, refs);
     const bool layered = has_gates && ops[first_gate].type == OP_LAYER;
     if (has_gates && !layered) {
       fuse_gates(ops, first_gate, W, g_fuse);
@@ -2052,6 +2056,15 @@ int pp_program_create(pp_program** out, int n_qubits, size_t n_sub, const size_t
     }
   }
   set_next_gates(ops);
+  // gates that directly follow a merge look their partners up in its table
+  for (size_t k = 0; k < ops.size(); ++k) {
+    if (ops[k].type != OP_MERGE) continue;
+    size_t q = k + 1;
+    while (q < ops.size() && ops[q].type != OP_GATE && ops[q].type != OP_GATES &&
+           ops[q].type != OP_LAYER && ops[q].type != OP_COUNT)
+      ++q;
+    if (q < ops.size() && (ops[q].type == OP_GATE || ops[q].type == OP_GATES)) ops[k].no_gtab = 0;
+  }
   for (const auto& op : ops) p->has_layer = p->has_layer || op.type == OP_LAYER;
   if (hipMalloc((void**)&p->d_ops, sizeof(Op) * ops.size()) != hipSuccess ||
       hipMalloc((void**)&p->d_tab, sizeof(double) * std::max<size_t>(tab.size(), 1)) !=

@@ -680,7 +680,7 @@ __global__ __launch_bounds__(kPABlock) void k_part_agg(Solo S) {
       if (pos >= b.cap) { atomicOr(&d.status, ST_OVERFLOW); continue; }
       uint64_t x[kMaxW], z[kMaxW];
       narrow_decode(b, unmix64(s_key[s]), x, z);
-      emit_term(b, d, pos, x, z, val[k]);
+      emit_term(b, d, pos, x, z, val[k], !mop.no_gtab);
       if (ng.anti(x, z, b.W)) ++cnt;
     }
     uint32_t tl, tc;

@@ -151,6 +151,9 @@ struct Op {
   uint32_t force_full;   // MERGE with group NONE: merge duplicates (creation)
   uint32_t trunc;        // MERGE: emit only terms passing eps / wmax (the
                          // sub-layer's truncation, folded into the merge)
+  uint32_t no_gtab;      // MERGE: its output gets no gate-table entries (a layer
+                         // op or nothing comes next; every list of gates that
+                         // may follow starts with a COUNT, which enters the set)
   uint32_t fallback;     // GATE(S): copy of a LAYER op's rotations, run only
                          // after that op failed
   uint32_t nrot;         // GATE: 1; GATES, LAYER: rotations in the op
@@ -275,7 +278,8 @@ struct InstDyn {
   uint32_t lfail;        // layer op: a bucket overflowed its slots or the LDS
   uint32_t lneed;        // layer op: survivors of an op whose output did not fit
   uint32_t gstale;       // the gate table does not hold the current set (a LAYER
-                         // op wrote it); cleared by whatever enters the set again
+                         // op or a MERGE with no_gtab wrote it); cleared by
+                         // whatever enters the set again
 };
 
 }  // namespace pp
