@@ -127,6 +127,7 @@ struct pp_state {
   uint32_t txn_m = 0, txn_half = 0, txn_parity = 0;
   bool shrunk = false;                 // a finished batched instance's store was compacted
   bool layer_used = false;             // layer ops ran: stores carry their staging
+  bool layer_big = false;              // layer ops run with 1024-thread blocks
   bool layer_off = false;              // layer ops failed too often: their fallbacks run
   int layer_fallbacks = 0;             // layer ops that fell back (this handle)
   size_t fb_lo = 0, fb_hi = 0;         // fallback ops [fb_lo, fb_hi) that launch_range runs
@@ -493,9 +494,12 @@ SoloFn solo_of(int kind, bool big, uint32_t nrot = 1, int lane_it = 0, int group
   }
 }
 
-SoloFn layer_of(int kind, int n, int W) {
+SoloFn layer_of(int kind, int n, int W, bool big) {
   if (kind == PP_K_LAYER_SCATTER) return W == 1 ? &k_layer_scatter<1> : &k_layer_scatter<2>;
   const int kw = layer_key_words(n, W);
+  if (big)
+    return kw == 1 ? &k_layer_apply<1, 1024> : kw == 2 ? &k_layer_apply<2, 1024>
+                                                       : &k_layer_apply<4, 1024>;
   if (g_tune.layer_block == 256)
     return kw == 1 ? &k_layer_apply<1, 256> : kw == 2 ? &k_layer_apply<2, 256>
                                                       : &k_layer_apply<4, 256>;
@@ -731,7 +735,7 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
       }
       const int block = kind == PP_K_PART_SCAN ? kPCBlock
                         : kind == PP_K_PART_AGG ? kPABlock
-                        : kind == PP_K_LAYER_APPLY ? g_tune.layer_block
+                        : kind == PP_K_LAYER_APPLY ? (s->layer_big ? 1024 : g_tune.layer_block)
                         : is_part_kind(kind)    ? kPHBlock
                                                 : kBlock;
       Solo S;
@@ -741,7 +745,7 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
       S.sync = s->d_sync;
       S.k = (uint32_t)k;
       if (layer)
-        hipLaunchKernelGGL(layer_of(kind, s->n, s->W), dim3(grid), dim3(block), 0, s->stream, S);
+        hipLaunchKernelGGL(layer_of(kind, s->n, s->W, s->layer_big), dim3(grid), dim3(block), 0, s->stream, S);
       else
         hipLaunchKernelGGL(solo_of(kind, big, nrot, lane_it, s->group), dim3(grid), dim3(block),
                            part_lds(s->buf, kind), s->stream, S);
@@ -762,7 +766,7 @@ int launch_ops(pp_state* s, const std::vector<Op>& ops, size_t from) {
 // overflow.
 using TabRefs = std::vector<std::pair<size_t, size_t>>;   // (op index, table offset)
 
-int layer_failed(pp_state* s, const Op* ops, size_t len);
+int layer_failed(pp_state* s, const Op* ops, size_t len, bool grew = false);
 
 int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
             const TabRefs& refs, bool nosync) {
@@ -2223,14 +2227,17 @@ int ensure_graph(BatchCtx* b) {
 // leaves a batch at a step boundary) instead of starting the program.
 // A layer op at pc reported a bucket that did not fit (ST_LAYER; h_dyn is
 // fresh and the device idles behind it): grow a crowded store, else run it
-// again with fewer buckets (staging slots overflowed) or more (the LDS
-// did), at most kLayerRetries times, else run its GATE(S) copies instead.
+// again with fewer buckets (staging slots overflowed), with larger blocks and
+// then more buckets (the LDS overflowed), at most kLayerRetries times, else
+// run its GATE(S) copies instead.  Larger blocks stay for the handle: closed
+// sets that outgrow 2048 strings come back in later sub-layers, and on sets
+// that fit either they cost 3%.
 // After kLayerGiveUp fallbacks the handle runs the copies in place of every
 // layer op.
 constexpr int kLayerGiveUp = 3;
 constexpr int kLayerRetries = 2;   // runs again with other bucket counts before a fallback
 
-int layer_failed(pp_state* s, const Op* ops, size_t len) {
+int layer_failed(pp_state* s, const Op* ops, size_t len, bool grew) {
   InstDyn& h = *s->h_dyn;
   h.status &= ~ST_LAYER;
   const uint32_t k = h.pc;
@@ -2246,8 +2253,13 @@ int layer_failed(pp_state* s, const Op* ops, size_t len) {
     }
     const int32_t step = h.lwhy & 1u ? -1 : 1;
     const int32_t next = h.lboost + step;
-    if (!ops[k].fail_test && (h.lwhy & 1u) && (uint64_t)h.M * 3 > s->buf.cap) {
+    const bool enlarge = !ops[k].fail_test && !(h.lwhy & 1u) && !s->layer_big;
+    if (!ops[k].fail_test && (h.lwhy & 1u) && grew) {
+      // the op ran in the store before the last growth: again, in the new one
+    } else if (!ops[k].fail_test && (h.lwhy & 1u) && (uint64_t)h.M * 3 > s->buf.cap) {
       if ((rc = grow(s))) return rc;           // more staging slots per bucket
+    } else if (enlarge) {
+      s->layer_big = true;                     // twice the strings per bucket, from here on
     } else if (!ops[k].fail_test && next >= -kLayerMaxBoost && next <= kLayerMaxBoost &&
                !s->layer_tried[next + kLayerMaxBoost] && s->layer_retries < kLayerRetries) {
       ++s->layer_retries;
@@ -2426,6 +2438,7 @@ int solo_program(pp_state* s, const pp_program* p, double* expectation, bool res
       // rarely has to stop (and the launches queued behind it idle)
       if ((uint64_t)dy.M * 3 > s->buf.cap && next_chunk < ends.size()) {
         if ((rc = read_dyn(s))) return rc;
+        const uint32_t old_cap = s->buf.cap;
         if (s->h_dyn->pc < len && !(s->h_dyn->status & ST_OVERFLOW) &&
             (uint64_t)s->h_dyn->M * 3 > s->buf.cap) {
           if ((rc = grow(s))) return rc;
@@ -2438,7 +2451,7 @@ int solo_program(pp_state* s, const pp_program* p, double* expectation, bool res
                                  hipMemcpyHostToDevice, st));
         }
         if (s->h_dyn->status & ST_LAYER) {
-          if ((rc = layer_failed(s, ops, len))) return rc;
+          if ((rc = layer_failed(s, ops, len, s->buf.cap > old_cap))) return rc;
         }
         launched_to = s->h_dyn->pc;
         next_chunk = 0;

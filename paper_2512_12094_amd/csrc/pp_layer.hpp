@@ -41,11 +41,14 @@ __host__ __device__ __forceinline__ int layer_key_words(int n, int W) {
   return n <= 32 ? 1 : 2 * W;
 }
 
-// Strings per bucket in LDS: two blocks of the apply step fit a CU's 160 KB.
-template <int KW> struct LayerCap;
-template <> struct LayerCap<1> { static constexpr int n = 2048; };
-template <> struct LayerCap<2> { static constexpr int n = 1792; };
-template <> struct LayerCap<4> { static constexpr int n = 1024; };
+// Strings per bucket in LDS for blocks of NB threads: two blocks of up to 512
+// threads fit a CU's 160 KB, or one of 1024 with twice the room (the form for
+// closed sets that do not fit the smaller one).
+template <int KW, int NB>
+constexpr int layer_cap() {
+  constexpr int n = KW == 1 ? 2048 : KW == 2 ? 1792 : 1024;
+  return NB == 1024 ? 2 * n : n;
+}
 
 // Bucket bits for a layer op over M entries: about 2^shift strings per
 // bucket, more after failures (boost), at most maxbits.
@@ -590,7 +593,7 @@ __device__ __forceinline__ uint16_t life_of(uint32_t born, uint32_t died) {
 // births and drops of the rotations before it.
 template <int KW, int NB>
 struct ApplySh {
-  static constexpr int CAP = LayerCap<KW>::n, HS = LdsTab<CAP>::HS, NW = NB / 64, NS = 7;
+  static constexpr int CAP = layer_cap<KW, NB>(), HS = LdsTab<CAP>::HS, NW = NB / 64, NS = 7;
   static constexpr int WW = KW == 1 ? 1 : KW / 2;
   uint64_t k[KW][CAP];
   double c[CAP];

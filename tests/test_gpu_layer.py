@@ -189,10 +189,12 @@ def test_failed_layer_op_keeps_the_gate_table(gpu):
 
 
 # (qubits, rotations, does the closed set of 2^rotations strings fit a block):
-# one, two and four key words, at and past each width's LDS capacity
-@pytest.mark.parametrize("n,k,fits", [(12, 10, True), (12, 11, True), (12, 12, False),
-                                      (40, 10, True), (40, 11, False),
-                                      (80, 10, True), (80, 11, False)])
+# one, two and four key words, at and past each width's LDS capacity (a set
+# past the smaller block's runs again with the larger one)
+@pytest.mark.parametrize("n,k,fits", [(12, 10, True), (12, 11, True), (12, 12, True),
+                                      (13, 13, False), (40, 10, True), (40, 11, True),
+                                      (40, 12, False), (80, 10, True), (80, 11, True),
+                                      (80, 12, False)])
 def test_closed_set_at_the_block_capacity(gpu, n, k, fits):
     """X rotations on k qubits of the one string Z...Z make 2^k strings in
     one closed set; then Z rotations, so every string meets its partners
