@@ -16,6 +16,8 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -96,7 +98,24 @@ constexpr size_t kSoloInflight = 2;
 constexpr int kSoloSlots = 4;
 static_assert(kSoloSlots >= (int)kSoloInflight, "a chunk in flight would reuse a live slot");
 
+// Pinned memory and events of one handle.  hipHostMalloc, hipHostFree and
+// event creation take 20-50 us each, as long as a small propagation's
+// kernels, so a destroyed handle (its stream drained) leaves its block for
+// the next one: at most kHostBlocks of ~80 KB are kept, per process.
+constexpr int kRing = 4;
+constexpr size_t kHostBlocks = 32;
+constexpr size_t kRingBytes = 16384, kStageBytes = 16384;
+struct HostBlock {
+  int dev = 0;
+  char* mem = nullptr;
+  hipEvent_t solo[kSoloSlots] = {}, ring[kRing] = {};
+};
+
 struct pp_state {
+  HostBlock* host = nullptr;
+  char* d_core = nullptr;              // one allocation: d_buf .. d_stats
+  char* h_stage = nullptr;             // pinned, kStageBytes: uploads of create_handle
+  size_t txn_cap = 0;                  // bytes of txn_backup (kept between calls)
   int n = 0, W = 1, group = 0;
   hipStream_t stream = nullptr;
   pp_allocator alloc{};
@@ -113,8 +132,7 @@ struct pp_state {
   uint64_t* d_stats = nullptr;        // kStatBytes of statistics lines
   Op* d_ops = nullptr;
   size_t ops_cap = 0;
-  double* d_tab = nullptr;
-  size_t tab_cap = 0;
+  double* d_tab = nullptr;             // inside d_ops' area
   InstDyn* h_dyn = nullptr;            // pinned
   double* h_na = nullptr;              // pinned: result and flag of pp_expectation_noalloc
   // transaction of a pp_apply_layer / pp_merge_canonicalize call: the store
@@ -144,8 +162,8 @@ struct pp_state {
     char* h = nullptr;
     size_t cap = 0;
     hipEvent_t ev = nullptr;
-    bool used = false;
-  } ring[4];
+    bool used = false, own = false;    // own: h was allocated here (outgrew the host block's)
+  } ring[kRing];
   unsigned ring_pos = 0;
   // per-kernel timing with events on this stream (pp_profile): every
   // prof_every-th run of back-to-back launches of one kind is bracketed by
@@ -173,6 +191,81 @@ struct pp_state {
 };
 
 namespace {
+
+std::mutex g_host_mu;
+std::vector<HostBlock*> g_host_free;
+
+constexpr size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+
+void host_block_free(HostBlock* h) {
+  if (h->mem) (void)hipHostFree(h->mem);
+  for (auto e : h->solo)
+    if (e) (void)hipEventDestroy(e);
+  for (auto e : h->ring)
+    if (e) (void)hipEventDestroy(e);
+  delete h;
+}
+
+// A block for the current device and its parts into s.
+int host_block_get(pp_state* s) {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  {
+    std::lock_guard<std::mutex> lk(g_host_mu);
+    for (size_t i = g_host_free.size(); i-- > 0;)
+      if (g_host_free[i]->dev == dev) {
+        s->host = g_host_free[i];
+        g_host_free.erase(g_host_free.begin() + i);
+        break;
+      }
+  }
+  const size_t dyn = align256(sizeof(InstDyn));
+  if (!s->host) {
+    HostBlock* h = new HostBlock;
+    h->dev = dev;
+    bool ok = hipHostMalloc((void**)&h->mem, (1 + kSoloSlots) * dyn + 256 + kStageBytes +
+                                                 kRing * kRingBytes,
+                            hipHostMallocDefault) == hipSuccess;
+    for (auto& e : h->solo)
+      ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    for (auto& e : h->ring)
+      ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+      host_block_free(h);
+      return fail(PP_ENOMEM, "pinned memory of a handle");
+    }
+    s->host = h;
+  }
+  char* p = s->host->mem;
+  s->h_dyn = (InstDyn*)p;
+  s->solo_slots = (InstDyn*)(p += dyn);
+  static_assert(sizeof(InstDyn) % 8 == 0, "the slots are contiguous");
+  s->h_na = (double*)(p += kSoloSlots * dyn);
+  s->h_stage = p += 256;
+  p += kStageBytes;
+  for (int k = 0; k < kRing; ++k, p += kRingBytes) {
+    s->ring[k].h = p;
+    s->ring[k].cap = kRingBytes;
+    s->ring[k].ev = s->host->ring[k];
+  }
+  for (int k = 0; k < kSoloSlots; ++k) s->solo_ev[k] = s->host->solo[k];
+  return PP_OK;
+}
+
+// After the handle's stream has drained.
+void host_block_put(pp_state* s) {
+  for (auto& st : s->ring)
+    if (st.own) (void)hipHostFree(st.h);
+  if (!s->host) return;
+  {
+    std::lock_guard<std::mutex> lk(g_host_mu);
+    if (g_host_free.size() < kHostBlocks) {
+      g_host_free.push_back(s->host);
+      s->host = nullptr;
+    }
+  }
+  if (s->host) host_block_free(s->host);
+}
 
 void* dev_alloc(pp_state* s, size_t bytes) {
   bytes = std::max<size_t>(bytes, 256);
@@ -304,8 +397,15 @@ uint32_t layer_slots(uint32_t cap) {
   return 1u << (ceil_log2(cap) + (cap <= kLayerSmallCap ? 2 : 0));
 }
 
+//
+// A store of at most kStoreBlock bytes is one allocation (a handle grows
+// through several small stores, and ~20 trips to the caller's allocator for
+// each took longer than initialising it); a larger one is an allocation per
+// array, which a fragmented device places more easily.
+constexpr size_t kStoreBlock = size_t(256) << 20;
+
 int alloc_store(pp_state* s, uint32_t cap, InstBuf* b, std::vector<void*>* allocs,
-                size_t* dry = nullptr) {
+                size_t* dry = nullptr, uint32_t n_alive = 0) {
   const int W = s->W;
   InstBuf nb = s->buf;
   nb.cap = cap;
@@ -318,88 +418,104 @@ int alloc_store(pp_state* s, uint32_t cap, InstBuf* b, std::vector<void*>* alloc
   }
   const size_t ng = size_t(1) << nb.hg_bits, nm = size_t(1) << nb.hm_bits;
   std::vector<void*> got;
-  auto take = [&](size_t bytes) -> void* {
-    if (dry) {
-      *dry += (std::max<size_t>(bytes, 256) + 255) / 256 * 256;
-      return reinterpret_cast<void*>(uintptr_t(256));
+  const bool wide = !nb.narrow;
+  // every array of the store, from take(bytes)
+  auto layout = [&](auto take) -> bool {
+    bool ok = true;
+    for (int h = 0; h < 2; ++h) {
+      ok = ok && (nb.x[h] = (uint64_t*)take(sizeof(uint64_t) * W * cap));
+      ok = ok && (nb.z[h] = (uint64_t*)take(sizeof(uint64_t) * W * cap));
+      ok = ok && (nb.c[h] = take((nb.f32 ? sizeof(float) : sizeof(double)) * cap));
+      for (int p = 0; p < 2; ++p) ok = ok && (nb.alive[h][p] = (uint8_t*)take(cap));
+    }
+    ok = ok && (nb.gtab = (uint64_t*)take(sizeof(uint64_t) * ng));
+    ok = ok && (nb.mkey = (uint64_t*)take(sizeof(uint64_t) * nm));
+    ok = ok && (nb.mfx = (uint64_t*)take(3 * sizeof(uint64_t) * nm));
+    ok = ok && (nb.accs = (uint64_t*)take(kAccBytes));
+    // staging of the partitioned merge (narrow keys, not S_n, large stores)
+    nb.phash = nullptr;
+    nb.pstage = nullptr;
+    nb.phist = nullptr;
+    nb.ptot = nullptr;
+    nb.pbase = nullptr;
+    nb.pwork = nullptr;
+    nb.plist = nullptr;
+    nb.pmaxbits = 0;
+    if (nb.narrow && s->group != PP_GROUP_PERMUTATION && cap >= kPartMin) {
+      nb.pshift = (uint32_t)g_tune.part_shift;
+      nb.pmaxbits = part_bits(cap, kPartMaxBits, nb.pshift);
+      const size_t P = size_t(1) << nb.pmaxbits;
+      const size_t tiles = (cap + kPartTileRec - 1) / kPartTileRec;
+      ok = ok && (nb.phash = (uint64_t*)take(sizeof(uint64_t) * cap));
+      ok = ok && (nb.pstage = (uint64_t*)take(2 * sizeof(uint64_t) * cap));
+      ok = ok && (nb.phist = (uint32_t*)take(sizeof(uint32_t) * tiles * P));
+      ok = ok && (nb.ptot = (uint32_t*)take(sizeof(uint32_t) * P));
+      ok = ok && (nb.pbase = (uint32_t*)take(sizeof(uint32_t) * (P + 1)));
+      ok = ok && (nb.pwork = (uint32_t*)take(sizeof(uint32_t) * 2 * P));
+      ok = ok && (nb.plist = (uint32_t*)take(sizeof(uint32_t) * nm));
+    }
+    // staging of the layer op (once a layer op has run on this handle)
+    nb.lstx = nb.lstz = nullptr;
+    nb.lstc = nullptr;
+    nb.lsta = nullptr;
+    nb.lcount = nullptr;
+    nb.lslots = 0;
+    nb.lmaxbits = 0;
+    if (s->layer_used) {
+      nb.lslots = layer_slots(cap);
+      nb.lmaxbits = layer_max_bits(nb.lslots);
+      ok = ok && (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
+      ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
+      ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
+      ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
+      ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
+    }
+    nb.mown = nullptr;
+    nb.wrep = nullptr;
+    nb.wslot = nullptr;
+    if (wide) {
+      ok = ok && (nb.mown = (uint32_t*)take(sizeof(uint32_t) * nm));
+      ok = ok && (nb.wrep = (uint64_t*)take(sizeof(uint64_t) * 2 * W * cap));
+      ok = ok && (nb.wslot = (uint32_t*)take(sizeof(uint32_t) * cap));
+    }
+    return ok;
+  };
+  size_t total = 0;
+  (void)layout([&](size_t bytes) -> void* {
+    total += align256(std::max<size_t>(bytes, 256));
+    return reinterpret_cast<void*>(uintptr_t(256));
+  });
+  if (dry) {
+    *dry += total;
+    return PP_OK;
+  }
+  char* block = nullptr;
+  if (total <= kStoreBlock) {
+    block = (char*)dev_alloc(s, total);
+    if (block) got.push_back(block);
+  }
+  const bool ok = (total > kStoreBlock || block) && layout([&](size_t bytes) -> void* {
+    if (block) {
+      void* p = block;
+      block += align256(std::max<size_t>(bytes, 256));
+      return p;
     }
     void* p = dev_alloc(s, bytes);
     if (p) got.push_back(p);
     return p;
-  };
-  bool ok = true;
-  for (int h = 0; h < 2; ++h) {
-    ok = ok && (nb.x[h] = (uint64_t*)take(sizeof(uint64_t) * W * cap));
-    ok = ok && (nb.z[h] = (uint64_t*)take(sizeof(uint64_t) * W * cap));
-    ok = ok && (nb.c[h] = take((nb.f32 ? sizeof(float) : sizeof(double)) * cap));
-    for (int p = 0; p < 2; ++p) ok = ok && (nb.alive[h][p] = (uint8_t*)take(cap));
-  }
-  ok = ok && (nb.gtab = (uint64_t*)take(sizeof(uint64_t) * ng));
-  ok = ok && (nb.mkey = (uint64_t*)take(sizeof(uint64_t) * nm));
-  ok = ok && (nb.mfx = (uint64_t*)take(3 * sizeof(uint64_t) * nm));
-  ok = ok && (nb.accs = (uint64_t*)take(kAccBytes));
-  // staging of the partitioned merge (narrow keys, not S_n, large stores)
-  nb.phash = nullptr;
-  nb.pstage = nullptr;
-  nb.phist = nullptr;
-  nb.ptot = nullptr;
-  nb.pbase = nullptr;
-  nb.pwork = nullptr;
-  nb.plist = nullptr;
-  nb.pmaxbits = 0;
-  if (nb.narrow && s->group != PP_GROUP_PERMUTATION && cap >= kPartMin) {
-    nb.pshift = (uint32_t)g_tune.part_shift;
-    nb.pmaxbits = part_bits(cap, kPartMaxBits, nb.pshift);
-    const size_t P = size_t(1) << nb.pmaxbits;
-    const size_t tiles = (cap + kPartTileRec - 1) / kPartTileRec;
-    ok = ok && (nb.phash = (uint64_t*)take(sizeof(uint64_t) * cap));
-    ok = ok && (nb.pstage = (uint64_t*)take(2 * sizeof(uint64_t) * cap));
-    ok = ok && (nb.phist = (uint32_t*)take(sizeof(uint32_t) * tiles * P));
-    ok = ok && (nb.ptot = (uint32_t*)take(sizeof(uint32_t) * P));
-    ok = ok && (nb.pbase = (uint32_t*)take(sizeof(uint32_t) * (P + 1)));
-    ok = ok && (nb.pwork = (uint32_t*)take(sizeof(uint32_t) * 2 * P));
-    ok = ok && (nb.plist = (uint32_t*)take(sizeof(uint32_t) * nm));
-  }
-  // staging of the layer op (once a layer op has run on this handle)
-  nb.lstx = nb.lstz = nullptr;
-  nb.lstc = nullptr;
-  nb.lsta = nullptr;
-  nb.lcount = nullptr;
-  nb.lslots = 0;
-  nb.lmaxbits = 0;
-  if (s->layer_used) {
-    nb.lslots = layer_slots(cap);
-    nb.lmaxbits = layer_max_bits(nb.lslots);
-    ok = ok && (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
-    ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
-    ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
-    ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
-    ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
-  }
-  const bool wide = !nb.narrow;
-  nb.mown = nullptr;
-  nb.wrep = nullptr;
-  nb.wslot = nullptr;
-  if (wide) {
-    ok = ok && (nb.mown = (uint32_t*)take(sizeof(uint32_t) * nm));
-    ok = ok && (nb.wrep = (uint64_t*)take(sizeof(uint64_t) * 2 * W * cap));
-    ok = ok && (nb.wslot = (uint32_t*)take(sizeof(uint32_t) * cap));
-  }
+  });
   if (!ok) {
     for (void* p : got) dev_free(s, p);
     return fail(PP_ENOMEM, "allocation of a term store of capacity " + std::to_string(cap) +
                                " failed");
   }
-  if (dry) return PP_OK;
   // the tables' initial state in one launch (instead of a fill per array)
   const uint64_t init_elems = std::max<uint64_t>({ng, nm, cap / 8});
   const int init_grid = (int)std::min<uint64_t>(
       std::max<uint64_t>(1, (init_elems + 4 * kBlock - 1) / (4 * kBlock)), 2048);
   hipLaunchKernelGGL(k_init_store, dim3(init_grid), dim3(kBlock), 0, s->stream, nb, (uint64_t)ng,
-                     (uint64_t)nm, wide ? 1u : 0u);
+                     (uint64_t)nm, wide ? 1u : 0u, n_alive);
   HIP_TRY(hipGetLastError());
-  if (nb.lcount)
-    HIP_TRY(hipMemsetAsync(nb.lcount, 0, sizeof(uint32_t) << nb.lmaxbits, s->stream));
   *b = nb;
   *allocs = std::move(got);
   return PP_OK;
@@ -592,21 +708,23 @@ int grow(pp_state* s) {
   return read_dyn(s);
 }
 
+// Room for a scratch program: nops ops, then ntab table entries (one area, one
+// upload).
 int ensure_ops(pp_state* s, size_t nops, size_t ntab) {
-  if (nops > s->ops_cap) {
+  const size_t need = sizeof(Op) * nops + sizeof(double) * ntab;
+  if (need > s->ops_cap) {
     dev_free(s, s->d_ops);
-    s->ops_cap = std::max<size_t>(nops, 2 * s->ops_cap);
-    s->d_ops = (Op*)dev_alloc(s, sizeof(Op) * s->ops_cap);
-    if (!s->d_ops) return fail(PP_ENOMEM, "program buffer");
+    s->ops_cap = std::max<size_t>(need, 2 * s->ops_cap);
+    s->d_ops = (Op*)dev_alloc(s, s->ops_cap);
+    if (!s->d_ops) {
+      s->ops_cap = 0;
+      return fail(PP_ENOMEM, "program buffer");
+    }
   }
-  if (ntab > s->tab_cap) {
-    dev_free(s, s->d_tab);
-    s->tab_cap = std::max<size_t>(ntab, 2 * s->tab_cap);
-    s->d_tab = (double*)dev_alloc(s, sizeof(double) * s->tab_cap);
-    if (!s->d_tab) return fail(PP_ENOMEM, "table buffer");
-  }
+  s->d_tab = reinterpret_cast<double*>(s->d_ops + nops);
   return PP_OK;
 }
+static_assert(sizeof(Op) % sizeof(double) == 0, "the table follows the ops");
 
 bool is_part_kind(int kind) {
   return kind == PP_K_PART_HIST || kind == PP_K_PART_SCAN || kind == PP_K_PART_SCATTER ||
@@ -791,20 +909,19 @@ int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
     const size_t ob = sizeof(Op) * ops.size(), tb = sizeof(double) * tab.size();
     const size_t bb = sizeof(InstBuf);
     if (st.used) HIP_TRY(hipEventSynchronize(st.ev));
-    if (!st.ev) HIP_TRY(hipEventCreateWithFlags(&st.ev, hipEventDisableTiming));
     if (st.cap < ob + tb + bb) {
-      if (st.h) HIP_TRY(hipHostFree(st.h));
-      st.h = nullptr;
-      st.cap = std::max<size_t>(ob + tb + bb, 4096);
-      HIP_TRY(hipHostMalloc((void**)&st.h, st.cap, hipHostMallocDefault));
+      if (st.own) HIP_TRY(hipHostFree(st.h));
+      st.own = false;
+      st.cap = 0;
+      HIP_TRY(hipHostMalloc((void**)&st.h, ob + tb + bb, hipHostMallocDefault));
+      st.cap = ob + tb + bb;
+      st.own = true;
     }
     std::memcpy(st.h, &s->buf, bb);
     std::memcpy(st.h + bb, ops.data(), ob);
     if (tb) std::memcpy(st.h + bb + ob, tab.data(), tb);
     HIP_TRY(hipMemcpyAsync(s->d_buf, st.h, bb, hipMemcpyHostToDevice, s->stream));
-    HIP_TRY(hipMemcpyAsync(s->d_ops, st.h + bb, ob, hipMemcpyHostToDevice, s->stream));
-    if (tb)
-      HIP_TRY(hipMemcpyAsync(s->d_tab, st.h + bb + ob, tb, hipMemcpyHostToDevice, s->stream));
+    HIP_TRY(hipMemcpyAsync(s->d_ops, st.h + bb, ob + tb, hipMemcpyHostToDevice, s->stream));
     HIP_TRY(hipEventRecord(st.ev, s->stream));
     st.used = true;
   }
@@ -1210,28 +1327,14 @@ void pp_destroy(pp_state* s) {
   if (!s) return;
   (void)hipStreamSynchronize(s->stream);
   free_store(s, s->store);
+  dev_free(s, s->txn_backup);
   dev_free(s, s->d_ops);
-  dev_free(s, s->d_tab);
-  dev_free(s, s->d_buf);
-  dev_free(s, s->d_dyn);
-  dev_free(s, s->d_bufp);
-  dev_free(s, s->d_dynp);
-  dev_free(s, s->d_ninst);
-  dev_free(s, s->d_sync);
-  dev_free(s, s->d_stats);
+  dev_free(s, s->d_core);
   dev_free(s, s->d_gperm);
   dev_free(s, s->d_act);
-  if (s->h_dyn) (void)hipHostFree(s->h_dyn);
-  if (s->h_na) (void)hipHostFree(s->h_na);
-  for (auto& st : s->ring) {
-    if (st.h) (void)hipHostFree(st.h);
-    if (st.ev) (void)hipEventDestroy(st.ev);
-  }
   prof_resolve(s);
   for (hipEvent_t e : s->pool) (void)hipEventDestroy(e);
-  if (s->solo_slots) (void)hipHostFree(s->solo_slots);
-  for (auto e : s->solo_ev)
-    if (e) (void)hipEventDestroy(e);
+  host_block_put(s);
   delete s;
 }
 
@@ -1249,7 +1352,13 @@ int create_handle(pp_state** out, int n_qubits, int group, int lx, int dtype,
   if (n_obs && (!obs_x || !obs_z || !obs_coef)) return fail(PP_EINVAL, "observable is NULL");
   if (n_obs > 0x3FFFFFFFull) return fail(PP_EINVAL, "too many observable rows");
   const int W = (n_qubits + 63) / 64;
+  uint64_t any[2 * kMaxW] = {};            // all rows or-ed: the common case in one sweep
   for (size_t r = 0; r < n_obs; ++r)
+    for (int w = 0; w < W; ++w) {
+      any[w] |= obs_x[r * W + w];
+      any[kMaxW + w] |= obs_z[r * W + w];
+    }
+  for (size_t r = 0; r < n_obs && !row_in_range(any, any + kMaxW, n_qubits, W); ++r)
     if (!row_in_range(obs_x + r * W, obs_z + r * W, n_qubits, W))
       return fail(PP_EINVAL, "observable row " + std::to_string(r) + " has bits >= n_qubits");
   if (alloc && (!alloc->alloc || !alloc->free)) return fail(PP_EINVAL, "incomplete allocator");
@@ -1273,23 +1382,29 @@ int create_handle(pp_state** out, int n_qubits, int group, int lx, int dtype,
   s->buf.lx = lx;
   s->lx = lx;
 
-  HIP_TRY(hipHostMalloc((void**)&s->h_dyn, sizeof(InstDyn), hipHostMallocDefault));
-  HIP_TRY(hipHostMalloc((void**)&s->h_na, 2 * sizeof(double), hipHostMallocDefault));
-  s->d_buf = (InstBuf*)dev_alloc(s.get(), sizeof(InstBuf));
-  s->d_dyn = (InstDyn*)dev_alloc(s.get(), sizeof(InstDyn));
-  s->d_bufp = (const InstBuf**)dev_alloc(s.get(), sizeof(void*));
-  s->d_dynp = (InstDyn**)dev_alloc(s.get(), sizeof(void*));
-  s->d_ninst = (int*)dev_alloc(s.get(), sizeof(int));
-  s->d_sync = (uint32_t*)dev_alloc(s.get(), kSyncBytes);
-  s->d_stats = (uint64_t*)dev_alloc(s.get(), kStatBytes);
-  s->buf.stats = s->d_stats;
-  if (!s->d_buf || !s->d_dyn || !s->d_bufp || !s->d_dynp || !s->d_ninst || !s->d_sync ||
-      !s->d_stats) {
+  int rc = host_block_get(s.get());
+  if (rc) return rc;
+  // the handle's small device structures, one allocation and one upload
+  const size_t off_dyn = align256(sizeof(InstBuf)), off_ptr = off_dyn + align256(sizeof(InstDyn)),
+               off_sync = off_ptr + 256, off_stats = off_sync + align256(kSyncBytes),
+               core = off_stats + kStatBytes;
+  static_assert(align256(sizeof(InstBuf)) + align256(sizeof(InstDyn)) + 256 +
+                        align256(kSyncBytes) + kStatBytes <= kStageBytes,
+                "the handle's image fits its staging");
+  s->d_core = (char*)dev_alloc(s.get(), core);
+  if (!s->d_core) {
     pp_destroy(s.release());
     return fail(PP_ENOMEM, "handle allocation failed");
   }
+  s->d_buf = (InstBuf*)s->d_core;
+  s->d_dyn = (InstDyn*)(s->d_core + off_dyn);
+  s->d_bufp = (const InstBuf**)(s->d_core + off_ptr);
+  s->d_dynp = (InstDyn**)(s->d_core + off_ptr + 64);
+  s->d_ninst = (int*)(s->d_core + off_ptr + 128);
+  s->d_sync = (uint32_t*)(s->d_core + off_sync);
+  s->d_stats = (uint64_t*)(s->d_core + off_stats);
+  s->buf.stats = s->d_stats;
   const int one = 1;
-  int rc;
   auto bail = [&](int code) {
     pp_destroy(s.release());
     return code;
@@ -1304,37 +1419,6 @@ int create_handle(pp_state** out, int n_qubits, int group, int lx, int dtype,
     s->buf.gperm = s->d_gperm;
     s->buf.gsize = (uint32_t)(s->gperm.size() / n_qubits);
   }
-  if (hipMemcpyAsync(s->d_bufp, &s->d_buf, sizeof(void*), hipMemcpyHostToDevice, s->stream) ||
-      hipMemcpyAsync(s->d_dynp, &s->d_dyn, sizeof(void*), hipMemcpyHostToDevice, s->stream) ||
-      hipMemcpyAsync(s->d_ninst, &one, sizeof(int), hipMemcpyHostToDevice, s->stream) ||
-      hipMemsetAsync(s->d_sync, 0, kSyncBytes, s->stream) ||
-      hipMemsetAsync(s->d_stats, 0, kStatBytes, s->stream))
-    return bail(fail(PP_EDEVICE, "handle initialisation failed"));
-
-  const uint32_t cap = (uint32_t)std::max<uint64_t>(4096, 2 * n_obs);
-  if ((rc = alloc_store(s.get(), cap, &s->buf, &s->store))) return bail(rc);
-
-  // rows -> word-major planes of half 0, all alive
-  std::vector<uint64_t> xs((size_t)W * cap, 0), zs((size_t)W * cap, 0);
-  for (size_t r = 0; r < n_obs; ++r)
-    for (int w = 0; w < W; ++w) {
-      xs[(size_t)w * cap + r] = obs_x[r * W + w];
-      zs[(size_t)w * cap + r] = obs_z[r * W + w];
-    }
-  std::vector<uint8_t> ones(std::max<size_t>(n_obs, 1), 1);
-  // FP32 storage: each observable coefficient is rounded once
-  std::vector<float> cf(s->buf.f32 ? n_obs : 0);
-  for (size_t r = 0; r < cf.size(); ++r) cf[r] = (float)obs_coef[r];
-  const void* csrc = s->buf.f32 ? (const void*)cf.data() : (const void*)obs_coef;
-  const size_t csize = (s->buf.f32 ? sizeof(float) : sizeof(double)) * n_obs;
-  if (hipMemcpyAsync(s->buf.x[0], xs.data(), sizeof(uint64_t) * xs.size(), hipMemcpyHostToDevice,
-                     s->stream) ||
-      hipMemcpyAsync(s->buf.z[0], zs.data(), sizeof(uint64_t) * zs.size(), hipMemcpyHostToDevice,
-                     s->stream) ||
-      (n_obs && hipMemcpyAsync(s->buf.c[0], csrc, csize, hipMemcpyHostToDevice, s->stream)) ||
-      (n_obs && hipMemcpyAsync(s->buf.alive[0][0], ones.data(), n_obs, hipMemcpyHostToDevice,
-                               s->stream)))
-    return bail(fail(PP_EDEVICE, "observable upload failed"));
   InstDyn& d = *s->h_dyn;
   std::memset(&d, 0, sizeof(InstDyn));
   d.M = d.Mnext = (uint32_t)n_obs;
@@ -1345,8 +1429,48 @@ int create_handle(pp_state** out, int n_qubits, int group, int lx, int dtype,
   d.seed = 1;
   d.failed_pc = kNone32;
   s->m_hint = (uint32_t)n_obs;
-  if (hipMemcpyAsync(s->d_dyn, &d, sizeof(InstDyn), hipMemcpyHostToDevice, s->stream))
-    return bail(fail(PP_EDEVICE, "state upload failed"));
+  std::memset(s->h_stage, 0, core);
+  std::memcpy(s->h_stage + off_dyn, &d, sizeof(InstDyn));
+  std::memcpy(s->h_stage + off_ptr, &s->d_buf, sizeof(void*));
+  std::memcpy(s->h_stage + off_ptr + 64, &s->d_dyn, sizeof(void*));
+  std::memcpy(s->h_stage + off_ptr + 128, &one, sizeof(int));
+  if (hipMemcpyAsync(s->d_core, s->h_stage, core, hipMemcpyHostToDevice, s->stream))
+    return bail(fail(PP_EDEVICE, "handle initialisation failed"));
+
+  const uint32_t cap = (uint32_t)std::max<uint64_t>(4096, 2 * n_obs);
+  if ((rc = alloc_store(s.get(), cap, &s->buf, &s->store, nullptr, (uint32_t)n_obs)))
+    return bail(rc);
+
+  // rows -> word-major planes of half 0 (all alive, k_init_store): one word a
+  // row is that already; more words go through a copy in plane order
+  std::vector<uint64_t> xs, zs;
+  if (W > 1) {
+    xs.resize((size_t)W * n_obs);
+    zs.resize((size_t)W * n_obs);
+    for (size_t r = 0; r < n_obs; ++r)
+      for (int w = 0; w < W; ++w) {
+        xs[(size_t)w * n_obs + r] = obs_x[r * W + w];
+        zs[(size_t)w * n_obs + r] = obs_z[r * W + w];
+      }
+  }
+  // FP32 storage: each observable coefficient is rounded once
+  std::vector<float> cf(s->buf.f32 ? n_obs : 0);
+  for (size_t r = 0; r < cf.size(); ++r) cf[r] = (float)obs_coef[r];
+  const void* csrc = s->buf.f32 ? (const void*)cf.data() : (const void*)obs_coef;
+  const size_t csize = (s->buf.f32 ? sizeof(float) : sizeof(double)) * n_obs;
+  const size_t plane = sizeof(uint64_t) * n_obs;
+  bool up = true;
+  for (int w = 0; n_obs && w < W; ++w) {
+    const uint64_t* px = W > 1 ? xs.data() + (size_t)w * n_obs : obs_x;
+    const uint64_t* pz = W > 1 ? zs.data() + (size_t)w * n_obs : obs_z;
+    up = up && hipMemcpyAsync(s->buf.x[0] + (size_t)w * cap, px, plane, hipMemcpyHostToDevice,
+                              s->stream) == hipSuccess;
+    up = up && hipMemcpyAsync(s->buf.z[0] + (size_t)w * cap, pz, plane, hipMemcpyHostToDevice,
+                              s->stream) == hipSuccess;
+  }
+  up = up && (!n_obs || hipMemcpyAsync(s->buf.c[0], csrc, csize, hipMemcpyHostToDevice,
+                                       s->stream) == hipSuccess);
+  if (!up) return bail(fail(PP_EDEVICE, "observable upload failed"));
   // Algorithm 1, step 1: merge the rows by representative (duplicates too)
   std::vector<Op> ops(1, make_op(OP_MERGE));
   ops[0].force_full = 1;
@@ -1520,24 +1644,24 @@ size_t txn_bytes(const pp_state* s, uint32_t M) {
 int txn_begin(pp_state* s) {
   const InstDyn& h = *s->h_dyn;
   const uint32_t M = h.M;
-  void* b = dev_alloc(s, txn_bytes(s, M));
-  if (!b) return fail(PP_ENOMEM, "transaction backup allocation failed");
-  char* p = static_cast<char*>(b);
-  const size_t cs = s->buf.f32 ? sizeof(float) : sizeof(double);
-  HIP_TRY(hipMemcpyAsync(p, s->d_dyn, sizeof(InstDyn), hipMemcpyDeviceToDevice, s->stream));
-  p += sizeof(InstDyn);
-  HIP_TRY(hipMemcpyAsync(p, s->d_stats, kStatBytes, hipMemcpyDeviceToDevice, s->stream));
-  p += kStatBytes;
-  if (M) {
-    HIP_TRY(hipMemcpyAsync(p, s->buf.c[h.half], (size_t)M * cs, hipMemcpyDeviceToDevice,
-                           s->stream));
-    p += (size_t)M * cs;
-    HIP_TRY(hipMemcpyAsync(p, s->buf.alive[h.half][h.parity], M, hipMemcpyDeviceToDevice,
-                           s->stream));
+  if (txn_bytes(s, M) > s->txn_cap) {      // kept between calls, sized with headroom
+    dev_free(s, s->txn_backup);
+    s->txn_cap = 2 * txn_bytes(s, M);
+    s->txn_backup = dev_alloc(s, s->txn_cap);
+    if (!s->txn_backup) {
+      s->txn_cap = 0;
+      return fail(PP_ENOMEM, "transaction backup allocation failed");
+    }
   }
+  const uint32_t cw = s->buf.f32 ? 1 : 2;
+  hipLaunchKernelGGL(k_save, dim3(launch_blocks((uint64_t)M * cw + 4 * kBlock)), dim3(kBlock), 0,
+                     s->stream, (const uint32_t*)s->d_dyn, (const uint32_t*)s->d_stats,
+                     (const uint32_t*)s->buf.c[h.half],
+                     (const uint8_t*)s->buf.alive[h.half][h.parity], M, cw,
+                     (uint32_t*)s->txn_backup);
+  HIP_TRY(hipGetLastError());
   s->txn = true;
   s->txn_buf = s->buf;
-  s->txn_backup = b;
   s->txn_m = M;
   s->txn_half = h.half;
   s->txn_parity = h.parity;
@@ -1545,8 +1669,6 @@ int txn_begin(pp_state* s) {
 }
 
 void txn_end(pp_state* s) {
-  dev_free(s, s->txn_backup);
-  s->txn_backup = nullptr;
   for (auto& st : s->retired) free_store(s, st);
   s->retired.clear();
   s->txn = false;
@@ -1861,6 +1983,42 @@ int pp_counters(pp_state* s, uint64_t out[2]) {
   return PP_OK;
 }
 
+namespace {
+
+// Writes a zero into every page of some output arrays (which are overwritten
+// whole afterwards) from a few threads; joined before the arrays are used.
+struct Prefault {
+  static constexpr size_t kMin = size_t(2) << 20;    // below: the copies fault them in
+  static constexpr size_t kPage = 4096, kMaxThreads = 8;
+  std::vector<std::thread> th;
+  void start(std::vector<std::pair<void*, size_t>> parts) {
+    size_t total = 0;
+    for (const auto& p : parts) total += p.second;
+    if (total < kMin) return;
+    const size_t n = std::min<size_t>(kMaxThreads, total / (kMin / 2));
+    for (size_t t = 0; t < n; ++t) {
+      try {
+        th.emplace_back([parts, t, n] {
+          for (const auto& p : parts) {
+            volatile char* c = static_cast<volatile char*>(p.first);
+            const size_t lo = p.second / n * t, hi = t + 1 == n ? p.second : p.second / n * (t + 1);
+            for (size_t o = lo; o < hi; o += kPage) c[o] = 0;
+          }
+        });
+      } catch (const std::system_error&) {           // no thread to be had: the copies do it
+        return;
+      }
+    }
+  }
+  void join() {
+    for (auto& t : th) t.join();
+    th.clear();
+  }
+  ~Prefault() { join(); }
+};
+
+}  // namespace
+
 int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t cap,
                     size_t* n_out) {
   if (!s || !n_out) return fail(PP_EINVAL, "NULL argument");
@@ -1880,16 +2038,21 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
   const size_t nhist = (size_t)kSortBlock * tiles0;
   const uint32_t nscan = (uint32_t)((nhist + kScanTile - 1) / kScanTile);
   const size_t rows = (size_t)N * W * sizeof(uint64_t);
-  struct Ws {
+  struct Ws {                               // one allocation
     pp_state* s;
-    std::vector<void*> p;
-    ~Ws() { for (void* q : p) dev_free(s, q); }
+    char* base;
+    size_t used = 0;
+    ~Ws() { dev_free(s, base); }
     void* get(size_t bytes) {
-      void* q = dev_alloc(s, bytes);
-      if (q) p.push_back(q);
+      void* q = base + used;
+      used += align256(bytes);
       return q;
     }
-  } ws{s, {}};
+  } ws{s, (char*)dev_alloc(s, 2 * align256(sizeof(uint32_t) * N) +
+                                  align256(sizeof(uint32_t) * nhist) +
+                                  align256(sizeof(uint32_t) * (nscan + 1)) + 2 * align256(rows) +
+                                  align256(sizeof(double) * N))};
+  if (!ws.base) return fail(PP_ENOMEM, "export workspace");
   auto* ord0 = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * N));
   auto* ord1 = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * N));
   auto* hist = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * nhist));
@@ -1897,8 +2060,11 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
   auto* ox = static_cast<uint64_t*>(ws.get(rows));
   auto* oz = static_cast<uint64_t*>(ws.get(rows));
   auto* oc = static_cast<double*>(ws.get(sizeof(double) * N));
-  if (!ord0 || !ord1 || !hist || !part || !ox || !oz || !oc)
-    return fail(PP_ENOMEM, "export workspace");
+  // The caller's arrays are often fresh pages, which the copies back would
+  // fault in one by one (2/3 of the call at 8x10^6 terms): threads write them
+  // while the sort runs.
+  Prefault touch;
+  touch.start({{x, rows}, {z, rows}, {coef, sizeof(double) * N}});
   SortPass p{};
   p.x = s->buf.x[d.half];
   p.z = s->buf.z[d.half];
@@ -1946,6 +2112,7 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
                      s->stream, out, N, p.x, p.z, s->buf.c[d.half], (int)s->buf.f32, C, W, ox,
                      oz, oc);
   HIP_TRY(hipGetLastError());
+  touch.join();
   HIP_TRY(hipMemcpyAsync(x, ox, rows, hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(hipMemcpyAsync(z, oz, rows, hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(hipMemcpyAsync(coef, oc, sizeof(double) * N, hipMemcpyDeviceToHost, s->stream));
@@ -2381,11 +2548,6 @@ int solo_program(pp_state* s, const pp_program* p, double* expectation, bool res
     if (merge_end || ops[k].type == OP_TRUNC) ++subs;
     if (((merge_end || ops[k].type == OP_TRUNC) && subs % kChunkSubs == 0) || k + 1 == len)
       ends.push_back(k + 1);
-  }
-  if (!s->solo_slots) {
-    HIP_TRY(hipHostMalloc((void**)&s->solo_slots, sizeof(InstDyn) * kSoloSlots,
-                          hipHostMallocDefault));
-    for (auto& e : s->solo_ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
   size_t next_chunk = 0, launched_to = resume ? s->h_dyn->pc : 0;
   while (next_chunk < ends.size() && ends[next_chunk] <= launched_to) ++next_chunk;

@@ -2549,11 +2549,12 @@ __global__ __launch_bounds__(kBlock) void k_compact_solo(Solo S) {
 // ---------------------------------------------------------------------------
 // Initial state of a new store's tables, in one launch (grid-stride): gate
 // table slots free (generation 0), merge keys empty, merge sums, count
-// accumulators and (wide keys) slot owners cleared, the four alive arrays
-// zero (written as 64-bit words; the allocations are 8-byte aligned).
+// accumulators, layer bucket counts and (wide keys) slot owners cleared, the
+// four alive arrays zero (written as 64-bit words; the allocations are 8-byte
+// aligned) but for the first n_alive entries of the first.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_init_store(InstBuf nb, uint64_t ng, uint64_t nm,
-                                                       uint32_t wide) {
+                                                       uint32_t wide, uint32_t n_alive) {
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
   const uint64_t first = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   for (uint64_t i = first; i < ng; i += stride) nb.gtab[i] = 0;
@@ -2563,13 +2564,20 @@ __global__ __launch_bounds__(kBlock) void k_init_store(InstBuf nb, uint64_t ng, 
     if (wide) nb.mown[i] = kNone32;
   }
   for (uint64_t i = first; i < kAccBytes / sizeof(uint64_t); i += stride) nb.accs[i] = 0;
+  if (nb.lcount)
+    for (uint64_t i = first; i < (1ull << nb.lmaxbits); i += stride) nb.lcount[i] = 0;
   const uint64_t words = nb.cap / 8;
-  for (uint64_t i = first; i < words; i += stride)
+  for (uint64_t i = first; i < words; i += stride) {
+    const uint64_t set = n_alive > 8 * i ? n_alive - 8 * i : 0;      // live bytes of the word
+    const uint64_t ones = 0x0101010101010101ull;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) reinterpret_cast<uint64_t*>(nb.alive[a >> 1][a & 1])[i] = 0;
+    for (int a = 0; a < 4; ++a)
+      reinterpret_cast<uint64_t*>(nb.alive[a >> 1][a & 1])[i] =
+          a || !set ? 0 : (set >= 8 ? ones : ones & ((1ull << (8 * set)) - 1));
+  }
   for (uint64_t i = 8 * words + first; i < nb.cap; i += stride)
 #pragma unroll
-    for (int a = 0; a < 4; ++a) nb.alive[a >> 1][a & 1][i] = 0;
+    for (int a = 0; a < 4; ++a) nb.alive[a >> 1][a & 1][i] = a == 0 && i < n_alive ? 1 : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -2635,6 +2643,25 @@ __global__ __launch_bounds__(kBlock) void k_grow(InstBuf src, InstBuf dst, InstD
 }
 
 __global__ void k_set_pc(InstDyn* d, uint32_t pc) { d->pc = pc; }
+
+// What a transaction may have to restore, into one backup area: the dynamic
+// state, the statistics lines, m coefficients (cw 4-byte words each) and m
+// liveness flags (one launch instead of four copies).
+__global__ __launch_bounds__(kBlock) void k_save(const uint32_t* dyn, const uint32_t* stats,
+                                                 const uint32_t* c, const uint8_t* alive,
+                                                 uint32_t m, uint32_t cw, uint32_t* out) {
+  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+  const uint64_t first = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  constexpr uint64_t nd = sizeof(InstDyn) / 4, ns = kStatBytes / 4;
+  for (uint64_t i = first; i < nd; i += stride) out[i] = dyn[i];
+  for (uint64_t i = first; i < ns; i += stride) out[nd + i] = stats[i];
+  uint32_t* oc = out + nd + ns;
+  const uint64_t nc = (uint64_t)m * cw;
+  for (uint64_t i = first; i < nc; i += stride) oc[i] = c[i];
+  uint8_t* oa = reinterpret_cast<uint8_t*>(oc + nc);
+  for (uint64_t i = first; i < m; i += stride) oa[i] = alive[i];
+}
+static_assert(sizeof(InstDyn) % 8 == 0 && kStatBytes % 8 == 0, "k_save copies words");
 
 // Which of nrot rotations (LAYER table records) some live term anticommutes
 // with: bit g of mask, which the caller cleared.  A block takes a tile of
