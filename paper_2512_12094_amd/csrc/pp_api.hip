@@ -2019,6 +2019,64 @@ struct Prefault {
 
 }  // namespace
 
+}  // extern "C"
+
+namespace {
+
+// The sampling sort's launches; *found (pinned or pageable, read after the
+// stream's next synchronisation) receives the live strings it met.
+template <int NK>
+int sample_sort(pp_state* s, SampSort p, char* ws, uint32_t* found) {
+  uint32_t P = 1;
+  if (p.N > samp_cap<NK>() / 2) {              // buckets of about a quarter of the LDS
+    while (P < samp_buckets<NK>() && p.N / P > samp_cap<NK>() / 4) P <<= 1;
+  }
+  p.P = P;
+  auto get = [&](size_t bytes) {
+    void* q = ws;
+    ws += align256(bytes);
+    return q;
+  };
+  p.cnt = (uint32_t*)get(sizeof(uint32_t) * (1 + P));
+  p.base = (uint32_t*)get(sizeof(uint32_t) * P);
+  p.split = (uint64_t*)get(sizeof(uint64_t) * NK * P);
+  p.key = (uint64_t*)get(sizeof(uint64_t) * NK * p.N);
+  p.slot = (uint32_t*)get(sizeof(uint32_t) * p.N);
+  p.key2 = p.key;
+  p.slot2 = p.slot;
+  const dim3 t(kSortBlock);
+  HIP_TRY(hipMemsetAsync(p.cnt, 0, sizeof(uint32_t) * (1 + P), s->stream));
+  hipLaunchKernelGGL(k_samp_keys<NK>, dim3((p.M + 4 * kSortBlock - 1) / (4 * kSortBlock)), t, 0,
+                     s->stream, p);
+  if (P > 1) {
+    p.key2 = (uint64_t*)get(sizeof(uint64_t) * NK * p.N);
+    p.slot2 = (uint32_t*)get(sizeof(uint32_t) * p.N);
+    p.bk = (uint32_t*)get(sizeof(uint32_t) * p.N);
+    p.rank = (uint32_t*)get(sizeof(uint32_t) * p.N);
+    hipLaunchKernelGGL(k_samp_split<NK>, dim3(1), dim3(1024), 0, s->stream, p);
+    hipLaunchKernelGGL(k_samp_rank<NK>, dim3((p.N + 4 * kSortBlock - 1) / (4 * kSortBlock)), t, 0,
+                       s->stream, p);
+    hipLaunchKernelGGL(k_samp_place<NK>, dim3((p.N + kSortBlock - 1) / kSortBlock), t, 0,
+                       s->stream, p);
+  }
+  hipLaunchKernelGGL(k_samp_sort<NK>, dim3(P), t, 0, s->stream, p);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipMemcpyAsync(found, p.cnt, sizeof(uint32_t), hipMemcpyDeviceToHost, s->stream));
+  return PP_OK;
+}
+
+// Workspace of sample_sort for N strings of nk key words.
+size_t sample_bytes(uint64_t N, int nk) {
+  const uint32_t P = nk == 4 ? samp_buckets<4>() : samp_buckets<1>();
+  return align256(sizeof(uint32_t) * (1 + P)) + align256(sizeof(uint32_t) * P) +
+         align256(sizeof(uint64_t) * nk * P) + 2 * align256(sizeof(uint64_t) * nk * N) +
+         4 * align256(sizeof(uint32_t) * N);
+}
+
+}  // namespace
+
+extern "C" {
+
 int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t cap,
                     size_t* n_out) {
   if (!s || !n_out) return fail(PP_EINVAL, "NULL argument");
@@ -2038,7 +2096,7 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
   const size_t nhist = (size_t)kSortBlock * tiles0;
   const uint32_t nscan = (uint32_t)((nhist + kScanTile - 1) / kScanTile);
   const size_t rows = (size_t)N * W * sizeof(uint64_t);
-  struct Ws {                               // one allocation
+  struct Ws {                              // one allocation
     pp_state* s;
     char* base;
     size_t used = 0;
@@ -2048,15 +2106,16 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
       used += align256(bytes);
       return q;
     }
-  } ws{s, (char*)dev_alloc(s, 2 * align256(sizeof(uint32_t) * N) +
-                                  align256(sizeof(uint32_t) * nhist) +
-                                  align256(sizeof(uint32_t) * (nscan + 1)) + 2 * align256(rows) +
-                                  align256(sizeof(double) * N))};
+  };
+  const int nk = samp_words(n);
+  const bool sampled =
+      N <= (nk == 1 ? samp_max<1>() : nk == 2 ? samp_max<2>() : samp_max<4>());
+  const size_t out_bytes = 2 * align256(rows) + align256(sizeof(double) * N);
+  Ws ws{s, (char*)dev_alloc(s, out_bytes + (sampled ? sample_bytes(N, nk)
+                                                    : 2 * align256(sizeof(uint32_t) * N) +
+                                                          align256(sizeof(uint32_t) * nhist) +
+                                                          align256(sizeof(uint32_t) * (nscan + 1))))};
   if (!ws.base) return fail(PP_ENOMEM, "export workspace");
-  auto* ord0 = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * N));
-  auto* ord1 = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * N));
-  auto* hist = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * nhist));
-  auto* part = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * (nscan + 1)));
   auto* ox = static_cast<uint64_t*>(ws.get(rows));
   auto* oz = static_cast<uint64_t*>(ws.get(rows));
   auto* oc = static_cast<double*>(ws.get(sizeof(double) * N));
@@ -2065,6 +2124,48 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
   // while the sort runs.
   Prefault touch;
   touch.start({{x, rows}, {z, rows}, {coef, sizeof(double) * N}});
+  auto copy_out = [&]() -> int {
+    touch.join();
+    HIP_TRY(hipMemcpyAsync(x, ox, rows, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipMemcpyAsync(z, oz, rows, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipMemcpyAsync(coef, oc, sizeof(double) * N, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    return PP_OK;
+  };
+  uint32_t total = 0;
+  if (sampled) {
+    SampSort p{};
+    p.x = s->buf.x[d.half];
+    p.z = s->buf.z[d.half];
+    p.alive = s->buf.alive[d.half][d.parity];
+    p.c = s->buf.c[d.half];
+    p.cap = C;
+    p.M = M;
+    p.N = N;
+    p.W = W;
+    p.n = n;
+    p.f32 = (int)s->buf.f32;
+    p.sync = s->d_sync;
+    p.ox = ox;
+    p.oz = oz;
+    p.oc = oc;
+    uint32_t* found = reinterpret_cast<uint32_t*>(s->h_na);
+    char* area = ws.base + ws.used;
+    if ((rc = nk == 1   ? sample_sort<1>(s, p, area, found)
+              : nk == 2 ? sample_sort<2>(s, p, area, found)
+                        : sample_sort<4>(s, p, area, found)))
+      return rc;
+    if ((rc = copy_out())) return rc;
+    if (*found != N)
+      return fail(PP_EDEVICE, "live count mismatch: " + std::to_string(*found) + " flagged, " +
+                                  std::to_string(N) + " counted");
+    *n_out = N;
+    return PP_OK;
+  }
+  auto* ord0 = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * N));
+  auto* ord1 = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * N));
+  auto* hist = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * nhist));
+  auto* part = static_cast<uint32_t*>(ws.get(sizeof(uint32_t) * (nscan + 1)));
   SortPass p{};
   p.x = s->buf.x[d.half];
   p.z = s->buf.z[d.half];
@@ -2072,7 +2173,6 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
   p.cap = C;
   uint32_t* out = ord0;
   bool first = true;
-  uint32_t total = 0;
   for (int j = 0; 32 * j < n; ++j) {
     const int bits = 2 * std::min(32, n - 32 * j);
     for (int sh = 0; sh < bits; sh += 8) {
@@ -2112,11 +2212,7 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
                      s->stream, out, N, p.x, p.z, s->buf.c[d.half], (int)s->buf.f32, C, W, ox,
                      oz, oc);
   HIP_TRY(hipGetLastError());
-  touch.join();
-  HIP_TRY(hipMemcpyAsync(x, ox, rows, hipMemcpyDeviceToHost, s->stream));
-  HIP_TRY(hipMemcpyAsync(z, oz, rows, hipMemcpyDeviceToHost, s->stream));
-  HIP_TRY(hipMemcpyAsync(coef, oc, sizeof(double) * N, hipMemcpyDeviceToHost, s->stream));
-  HIP_TRY(hipStreamSynchronize(s->stream));
+  if ((rc = copy_out())) return rc;
   *n_out = N;
   return PP_OK;
 }

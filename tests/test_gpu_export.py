@@ -175,3 +175,50 @@ def test_export_spans_tiles_and_empty_set(gpu):
         assert len(c) == 0
     finally:
         ps.close()
+
+
+def _spread(v):
+    v = v.astype(np.uint64)
+    for s, m in ((16, 0x0000FFFF0000FFFF), (8, 0x00FF00FF00FF00FF), (4, 0x0F0F0F0F0F0F0F0F),
+                 (2, 0x3333333333333333), (1, 0x5555555555555555)):
+        v = (v | (v << np.uint64(s))) & np.uint64(m)
+    return v
+
+
+# strings around the one-block size (a half of the LDS bucket), the first
+# splitters, many buckets, and past what a sample serves (radix passes), for
+# one, two and four key words
+@pytest.mark.parametrize("n,rows", [(20, 1), (20, 2), (32, 1023), (32, 1024), (32, 1025),
+                                    (32, 2049), (32, 70001), (32, (1 << 20) + 3),
+                                    (33, 1025), (48, 30011), (64, 2047), (70, 513),
+                                    (96, 1025), (128, 9001), (128, (1 << 18) + 1)])
+def test_export_order_at_the_sort_sizes(gpu, n, rows):
+    from paper_2512_12094_amd import driver
+    words = W.n_words(n)
+    rng = np.random.default_rng(rows * 131 + n)
+    mask = np.array([(1 << min(64, n - 64 * w)) - 1 for w in range(words)], dtype=np.uint64)
+    x = rng.integers(0, 1 << 63, size=(2 * rows, words), dtype=np.uint64) * np.uint64(2)
+    z = rng.integers(0, 1 << 63, size=(2 * rows, words), dtype=np.uint64) * np.uint64(2) + \
+        rng.integers(0, 2, size=(2 * rows, words), dtype=np.uint64)
+    x, z = x & mask, z & mask
+    half = rng.random(2 * rows) < 0.5          # clustered: half of them on the low qubits
+    x[half, :] &= np.uint64(0xFFFFF)
+    z[half, :] &= np.uint64(0xFFFFF)
+    both = np.unique(np.concatenate([x, z], axis=1), axis=0)
+    both = both[rng.permutation(len(both))[:rows]]
+    x, z = both[:, :words].copy(), both[:, words:].copy()
+    x[0], z[0] = 0, mask                       # Z...Z: the largest integer
+    c = np.arange(1, len(x) + 1, dtype=np.float64)
+    print(f"[case] export order n {n} rows {len(x)}", flush=True)
+    ps = driver.PauliSet(n, "none", x, z, c, gpu["handle"], gpu["alloc"])
+    ox, oz, oc = ps.export()
+    ps.close()
+    keys = []
+    for w in range(words):                     # least significant word first
+        for sh in (0, 32):
+            lo = np.uint64(0xFFFFFFFF)
+            zz, xx = (z[:, w] >> np.uint64(sh)) & lo, ((x ^ z)[:, w] >> np.uint64(sh)) & lo
+            keys.append((_spread(zz) << np.uint64(1)) | _spread(xx))
+    order = np.lexsort(keys)
+    assert np.array_equal(ox, x[order]) and np.array_equal(oz, z[order])
+    assert np.array_equal(oc, c[order])
