@@ -253,7 +253,8 @@ int pp_layer_stats(pp_state* s, uint64_t out[4]);
  * group and dtype (both halves, tables and the merge staging, as the
  * library would allocate them now; no allocation happens).  A handle that
  * has run a layer op (one-instance programs, see pp_set_layer_ops) also
- * carries its staging: 16W + 20 bytes per entry more.  A handle's
+ * carries its staging: 16W + 16 bytes per entry more (16W + 36 once closed
+ * sets outgrew their shares, and then up to 125 MB of workspace).  A handle's
  * store grows to hold its largest set with headroom (4x below 2^24
  * entries, 2x below 2^27, 1.5x above), and the old store is freed only
  * after the new one is filled.  PP_EINVAL for a bad group or size.
@@ -484,7 +485,8 @@ int pp_set_gate_fusion(int max_rotations, int lanes);
  * as the gate launches.  Results, expectations and the propagated / merged
  * counters equal those with layer ops off, bitwise.  A bucket that does not
  * fit its staging slots or the block's LDS makes the op run again with
- * another bucket count, then as its fused gate launches; after three such
+ * another bucket count, exact placement, larger blocks or the bucket in
+ * device memory, then as its fused gate launches; after three such
  * fallbacks a handle runs the gate launches throughout.  Programs built from
  * now on have them, and pp_apply_layer calls made from now on run them.  The
  * store then also carries (16W + 16) bytes of staging per entry (four times

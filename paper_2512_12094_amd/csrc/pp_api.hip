@@ -145,6 +145,9 @@ struct pp_state {
   uint32_t txn_m = 0, txn_half = 0, txn_parity = 0;
   bool shrunk = false;                 // a finished batched instance's store was compacted
   bool layer_used = false;             // layer ops ran: stores carry their staging
+  bool layer_huge = false;             // buckets past a block's LDS run from HBM
+  char* d_huge = nullptr;              // their workspace: list, then kHugeBlocks slabs
+  bool layer_exact = false;            // layer ops place their strings exactly
   bool layer_big = false;              // layer ops run with 1024-thread blocks
   bool layer_off = false;              // layer ops failed too often: their fallbacks run
   int layer_fallbacks = 0;             // layer ops that fell back (this handle)
@@ -397,7 +400,32 @@ uint32_t layer_slots(uint32_t cap) {
   return 1u << (ceil_log2(cap) + (cap <= kLayerSmallCap ? 2 : 0));
 }
 
-//
+void clear_layer(InstBuf& nb) {
+  nb.lstx = nb.lstz = nb.lsta = nb.lpat = nullptr;
+  nb.lstc = nullptr;
+  nb.lcount = nb.lbk = nb.lrank = nb.lbase = nullptr;
+  nb.lslots = nb.lmaxbits = nb.lexact = 0;
+}
+
+// The layer op's staging for nb's capacity, from take(bytes).
+template <class Take>
+bool take_layer(InstBuf& nb, int W, bool exact, Take take) {
+  nb.lslots = layer_slots(nb.cap);
+  nb.lmaxbits = layer_max_bits(nb.lslots);
+  bool ok = (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots)) != nullptr;
+  ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
+  ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
+  ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
+  ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
+  if (exact) {
+    ok = ok && (nb.lpat = (uint64_t*)take(sizeof(uint64_t) * nb.cap));
+    ok = ok && (nb.lbk = (uint32_t*)take(sizeof(uint32_t) * nb.cap));
+    ok = ok && (nb.lrank = (uint32_t*)take(sizeof(uint32_t) * nb.cap));
+    ok = ok && (nb.lbase = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
+  }
+  return ok;
+}
+
 // A store of at most kStoreBlock bytes is one allocation (a handle grows
 // through several small stores, and ~20 trips to the caller's allocator for
 // each took longer than initialising it); a larger one is an allocation per
@@ -455,21 +483,8 @@ int alloc_store(pp_state* s, uint32_t cap, InstBuf* b, std::vector<void*>* alloc
       ok = ok && (nb.plist = (uint32_t*)take(sizeof(uint32_t) * nm));
     }
     // staging of the layer op (once a layer op has run on this handle)
-    nb.lstx = nb.lstz = nullptr;
-    nb.lstc = nullptr;
-    nb.lsta = nullptr;
-    nb.lcount = nullptr;
-    nb.lslots = 0;
-    nb.lmaxbits = 0;
-    if (s->layer_used) {
-      nb.lslots = layer_slots(cap);
-      nb.lmaxbits = layer_max_bits(nb.lslots);
-      ok = ok && (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
-      ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
-      ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
-      ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
-      ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
-    }
+    clear_layer(nb);
+    if (s->layer_used) ok = ok && take_layer(nb, W, s->layer_exact, take);
     nb.mown = nullptr;
     nb.wrep = nullptr;
     nb.wslot = nullptr;
@@ -610,9 +625,17 @@ SoloFn solo_of(int kind, bool big, uint32_t nrot = 1, int lane_it = 0, int group
   }
 }
 
+// The two launches of exact placement, which stand in for the scatter.
+constexpr int kLayerRank = PP_KERNEL_KINDS, kLayerPlace = PP_KERNEL_KINDS + 1;
+constexpr int kLayerHuge = PP_KERNEL_KINDS + 2;   // and the launch behind the apply step
+
 SoloFn layer_of(int kind, int n, int W, bool big) {
   if (kind == PP_K_LAYER_SCATTER) return W == 1 ? &k_layer_scatter<1> : &k_layer_scatter<2>;
+  if (kind == kLayerRank) return W == 1 ? &k_layer_rank<1> : &k_layer_rank<2>;
+  if (kind == kLayerPlace) return W == 1 ? &k_layer_place<1> : &k_layer_place<2>;
   const int kw = layer_key_words(n, W);
+  if (kind == kLayerHuge)
+    return kw == 1 ? &k_layer_huge<1> : kw == 2 ? &k_layer_huge<2> : &k_layer_huge<4>;
   if (big)
     return kw == 1 ? &k_layer_apply<1, 1024> : kw == 2 ? &k_layer_apply<2, 1024>
                                                        : &k_layer_apply<4, 1024>;
@@ -626,35 +649,43 @@ SoloFn layer_of(int kind, int n, int W, bool big) {
 // The layer op's staging, allocated when a handle first runs one (and
 // then with every store it grows into).
 int ensure_layer(pp_state* s) {
-  if (s->buf.lcount) return PP_OK;
+  if (s->buf.lcount && (s->buf.lbase || !s->layer_exact)) return PP_OK;
   s->layer_used = true;
-  InstBuf& nb = s->buf;
-  const int W = s->W;
-  nb.lslots = layer_slots(nb.cap);
-  nb.lmaxbits = layer_max_bits(nb.lslots);
+  InstBuf nb = s->buf;
   std::vector<void*> got;
   auto take = [&](size_t bytes) -> void* {
     void* p = dev_alloc(s, bytes);
     if (p) got.push_back(p);
     return p;
   };
-  bool ok = (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots)) != nullptr;
-  ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
-  ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
-  ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
-  ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
-  if (!ok) {
+  clear_layer(nb);
+  if (!take_layer(nb, s->W, s->layer_exact, take)) {
     for (void* p : got) dev_free(s, p);
-    nb.lstx = nb.lstz = nullptr;
-    nb.lstc = nullptr;
-    nb.lsta = nullptr;
-    nb.lcount = nullptr;
-    nb.lslots = nb.lmaxbits = 0;
     return fail(PP_ENOMEM, "allocation of the layer staging failed");
   }
   HIP_TRY(hipMemsetAsync(nb.lcount, 0, sizeof(uint32_t) << nb.lmaxbits, s->stream));
+  // (a staging that is replaced is freed with the store)
   for (void* p : got) s->store.push_back(p);
+  s->buf = nb;
   return upload_buf(s);
+}
+
+// Staging with exact placement; false (and the staging stays as it is) if its
+// memory is not to be had.
+bool ensure_exact(pp_state* s) {
+  s->layer_exact = true;
+  s->layer_exact = ensure_layer(s) == PP_OK;
+  return s->layer_exact;
+}
+
+// The workspace of buckets that outgrow a block's LDS (from then on kept by
+// the handle): 75 to 125 MB.
+int ensure_huge(pp_state* s) {
+  if (s->d_huge) return PP_OK;
+  const int kw = layer_key_words(s->n, s->W);
+  const size_t slab = kw == 1 ? huge_slab<1>() : kw == 2 ? huge_slab<2>() : huge_slab<4>();
+  s->d_huge = (char*)dev_alloc(s, kHugeListBytes + kHugeBlocks * slab);
+  return s->d_huge ? PP_OK : fail(PP_ENOMEM, "allocation of the layer workspace failed");
 }
 
 int items_of(int kind, bool big = false) {
@@ -859,14 +890,26 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
       Solo S;
       S.b = s->buf;
       if (small) S.b.nopart = 1;
+      // (only here: the batched form, which reads d_buf, scatters to equal slots)
+      S.b.lexact = s->layer_exact && s->buf.lbase ? 1u : 0u;
+      S.b.lhuge = s->layer_huge ? s->d_huge : nullptr;
       S.d = s->d_dyn;
       S.sync = s->d_sync;
       S.k = (uint32_t)k;
-      if (layer)
-        hipLaunchKernelGGL(layer_of(kind, s->n, s->W, s->layer_big), dim3(grid), dim3(block), 0, s->stream, S);
+      if (kind == PP_K_LAYER_SCATTER && S.b.lexact) {
+        hipLaunchKernelGGL(layer_of(kLayerRank, s->n, s->W, false), dim3(grid), dim3(block), 0,
+                           s->stream, S);
+        hipLaunchKernelGGL(layer_of(kLayerPlace, s->n, s->W, false), dim3(grid), dim3(block), 0,
+                           s->stream, S);
+      } else if (layer)
+        hipLaunchKernelGGL(layer_of(kind, s->n, s->W, s->layer_big), dim3(grid), dim3(block), 0,
+                           s->stream, S);
       else
         hipLaunchKernelGGL(solo_of(kind, big, nrot, lane_it, s->group), dim3(grid), dim3(block),
                            part_lds(s->buf, kind), s->stream, S);
+      if (kind == PP_K_LAYER_APPLY && s->layer_huge)
+        hipLaunchKernelGGL(layer_of(kLayerHuge, s->n, s->W, true), dim3(kHugeBlocks), dim3(1024), 0,
+                           s->stream, S);
       ++run_len;
     }
   }
@@ -1007,15 +1050,25 @@ void append_rotation(std::vector<double>& tab, const Op& op) {
 
 // The one-rotation ops [from, to) commute pairwise.
 bool all_commute(const std::vector<Op>& ops, size_t from, size_t to, int W) {
+  // strings of one letter each (x or z absent, or equal) commute: the usual
+  // sub-layer, without the pairwise check
+  bool letter[3] = {true, true, true};
   for (size_t a = from; a < to; ++a) {
     if (ops[a].type != OP_GATE) return false;
+    for (int w = 0; w < W; ++w) {
+      letter[0] = letter[0] && ops[a].pz[w] == 0;
+      letter[1] = letter[1] && ops[a].px[w] == 0;
+      letter[2] = letter[2] && ops[a].px[w] == ops[a].pz[w];
+    }
+  }
+  if (letter[0] || letter[1] || letter[2]) return true;
+  for (size_t a = from; a < to; ++a)
     for (size_t c = a + 1; c < to; ++c) {
       int odd = 0;
       for (int w = 0; w < W; ++w)
         odd += __builtin_popcountll((ops[a].px[w] & ops[c].pz[w]) ^ (ops[a].pz[w] & ops[c].px[w]));
       if (odd & 1) return false;
     }
-  }
   return true;
 }
 
@@ -1332,6 +1385,7 @@ void pp_destroy(pp_state* s) {
   dev_free(s, s->d_core);
   dev_free(s, s->d_gperm);
   dev_free(s, s->d_act);
+  dev_free(s, s->d_huge);
   prof_resolve(s);
   for (hipEvent_t e : s->pool) (void)hipEventDestroy(e);
   host_block_put(s);
@@ -2490,11 +2544,12 @@ int ensure_graph(BatchCtx* b) {
 // leaves a batch at a step boundary) instead of starting the program.
 // A layer op at pc reported a bucket that did not fit (ST_LAYER; h_dyn is
 // fresh and the device idles behind it): grow a crowded store, else run it
-// again with fewer buckets (staging slots overflowed), with larger blocks and
-// then more buckets (the LDS overflowed), at most kLayerRetries times, else
-// run its GATE(S) copies instead.  Larger blocks stay for the handle: closed
-// sets that outgrow 2048 strings come back in later sub-layers, and on sets
-// that fit either they cost 3%.
+// again with exact placement (staging slots overflowed), with larger blocks,
+// then with buckets past those in HBM (the LDS overflowed), then with other
+// bucket counts, at most kLayerRetries times, else run its GATE(S) copies
+// instead.  What is turned on stays for the handle: closed sets that outgrow
+// 2048 strings come back in later sub-layers, and on sets that fit they cost
+// 3% (larger blocks) and 3 us (an idle launch) a layer op.
 // After kLayerGiveUp fallbacks the handle runs the copies in place of every
 // layer op.
 constexpr int kLayerGiveUp = 3;
@@ -2516,13 +2571,23 @@ int layer_failed(pp_state* s, const Op* ops, size_t len, bool grew) {
     }
     const int32_t step = h.lwhy & 1u ? -1 : 1;
     const int32_t next = h.lboost + step;
+    // (half the buckets first: exact placement takes one launch and one pass
+    // over the set more in every later layer op, 7.3 -> 8.5 ms on the unmerged
+    // Z_32 ring, which needs that once)
+    const bool exact = !ops[k].fail_test && (h.lwhy & 1u) && !s->layer_exact && h.lboost < 0;
     const bool enlarge = !ops[k].fail_test && !(h.lwhy & 1u) && !s->layer_big;
     if (!ops[k].fail_test && (h.lwhy & 1u) && grew) {
       // the op ran in the store before the last growth: again, in the new one
+    } else if (exact && ensure_exact(s)) {
+      h.lboost = 0;                            // no bucket overflows its slots from here on
+      HIP_TRY(hipMemcpyAsync(&s->d_dyn->lboost, &h.lboost, sizeof(int32_t),
+                             hipMemcpyHostToDevice, s->stream));
     } else if (!ops[k].fail_test && (h.lwhy & 1u) && (uint64_t)h.M * 3 > s->buf.cap) {
       if ((rc = grow(s))) return rc;           // more staging slots per bucket
     } else if (enlarge) {
       s->layer_big = true;                     // twice the strings per bucket, from here on
+    } else if (!ops[k].fail_test && (h.lwhy & 2u) && !s->layer_huge && ensure_huge(s) == PP_OK) {
+      s->layer_huge = true;                    // and those that outgrow that in HBM
     } else if (!ops[k].fail_test && next >= -kLayerMaxBoost && next <= kLayerMaxBoost &&
                !s->layer_tried[next + kLayerMaxBoost] && s->layer_retries < kLayerRetries) {
       ++s->layer_retries;

@@ -47,7 +47,8 @@ __host__ __device__ __forceinline__ int layer_key_words(int n, int W) {
 template <int KW, int NB>
 constexpr int layer_cap() {
   constexpr int n = KW == 1 ? 2048 : KW == 2 ? 1792 : 1024;
-  return NB == 1024 ? 2 * n : n;
+  // (one word: room beside a full set of 2^12 strings)
+  return NB == 1024 ? (KW == 1 ? 4608 : 2 * n) : n;
 }
 
 // Bucket bits for a layer op over M entries: about 2^shift strings per
@@ -209,6 +210,95 @@ __global__ __launch_bounds__(kBlock) void k_layer_scatter(Solo S) {
   if (over) atomicOr(&d.lfail, 1u);        // a bucket's staging slots overflowed
 }
 
+// Exact placement (one-instance path, once a bucket's staging slots have
+// overflowed on the handle): closed sets of thousands of strings do not fit
+// equal shares of the staging, so the strings are counted first.
+// k_layer_rank computes every string's pattern, bucket and rank in it (the
+// count kernel's LDS counts and one global add per block and bucket, as the
+// scatter does) and its last block turns the counts into bucket bases;
+// k_layer_place moves the strings to base + rank.  One launch more than the
+// scatter, ~15 us at 10^6 strings, where a failed op's gate launches cost ms.
+template <int WW>
+__global__ __launch_bounds__(kBlock) void k_layer_rank(Solo S) {
+  __shared__ ScatterSh<WW> sh;
+  __shared__ uint32_t s_tmp[kWaves + 1], s_flag;
+  const InstBuf& b = S.b;
+  InstDyn& d = *S.d;
+  if (d.pc != S.k) return;                 // an earlier op did not complete
+  const Op& op = b.prog[S.k];
+  load_rot_strings<WW, kBlock>(op, sh.px, sh.pz);
+  const uint32_t M = op.fail_test ? 0u : d.M;
+  const uint32_t bits = layer_bits(d.M, d.lboost, b.lmaxbits, b.lshift), P = 1u << bits;
+  const bool agg = P <= (uint32_t)kLAggMax;
+  const uint32_t rounds = (M + kBlock - 1) / kBlock, workers = worker_count(rounds);
+  if (blockIdx.x >= workers) return;
+  const View v = view_of(b, d);
+  for (uint32_t t = blockIdx.x; t < rounds; t += gridDim.x) {
+    __syncthreads();
+    if (agg)
+      for (uint32_t k = threadIdx.x; k < P; k += kBlock) sh.cnt[k] = 0;
+    __syncthreads();                       // rotations loaded, counts zero
+    const uint32_t i = t * kBlock + threadIdx.x;
+    const bool has = i < M && v.al[i];
+    uint32_t bk = kNone32, rank = 0;
+    if (has) {
+      uint64_t x[WW], z[WW], a;
+#pragma unroll
+      for (int w = 0; w < WW; ++w) {
+        x[w] = v.X[(size_t)w * v.cap + i];
+        z[w] = v.Z[(size_t)w * v.cap + i];
+      }
+      const uint64_t h = layer_key<WW>(x, z, op.nrot, sh.px, sh.pz, &a);
+      bk = bits ? (uint32_t)(h >> (64 - bits)) : 0u;
+      rank = agg ? atomicAdd(&sh.cnt[bk], 1u) : atomicAdd(&b.lcount[bk], 1u);
+      b.lpat[i] = a;
+    }
+    if (agg) {
+      __syncthreads();
+      for (uint32_t k = threadIdx.x; k < P; k += kBlock) {
+        const uint32_t n = sh.cnt[k];
+        sh.cnt[k] = n ? atomicAdd(&b.lcount[k], n) : 0u;
+      }
+      __syncthreads();
+      if (has) rank += sh.cnt[bk];
+    }
+    if (i < M) b.lbk[i] = bk;
+    if (has) b.lrank[i] = rank;
+  }
+  if (!last_block(S.sync, &s_flag, workers)) return;
+  __syncthreads();
+  uint32_t carry = 0;                      // the last block: bucket bases
+  for (uint32_t k0 = 0; k0 < P; k0 += kBlock) {
+    const uint32_t k = k0 + threadIdx.x, n = k < P ? ld_agent(&b.lcount[k]) : 0u;
+    uint32_t total;
+    const uint32_t off = block_scan(n, s_tmp, &total);
+    if (k < P) b.lbase[k] = carry + off;
+    carry += total;
+  }
+  if (threadIdx.x == 0 && op.fail_test) atomicOr(&d.lfail, 1u);
+}
+
+template <int WW>
+__global__ __launch_bounds__(kBlock) void k_layer_place(Solo S) {
+  const InstBuf& b = S.b;
+  InstDyn& d = *S.d;
+  if (d.pc != S.k) return;
+  const uint32_t M = b.prog[S.k].fail_test ? 0u : d.M, L = b.lslots;
+  const View v = view_of(b, d);
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < M; i += gridDim.x * kBlock) {
+    const uint32_t bk = b.lbk[i];
+    if (bk == kNone32) continue;
+    const uint32_t pos = b.lbase[bk] + b.lrank[i];   // < the live strings <= lslots
+#pragma unroll
+    for (int w = 0; w < WW; ++w) {
+      b.lstx[(size_t)w * L + pos] = v.X[(size_t)w * v.cap + i];
+      b.lstz[(size_t)w * L + pos] = v.Z[(size_t)w * v.cap + i];
+    }
+    b.lstc[pos] = v.getc(i);
+    b.lsta[pos] = b.lpat[i];
+  }
+}
+
 // An instance of a batch takes the layer op when it stands at one with
 // staging, its key width matches the kernel's and nothing stopped it.
 template <int WW>
@@ -339,12 +429,12 @@ __device__ __forceinline__ uint32_t lk_hash(const uint64_t* k) {
 // The bucket's hash table: open addressing, linear probing, 32-bit entries: a
 // string's index + 1 in the low IB bits (0: empty) and the hash's low bits
 // as a tag above, so that a probe of another string's slot hardly ever costs
-// a key compare.  At most half full.
+// a key compare.  At most 4/7 full.
 template <int CAP>
 struct LdsTab {
-  static constexpr int HB = 33 - __builtin_clz(CAP - 1), HS = 1 << HB;
+  static constexpr int HB = 32 - __builtin_clz(CAP + CAP / 2 + CAP / 4 - 1), HS = 1 << HB;
   static constexpr int IB = HB;            // CAP < 2^IB
-  static_assert(HS >= 2 * CAP && CAP < (1 << IB), "at most half full");
+  static_assert(4 * HS >= 7 * CAP && CAP < (1 << IB), "at most 4/7 full");
   __device__ __forceinline__ static uint32_t slot(uint32_t h) { return h >> (32 - HB); }
   __device__ __forceinline__ static uint32_t tagged(uint32_t h) { return h << IB; }
   __device__ __forceinline__ static bool tag_is(uint32_t e, uint32_t tg) {
@@ -591,24 +681,47 @@ __device__ __forceinline__ uint16_t life_of(uint32_t born, uint32_t died) {
 // with a block barrier after it; then the survivors go to the other half.
 // Live counts before each rotation follow from the strings entering and the
 // births and drops of the rotations before it.
-template <int KW, int NB>
-struct ApplySh {
-  static constexpr int CAP = layer_cap<KW, NB>(), HS = LdsTab<CAP>::HS, NW = NB / 64, NS = 7;
-  static constexpr int WW = KW == 1 ? 1 : KW / 2;
+// A bucket's strings: in LDS, or (k_layer_huge) in HBM.
+template <int KW, int CAP_>
+struct alignas(16) BucketMem {
+  static constexpr int CAP = CAP_, HS = LdsTab<CAP>::HS;
   uint64_t k[KW][CAP];
   double c[CAP];
   uint64_t a[CAP];                         // rotations still to run on the string
   uint32_t hash[HS];                       // LdsTab entries
   uint16_t life[CAP];
+};
+
+// Buckets that outgrow a block's LDS (at most kHugeList of an op): a list of
+// (bucket, strings), then a slab per block of k_layer_huge.
+constexpr uint32_t kHugeList = 1024;
+constexpr int kHugeBlocks = 64, kHugeCap = 32768;
+constexpr size_t kHugeListBytes = 2 * sizeof(uint32_t) * kHugeList;
+template <int KW> constexpr size_t huge_slab() {
+  return (sizeof(BucketMem<KW, kHugeCap>) + 255) / 256 * 256;
+}
+
+// What a block keeps in LDS beside its bucket's strings.
+template <int KW, int NB>
+struct ApplyCtl {
+  static constexpr int NW = NB / 64, NS = 7;
+  static constexpr int WW = KW == 1 ? 1 : KW / 2;
+  static_assert(NB >= kAccShards * 8, "one thread per shard entry (layer_end)");
   struct Rot {
     uint64_t p[KW];
     double cs, sn;
   } rot[kLayerMaxRot];
   uint32_t steps;                          // most rotations any string of the bucket takes
-  uint32_t inc[3], n0, fail, flag, tmp[NW + 1], base;
+  uint32_t inc[3], fail, flag, tmp[NW + 1], base;
   uint32_t red[NW][NS];
   uint64_t fold[kAccShards][NS + 1];
 };
+
+template <int KW, int NB>
+struct ApplySh : ApplyCtl<KW, NB> {
+  BucketMem<KW, layer_cap<KW, NB>()> mem;
+};
+
 
 // Per-thread sums of one instance: live before each rotation (as r *
 // entering + weighted births - drops), anticommuting, survivors, survivors
@@ -623,8 +736,8 @@ struct LayerSums {
 
 template <int KW, int NB>
 __device__ __forceinline__ void load_rotations(const double* table, uint32_t nrot,
-                                               ApplySh<KW, NB>& sh) {
-  constexpr int WW = ApplySh<KW, NB>::WW;
+                                               ApplyCtl<KW, NB>& sh) {
+  constexpr int WW = ApplyCtl<KW, NB>::WW;
   for (uint32_t g = threadIdx.x; g < nrot; g += NB) {
     uint64_t x[WW], z[WW], k[KW];
 #pragma unroll
@@ -641,9 +754,10 @@ __device__ __forceinline__ void load_rotations(const double* table, uint32_t nro
   }
 }
 
-// Bucket bk of one instance (bits: the op's bucket bits).  Every thread of
-// the block calls it; it starts with a barrier (the LDS of the previous
-// bucket, and the rotations, are then free and loaded).
+// Bucket bk of one instance (bits: the op's bucket bits; cnt: its strings),
+// with its strings in mm.  Every thread of the block calls it; it starts with
+// a barrier (the memory of the previous bucket, and the rotations, are then
+// free and loaded).  False if the bucket does not fit mm (uniform).
 //
 // Step q runs every string's q-th own rotation: the strings of one closed set
 // anticommute with the same rotations, so they are at the same one, and sets
@@ -654,16 +768,17 @@ __device__ __forceinline__ void load_rotations(const double* table, uint32_t nro
 // bounds the kernel (a step of one wave measured about 5 cycles per
 // instruction, LDS round trips included).  The loops over a thread's strings
 // stay rolled: a launch starts with a cold instruction cache.
-template <int KW, int NB>
-__device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const LayerArgs& op,
-                                             uint32_t bits, uint32_t bk, ApplySh<KW, NB>& sh,
-                                             LayerSums& sum) {
-  using Sh = ApplySh<KW, NB>;
-  constexpr int CAP = Sh::CAP, HS = Sh::HS, WW = Sh::WW;
+template <int KW, int NB, class Mem>
+__device__ __forceinline__ bool apply_bucket(const InstBuf& b, InstDyn& d, const LayerArgs& op,
+                                             uint32_t bits, uint32_t bk, uint32_t cnt,
+                                             ApplyCtl<KW, NB>& sh, Mem& mm, LayerSums& sum) {
+  using Sh = ApplyCtl<KW, NB>;
+  constexpr int CAP = Mem::CAP, HS = Mem::HS, WW = Sh::WW;
   using T = LdsTab<CAP>;
   const uint32_t r = op.nrot;
-  const uint32_t slots = b.lslots >> bits;
-  const uint32_t cnt = b.lcount[bk];       // (zeroed by thread 0 past the barriers)
+  // (exact placement: the bucket's own base, and no limit but the staging)
+  const uint32_t slots = b.lexact ? b.lslots : b.lslots >> bits;
+  const size_t base = b.lexact ? (size_t)b.lbase[bk] : (size_t)bk * slots;
   __syncthreads();
   if (threadIdx.x == 0) {
     sh.fail = 0;
@@ -671,11 +786,10 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
     sh.steps = 0;
   }
   for (int t = threadIdx.x; t < HS / 4; t += NB)
-    reinterpret_cast<uint4*>(sh.hash)[t] = make_uint4(0, 0, 0, 0);
+    reinterpret_cast<uint4*>(mm.hash)[t] = make_uint4(0, 0, 0, 0);
   __syncthreads();
-  if (threadIdx.x == 0) b.lcount[bk] = 0;  // zero for the next layer op
   const uint32_t n0 = __builtin_amdgcn_readfirstlane(cnt < slots ? cnt : slots);
-  if (n0 > (uint32_t)CAP) { sum.bad = true; return; }   // uniform
+  if (n0 > (uint32_t)CAP) return false;                // uniform
   const double eps = op.eps;
   const int wmax = op.wmax;
   const bool full = op.full, f32 = b.f32 != 0;
@@ -684,7 +798,7 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
     sum.lw += (int32_t)(r * n0);
   }
   {
-    const size_t base = (size_t)bk * slots, L = b.lslots;
+    const size_t L = b.lslots;
     uint32_t most = 0;
 #pragma unroll 1
     for (uint32_t j = threadIdx.x; j < n0; j += NB) {
@@ -698,16 +812,16 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
       const uint64_t a = b.lsta[base + j];
       lk_pack<KW>(x, z, k);
 #pragma unroll
-      for (int w = 0; w < KW; ++w) sh.k[w][j] = k[w];
-      sh.c[j] = c;
-      sh.a[j] = a;
+      for (int w = 0; w < KW; ++w) mm.k[w][j] = k[w];
+      mm.c[j] = c;
+      mm.a[j] = a;
       // the op's first rotation re-checks every string: one that commutes
       // with it is checked here and leaves after that rotation
       const bool drop = full && !(a & 1ull) && !(fabs(c) >= eps && !lk_heavy<KW>(k, wmax));
-      sh.life[j] = life_of(0, drop ? 0u : kAlive);
+      mm.life[j] = life_of(0, drop ? 0u : kAlive);
       if (drop) sum.lw -= (int32_t)(r - 1);
       const uint32_t h = lk_hash<KW>(k);
-      T::insert(sh.hash, h, j, T::slot(h));
+      T::insert(mm.hash, h, j, T::slot(h));
       most = max(most, (uint32_t)__popcll(a));
     }
     most = wave_max63(most);
@@ -723,16 +837,16 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
     for (uint32_t j = threadIdx.x; j < ng; j += NB) {
       // (a coefficient read here is used only by a string that leads its
       // pair or has none, and no other thread writes those)
-      const uint64_t rem = sh.a[j];
-      const uint32_t life = sh.life[j];
-      const double cq = sh.c[j];
+      const uint64_t rem = mm.a[j];
+      const uint32_t life = mm.life[j];
+      const double cq = mm.c[j];
       uint64_t qk[KW], rk[KW];
 #pragma unroll
-      for (int w = 0; w < KW; ++w) qk[w] = sh.k[w][j];
+      for (int w = 0; w < KW; ++w) qk[w] = mm.k[w][j];
       if (rem == 0) continue;
       const uint32_t g = (uint32_t)__builtin_ctzll(rem);
       const uint64_t left = rem & (rem - 1);
-      sh.a[j] = left;
+      mm.a[j] = left;
       if (!live_before(life, g)) continue;
       const typename Sh::Rot rot = sh.rot[g];
 #pragma unroll
@@ -745,15 +859,15 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
       double cp = 0.0;
 #pragma unroll 1
       for (int probe = 0; probe < HS; ++probe) {
-        const uint32_t e = T::entry(sh.hash, sl);
+        const uint32_t e = T::entry(mm.hash, sl);
         if (e == 0) break;
         if (T::tag_is(e, tg)) {
           const uint32_t m = T::index(e);
           bool eq = m < ng;
 #pragma unroll
-          for (int w = 0; w < KW; ++w) eq = eq & (sh.k[w][m] == rk[w]);
-          plife = sh.life[m];
-          cp = sh.c[m];
+          for (int w = 0; w < KW; ++w) eq = eq & (mm.k[w][m] == rk[w]);
+          plife = mm.life[m];
+          cp = mm.c[m];
           if (eq) { p = m; break; }
         }
         sl = (sl + 1) & (HS - 1);
@@ -773,26 +887,26 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
       sum.lw += (int32_t)(r - 1 - g) *
                 ((born ? 1 : 0) - (keep_q ? 0 : 1) - (plive && !keep_r ? 1 : 0));
       sum.ch += born ? 1u : 0u;
-      sh.c[j] = nq;
-      if (!keep_q) sh.life[j] = life_of(life >> 8, g);
+      mm.c[j] = nq;
+      if (!keep_q) mm.life[j] = life_of(life >> 8, g);
       if (!found && born) {
         p = ng + atomicAdd(&sh.inc[q % 3], 1u);
         if (p < (uint32_t)CAP) {
 #pragma unroll
-          for (int w = 0; w < KW; ++w) sh.k[w][p] = rk[w];
-          sh.a[p] = left;
-          T::insert(sh.hash, rh, p, sl);
+          for (int w = 0; w < KW; ++w) mm.k[w][p] = rk[w];
+          mm.a[p] = left;
+          T::insert(mm.hash, rh, p, sl);
         } else {
           sh.fail = 1;
           p = kNone32;
         }
       }
       if (p != kNone32 && (plive || born)) {
-        sh.c[p] = nr;
+        mm.c[p] = nr;
         if (born)
-          sh.life[p] = life_of(g + 1, kAlive);
+          mm.life[p] = life_of(g + 1, kAlive);
         else if (!keep_r)
-          sh.life[p] = life_of(plife >> 8, g);
+          mm.life[p] = life_of(plife >> 8, g);
       }
     }
     __syncthreads();
@@ -800,9 +914,40 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
     ng = ng + add < (uint32_t)CAP ? ng + add : (uint32_t)CAP;
   }
   if (threadIdx.x == 0) sum.held += ng;
-  if (sh.fail) { sum.bad = true; return; }  // uniform: read after the last barrier
-  emit_survivors<KW, NB, CAP>(b, d, op, sh.k, sh.c, sh.life, ng, sh.tmp, &sh.base, &sum.out,
+  if (sh.fail) return false;               // uniform: read after the last barrier
+  emit_survivors<KW, NB, CAP>(b, d, op, mm.k, mm.c, mm.life, ng, sh.tmp, &sh.base, &sum.out,
                               &sum.nx);
+  return true;
+}
+
+// apply_bucket from the block's LDS; a bucket that outgrows it goes on the list
+// of k_layer_huge (its sums undone; its strings are still staged) or, without
+// one, fails the op.
+template <int KW, int NB>
+__device__ __forceinline__ void apply_or_list(const InstBuf& b, InstDyn& d, const LayerArgs& op,
+                                              uint32_t bits, uint32_t bk, ApplySh<KW, NB>& sh,
+                                              LayerSums& sum, char* huge) {
+  const uint32_t cnt = b.lcount[bk];
+  const LayerSums before = sum;
+  const bool ok = apply_bucket<KW, NB>(b, d, op, bits, bk, cnt, sh, sh.mem, sum);
+  // (every thread has read the count: apply_bucket has barriers)
+  if (threadIdx.x == 0) b.lcount[bk] = 0;  // zero for the next layer op
+  if (ok) return;
+  sum = before;
+  if (!huge) {
+    sum.bad = true;
+    return;
+  }
+  if (threadIdx.x == 0) {
+    const uint32_t e = atomicAdd(&d.lnhuge, 1u);
+    uint32_t* list = reinterpret_cast<uint32_t*>(huge);
+    if (e < kHugeList) {
+      list[2 * e] = bk;
+      list[2 * e + 1] = cnt;
+    } else {
+      consume(atomicOr(&d.lfail, 2u));     // too many of them
+    }
+  }
 }
 
 // The block's sums of one instance to its shard line (entries 1..NS) and
@@ -811,9 +956,9 @@ __device__ __forceinline__ void apply_bucket(const InstBuf& b, InstDyn& d, const
 // rotations of its buckets' strings).  The atomics have returned when the
 // threads leave, so the last block needs no fence to read their totals.
 template <int KW, int NB>
-__device__ __forceinline__ void flush_sums(const InstBuf& b, InstDyn& d, ApplySh<KW, NB>& sh,
+__device__ __forceinline__ void flush_sums(const InstBuf& b, InstDyn& d, ApplyCtl<KW, NB>& sh,
                                            LayerSums& sum) {
-  constexpr int NS = ApplySh<KW, NB>::NS, NW = ApplySh<KW, NB>::NW;
+  constexpr int NS = ApplyCtl<KW, NB>::NS, NW = ApplyCtl<KW, NB>::NW;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint32_t v[NS] = {(uint32_t)sum.lw, sum.an, sum.out, sum.nx, sum.ch, sum.held, sum.in};
   __syncthreads();
@@ -834,10 +979,30 @@ __device__ __forceinline__ void flush_sums(const InstBuf& b, InstDyn& d, ApplySh
   sum = LayerSums();
 }
 
+// Last block of a layer op, every thread: folds the shard lines, one thread per
+// entry, and finishes.
+template <class Sh>
+__device__ __forceinline__ void layer_end(const InstBuf& b, InstDyn& d, const Op& op, Sh& sh) {
+  __syncthreads();
+  if (threadIdx.x < kAccShards * 8) {
+    const uint32_t s = threadIdx.x >> 3, k = threadIdx.x & 7;
+    sh.fold[s][k] = k < (uint32_t)Sh::NS
+        ? atomicExch((unsigned long long*)&b.accs[s * kLineU64 + 1 + k], 0ull) : 0ull;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < kAccShards; ++s)
+#pragma unroll
+      for (int k = 0; k < Sh::NS; ++k) t[k] += sh.fold[s][k];
+    layer_finish(b, d, op, t, false);
+  }
+}
+
 template <int KW, int NB>
 __global__ __launch_bounds__(NB) void k_layer_apply(Solo S) {
-  using Sh = ApplySh<KW, NB>;
-  __shared__ Sh sh;
+  __shared__ ApplySh<KW, NB> sh;
   const InstBuf& b = S.b;
   InstDyn& d = *S.d;
   const Op& op = b.prog[S.k];              // S.k < prog_len
@@ -859,29 +1024,56 @@ __global__ __launch_bounds__(NB) void k_layer_apply(Solo S) {
       if (threadIdx.x == 0) b.lcount[bk] = 0;
       continue;
     }
-    apply_bucket<KW, NB>(b, d, la, bits, bk, sh, sum);
+    apply_or_list<KW, NB>(b, d, la, bits, bk, sh, sum, b.lhuge);
     if (++done % kLayerFlush == 0) flush_sums<KW, NB>(b, d, sh, sum);
   }
   flush_sums<KW, NB>(b, d, sh, sum);
   if (!last_block(S.sync, &sh.flag, gridDim.x, false)) return;
-  // the shard lines, all at once
-  static_assert(NB >= kAccShards * 8, "one thread per shard entry");
-  if (threadIdx.x < kAccShards * 8) {
-    const uint32_t s = threadIdx.x >> 3, k = threadIdx.x & 7;
-    sh.fold[s][k] = k < (uint32_t)Sh::NS
-        ? atomicExch((unsigned long long*)&b.accs[s * kLineU64 + 1 + k], 0ull) : 0ull;
+  if (threadIdx.x == 0) {                  // (sh.flag may still be being read)
+    const uint32_t n = ld_agent(&d.lnhuge), why = ld_agent(&d.lfail);
+    if (why) d.lnhuge = 0;
+    sh.base = n && !why ? 1u : 0u;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int s = 0; s < kAccShards; ++s)
-#pragma unroll
-      for (int k = 0; k < Sh::NS; ++k) t[k] += sh.fold[s][k];
-    layer_finish(b, d, op, t, false);
-  }
+  if (sh.base) return;                     // k_layer_huge, launched behind this, ends the op
+  layer_end(b, d, op, sh);
 }
 
+// The buckets that outgrew a block's LDS, a block each, over slabs of HBM (L2,
+// mostly: a slab is ~1 MB): an LDS round trip becomes an L2 one, so a bucket
+// of 10^4 strings takes some hundred us, where running the sub-layer as gate
+// launches for their sake takes milliseconds.  With exact placement, whole
+// propagations: Z_32 ring grown to 8x10^6 strings 60 -> 39 ms, untruncated
+// 12-qubit Ising ring 27 -> 18 ms (their later sub-layers were gate launches).
+template <int KW>
+__global__ __launch_bounds__(1024) void k_layer_huge(Solo S) {
+  __shared__ ApplyCtl<KW, 1024> sh;
+  const InstBuf& b = S.b;
+  InstDyn& d = *S.d;
+  // nothing listed: the apply step ended the op (well, or with a failure that
+  // leaves pc); lnhuge changes only in the last block, when all have read it
+  const uint32_t listed = d.lnhuge;
+  if (d.pc != S.k || !b.lhuge || !listed) return;
+  const Op& op = b.prog[S.k];
+  const uint32_t n = listed < kHugeList ? listed : kHugeList;
+  const LayerArgs la = layer_args(op);
+  load_rotations(la.table, la.nrot, sh);
+  const uint32_t bits = layer_bits(d.M, d.lboost, b.lmaxbits, b.lshift);
+  const uint32_t* list = reinterpret_cast<const uint32_t*>(b.lhuge);
+  auto& mm = *reinterpret_cast<BucketMem<KW, kHugeCap>*>(b.lhuge + kHugeListBytes +
+                                                         blockIdx.x * huge_slab<KW>());
+  LayerSums sum;
+  uint32_t done = 0;
+  for (uint32_t e = blockIdx.x; e < n; e += gridDim.x) {
+    if (!apply_bucket<KW, 1024>(b, d, la, bits, list[2 * e], list[2 * e + 1], sh, mm, sum))
+      sum.bad = true;
+    if (++done % kLayerFlush == 0) flush_sums(b, d, sh, sum);
+  }
+  flush_sums(b, d, sh, sum);
+  if (!last_block(S.sync, &sh.flag, gridDim.x, false)) return;
+  if (threadIdx.x == 0) d.lnhuge = 0;
+  layer_end(b, d, op, sh);
+}
 // Block scan for NB-thread blocks over instances (as plan_tiles).
 template <int NB, class F>
 __device__ __forceinline__ uint32_t plan_tiles_n(int ninst, F tiles, uint32_t* s_pref,
@@ -948,7 +1140,7 @@ __global__ __launch_bounds__(NB) void k_layer_apply_multi(Ctx C) {
       if (threadIdx.x == 0) b.lcount[bk] = 0;
       continue;
     }
-    apply_bucket<KW, NB>(b, d, la, bits, bk, sh, sum);
+    apply_or_list<KW, NB>(b, d, la, bits, bk, sh, sum, nullptr);
     if (++done % kLayerFlush == 0) flush_sums<KW, NB>(b, d, sh, sum);
   }
   if (cur >= 0) flush_sums<KW, NB>(*C.bufs[cur], *C.dyns[cur], sh, sum);

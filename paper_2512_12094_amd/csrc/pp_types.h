@@ -122,9 +122,10 @@ constexpr int kPartProbe = 64;       // probes before the LDS table refuses a ke
 //      other half of the store.
 // Within a bucket step q runs every string's q-th own rotation, so a bucket
 // takes as many steps as its string with the most rotations.  A bucket that
-// does not fit its staging slots or the LDS fails the op; the host then
-// retries it with another bucket count, then falls back to the op's GATE(S)
-// copies.
+// does not fit its staging slots or the LDS fails the op, and the host runs it
+// again: with half the buckets, then with exact placement (k_layer_rank,
+// k_layer_place); with larger blocks, then with the buckets that outgrow them
+// in HBM (k_layer_huge); last as the op's GATE(S) copies.
 constexpr int kLayerMaxRot = 64;
 constexpr int kLayerMinRot = 4;
 constexpr int kLayerShift = 8;        // strings per bucket aimed at: 2^8 (default)
@@ -213,6 +214,13 @@ struct InstBuf {
   uint32_t lslots;       // staging slots (a power of two)
   uint32_t lmaxbits;     // largest bucket bits (lslots >> lmaxbits >= kLayerMinSlots)
   uint32_t lshift;       // log2 of the strings per bucket aimed at (tuning)
+  // exact placement (allocated once a bucket's staging slots overflowed)
+  uint64_t* lpat;        // [cap] anticommutation pattern of each string
+  uint32_t* lbk;         // [cap] its bucket (kNone32: dead)
+  uint32_t* lrank;       // [cap] its rank in the bucket
+  uint32_t* lbase;       // [2^lmaxbits] first staging slot of each bucket
+  uint32_t lexact;       // the staging is placed exactly
+  char* lhuge;           // list and slabs of buckets that outgrow the LDS, or null
   uint32_t nolayer;      // LAYER ops are skipped (their fallback ops run)
   const Op* prog;
   uint32_t prog_len;
@@ -276,6 +284,8 @@ struct InstDyn {
   uint32_t lfb;          // layer ops the batched form replaced by their gate copies
   uint32_t lserved;      // batched form: this step's scatter took the instance's layer op
   uint32_t lfail;        // layer op: a bucket overflowed its slots or the LDS
+  uint32_t lnhuge;       // layer op: buckets listed for k_layer_huge
+  uint32_t lpad;         // (keeps the size a multiple of 8)
   uint32_t lneed;        // layer op: survivors of an op whose output did not fit
   uint32_t gstale;       // the gate table does not hold the current set (a LAYER
                          // op or a MERGE with no_gtab wrote it); cleared by

@@ -188,13 +188,14 @@ def test_failed_layer_op_keeps_the_gate_table(gpu):
     same(run(gpu, prog, 1), off, "layer ops vs gate launches")
 
 
-# (qubits, rotations, does the closed set of 2^rotations strings fit a block):
-# one, two and four key words, at and past each width's LDS capacity (a set
-# past the smaller block's runs again with the larger one)
+# (qubits, rotations, does the op take the closed set of 2^rotations strings):
+# one, two and four key words, at and past the capacity of a block (2048, 1792
+# and 1024 strings), of the larger block (4608, 3584, 2048) and of a slab in HBM
+# (32768)
 @pytest.mark.parametrize("n,k,fits", [(12, 10, True), (12, 11, True), (12, 12, True),
-                                      (13, 13, False), (40, 10, True), (40, 11, True),
-                                      (40, 12, False), (80, 10, True), (80, 11, True),
-                                      (80, 12, False)])
+                                      (13, 13, True), (15, 15, True), (16, 16, False),
+                                      (40, 10, True), (40, 11, True), (40, 12, True),
+                                      (80, 10, True), (80, 11, True), (80, 12, True)])
 def test_closed_set_at_the_block_capacity(gpu, n, k, fits):
     """X rotations on k qubits of the one string Z...Z make 2^k strings in
     one closed set; then Z rotations, so every string meets its partners
@@ -239,3 +240,22 @@ def test_per_call_layers_equal_gate_launches(gpu, name):
         assert (st["layer_ops"] > 0) == (mode == 1), (mode, st)
     assert out[1] == out[0]
     assert out[2] == out[0]
+
+
+@pytest.mark.parametrize("n,k", [(12, 11), (40, 11), (80, 10)])
+def test_closed_set_past_the_staging_slots(gpu, n, k):
+    """All 2^k strings of one closed set in the observable, beside 512 strings
+    of other sets: a bucket's share of the staging does not hold the set, so
+    the op runs again with exact placement, as do the sub-layers after it.
+    Bitwise the gate launches."""
+    xs = [W.Gate(1 << q, 0, 0.3 + 0.01 * q) for q in range(k)]
+    full = (1 << k) - 1
+    obs = [(s, full, 1.0 / (1 + s)) for s in range(1 << k)]
+    obs += [(s << 3, (s * 37) & 0x1FF, 0.5 + s / 1024) for s in range(1, 512)
+            if (s * 37) & 0x1FF != full]
+    prog = W.Program(f"slots{n}_{k}", n, "none", obs, [W.SubLayer(xs), W.SubLayer(xs[::-1])],
+                     W.ZERO_STATE, {})
+    print(f"[case] staging slots n = {n}", flush=True)
+    on = run(gpu, prog, 1)
+    same(on, run(gpu, prog, 0), prog.name)
+    assert on["stats"]["fallbacks"] == 0 and on["stats"]["overflow_runs"] > 0, on["stats"]
