@@ -148,7 +148,7 @@ struct pp_state {
   bool layer_huge = false;             // buckets past a block's LDS run from HBM
   char* d_huge = nullptr;              // their workspace: list, then kHugeBlocks slabs
   bool layer_exact = false;            // layer ops place their strings exactly
-  bool layer_big = false;              // layer ops run with 1024-thread blocks
+  bool layer_big = false;              // layer ops run with twice the strings per block
   bool layer_off = false;              // layer ops failed too often: their fallbacks run
   int layer_fallbacks = 0;             // layer ops that fell back (this handle)
   size_t fb_lo = 0, fb_hi = 0;         // fallback ops [fb_lo, fb_hi) that launch_range runs
@@ -637,13 +637,13 @@ SoloFn layer_of(int kind, int n, int W, bool big) {
   if (kind == kLayerHuge)
     return kw == 1 ? &k_layer_huge<1> : kw == 2 ? &k_layer_huge<2> : &k_layer_huge<4>;
   if (big)
-    return kw == 1 ? &k_layer_apply<1, 1024> : kw == 2 ? &k_layer_apply<2, 1024>
-                                                       : &k_layer_apply<4, 1024>;
+    return kw == 1 ? &k_layer_apply<1, 512, true> : kw == 2 ? &k_layer_apply<2, 512, true>
+                                                            : &k_layer_apply<4, 512, true>;
   if (g_tune.layer_block == 256)
-    return kw == 1 ? &k_layer_apply<1, 256> : kw == 2 ? &k_layer_apply<2, 256>
-                                                      : &k_layer_apply<4, 256>;
-  return kw == 1 ? &k_layer_apply<1, 512> : kw == 2 ? &k_layer_apply<2, 512>
-                                                    : &k_layer_apply<4, 512>;
+    return kw == 1 ? &k_layer_apply<1, 256, false> : kw == 2 ? &k_layer_apply<2, 256, false>
+                                                             : &k_layer_apply<4, 256, false>;
+  return kw == 1 ? &k_layer_apply<1, 512, false> : kw == 2 ? &k_layer_apply<2, 512, false>
+                                                           : &k_layer_apply<4, 512, false>;
 }
 
 // The layer op's staging, allocated when a handle first runs one (and
@@ -678,8 +678,8 @@ bool ensure_exact(pp_state* s) {
   return s->layer_exact;
 }
 
-// The workspace of buckets that outgrow a block's LDS (from then on kept by
-// the handle): 75 to 125 MB.
+// The workspace of buckets that outgrow a block's LDS: 75 to 125 MB, from then
+// on kept by the handle (promoted instances of a batch give it back).
 int ensure_huge(pp_state* s) {
   if (s->d_huge) return PP_OK;
   const int kw = layer_key_words(s->n, s->W);
@@ -862,6 +862,7 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
       if (layer) {
         int rc = ensure_layer(s);
         if (rc) return rc;
+        if (s->layer_huge && ensure_huge(s) != PP_OK) s->layer_huge = false;
       }
       if (kind != run_kind) {
         if (run_kind >= 0) prof_end(s, run_kind, run_ev, run_len);
@@ -884,7 +885,7 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
       }
       const int block = kind == PP_K_PART_SCAN ? kPCBlock
                         : kind == PP_K_PART_AGG ? kPABlock
-                        : kind == PP_K_LAYER_APPLY ? (s->layer_big ? 1024 : g_tune.layer_block)
+                        : kind == PP_K_LAYER_APPLY ? (s->layer_big ? 512 : g_tune.layer_block)
                         : is_part_kind(kind)    ? kPHBlock
                                                 : kBlock;
       Solo S;
@@ -908,7 +909,7 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
         hipLaunchKernelGGL(solo_of(kind, big, nrot, lane_it, s->group), dim3(grid), dim3(block),
                            part_lds(s->buf, kind), s->stream, S);
       if (kind == PP_K_LAYER_APPLY && s->layer_huge)
-        hipLaunchKernelGGL(layer_of(kLayerHuge, s->n, s->W, true), dim3(kHugeBlocks), dim3(1024), 0,
+        hipLaunchKernelGGL(layer_of(kLayerHuge, s->n, s->W, true), dim3(kHugeBlocks), dim3(kHugeBlock), 0,
                            s->stream, S);
       ++run_len;
     }
@@ -2926,6 +2927,8 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
         double e = 0.0;
         s->m_hint = s->h_dyn->M;
         const int g = solo_program(s, prog, &e, true);
+        dev_free(s, s->d_huge);              // (a batch may promote many instances)
+        s->d_huge = nullptr;
         s->buf.prog = prog->d_ops;
         s->buf.prog_len = (uint32_t)prog->ops.size();
         s->buf.nopart = 1;

@@ -41,14 +41,15 @@ __host__ __device__ __forceinline__ int layer_key_words(int n, int W) {
   return n <= 32 ? 1 : 2 * W;
 }
 
-// Strings per bucket in LDS for blocks of NB threads: two blocks of up to 512
-// threads fit a CU's 160 KB, or one of 1024 with twice the room (the form for
-// closed sets that do not fit the smaller one).
-template <int KW, int NB>
+// Strings per bucket in LDS: two blocks fit a CU's 160 KB, or one with twice
+// the room (`big`: for closed sets that do not fit the smaller form; also of
+// 512 threads, since with 1024 the kernel's registers spill to scratch memory,
+// which the runtime cannot get once a caller's allocator holds the device's).
+template <int KW, bool Big>
 constexpr int layer_cap() {
   constexpr int n = KW == 1 ? 2048 : KW == 2 ? 1792 : 1024;
   // (one word: room beside a full set of 2^12 strings)
-  return NB == 1024 ? (KW == 1 ? 4608 : 2 * n) : n;
+  return Big ? (KW == 1 ? 4608 : 2 * n) : n;
 }
 
 // Bucket bits for a layer op over M entries: about 2^shift strings per
@@ -695,7 +696,7 @@ struct alignas(16) BucketMem {
 // Buckets that outgrow a block's LDS (at most kHugeList of an op): a list of
 // (bucket, strings), then a slab per block of k_layer_huge.
 constexpr uint32_t kHugeList = 1024;
-constexpr int kHugeBlocks = 64, kHugeCap = 32768;
+constexpr int kHugeBlocks = 64, kHugeBlock = 512, kHugeCap = 32768;
 constexpr size_t kHugeListBytes = 2 * sizeof(uint32_t) * kHugeList;
 template <int KW> constexpr size_t huge_slab() {
   return (sizeof(BucketMem<KW, kHugeCap>) + 255) / 256 * 256;
@@ -717,9 +718,9 @@ struct ApplyCtl {
   uint64_t fold[kAccShards][NS + 1];
 };
 
-template <int KW, int NB>
+template <int KW, int NB, bool Big = false>
 struct ApplySh : ApplyCtl<KW, NB> {
-  BucketMem<KW, layer_cap<KW, NB>()> mem;
+  BucketMem<KW, layer_cap<KW, Big>()> mem;
 };
 
 
@@ -923,9 +924,9 @@ __device__ __forceinline__ bool apply_bucket(const InstBuf& b, InstDyn& d, const
 // apply_bucket from the block's LDS; a bucket that outgrows it goes on the list
 // of k_layer_huge (its sums undone; its strings are still staged) or, without
 // one, fails the op.
-template <int KW, int NB>
+template <int KW, int NB, bool Big>
 __device__ __forceinline__ void apply_or_list(const InstBuf& b, InstDyn& d, const LayerArgs& op,
-                                              uint32_t bits, uint32_t bk, ApplySh<KW, NB>& sh,
+                                              uint32_t bits, uint32_t bk, ApplySh<KW, NB, Big>& sh,
                                               LayerSums& sum, char* huge) {
   const uint32_t cnt = b.lcount[bk];
   const LayerSums before = sum;
@@ -1000,9 +1001,9 @@ __device__ __forceinline__ void layer_end(const InstBuf& b, InstDyn& d, const Op
   }
 }
 
-template <int KW, int NB>
+template <int KW, int NB, bool Big>
 __global__ __launch_bounds__(NB) void k_layer_apply(Solo S) {
-  __shared__ ApplySh<KW, NB> sh;
+  __shared__ ApplySh<KW, NB, Big> sh;
   const InstBuf& b = S.b;
   InstDyn& d = *S.d;
   const Op& op = b.prog[S.k];              // S.k < prog_len
@@ -1024,7 +1025,7 @@ __global__ __launch_bounds__(NB) void k_layer_apply(Solo S) {
       if (threadIdx.x == 0) b.lcount[bk] = 0;
       continue;
     }
-    apply_or_list<KW, NB>(b, d, la, bits, bk, sh, sum, b.lhuge);
+    apply_or_list<KW, NB, Big>(b, d, la, bits, bk, sh, sum, b.lhuge);
     if (++done % kLayerFlush == 0) flush_sums<KW, NB>(b, d, sh, sum);
   }
   flush_sums<KW, NB>(b, d, sh, sum);
@@ -1046,8 +1047,8 @@ __global__ __launch_bounds__(NB) void k_layer_apply(Solo S) {
 // propagations: Z_32 ring grown to 8x10^6 strings 60 -> 39 ms, untruncated
 // 12-qubit Ising ring 27 -> 18 ms (their later sub-layers were gate launches).
 template <int KW>
-__global__ __launch_bounds__(1024) void k_layer_huge(Solo S) {
-  __shared__ ApplyCtl<KW, 1024> sh;
+__global__ __launch_bounds__(kHugeBlock) void k_layer_huge(Solo S) {
+  __shared__ ApplyCtl<KW, kHugeBlock> sh;
   const InstBuf& b = S.b;
   InstDyn& d = *S.d;
   // nothing listed: the apply step ended the op (well, or with a failure that
@@ -1065,7 +1066,7 @@ __global__ __launch_bounds__(1024) void k_layer_huge(Solo S) {
   LayerSums sum;
   uint32_t done = 0;
   for (uint32_t e = blockIdx.x; e < n; e += gridDim.x) {
-    if (!apply_bucket<KW, 1024>(b, d, la, bits, list[2 * e], list[2 * e + 1], sh, mm, sum))
+    if (!apply_bucket<KW, kHugeBlock>(b, d, la, bits, list[2 * e], list[2 * e + 1], sh, mm, sum))
       sum.bad = true;
     if (++done % kLayerFlush == 0) flush_sums(b, d, sh, sum);
   }
@@ -1140,7 +1141,7 @@ __global__ __launch_bounds__(NB) void k_layer_apply_multi(Ctx C) {
       if (threadIdx.x == 0) b.lcount[bk] = 0;
       continue;
     }
-    apply_or_list<KW, NB>(b, d, la, bits, bk, sh, sum, nullptr);
+    apply_or_list<KW, NB, false>(b, d, la, bits, bk, sh, sum, nullptr);
     if (++done % kLayerFlush == 0) flush_sums<KW, NB>(b, d, sh, sum);
   }
   if (cur >= 0) flush_sums<KW, NB>(*C.bufs[cur], *C.dyns[cur], sh, sum);

@@ -233,7 +233,16 @@ def _wide_programs():
     late = W.Program("late", 13, "none", [(0, 1, 1.0), (0, 0b111, 0.5), (0b11, 0, 0.25)],
                      [W.SubLayer(pairs, eps=1e-5, wmax=4), W.SubLayer(pairs, eps=1e-3, wmax=2)],
                      W.ZERO_STATE, {})
+    fields = lambda a, b: [W.Gate(*W.one_site(k, q), 0.3) for k, lo, hi in (("X", 0, a), ("Z", b, 70))
+                           for q in range(lo, hi)]
+    obs70 = [(0, 0b111, 1.0), (1 << 40, 0, 0.5), (0b11 << 65, 1 << 66, 0.25)]
     return {
+        # commuting letters mixed, and a sub-layer past 64 rotations that does
+        # not commute (every launch runs)
+        "mixed70": W.Program("mixed70", 70, "none", obs70, [W.SubLayer(fields(35, 35), eps=1e-4)],
+                             W.ZERO_STATE, {}),
+        "clash70": W.Program("clash70", 70, "none", obs70, [W.SubLayer(fields(42, 35), eps=1e-4)],
+                             W.ZERO_STATE, {}),
         "s12": W.heisenberg_all_to_all(12, 1, 0.05, obs=W.sum_single(12, "Z"), eps=1e-4),
         "s70_two_words": prefix(W.heisenberg_all_to_all(70, 1, 0.02, p=1e-3,
                                                         obs=W.sum_single(70, "Z"), eps=1e-3), 2),
