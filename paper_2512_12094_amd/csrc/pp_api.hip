@@ -143,6 +143,7 @@ struct pp_state {
   std::vector<std::vector<void*>> retired;   // stores replaced during the call
   void* txn_backup = nullptr;
   uint32_t txn_m = 0, txn_half = 0, txn_parity = 0;
+  uint32_t txn_gen = 0;                // gate-table generation the call left that store with
   bool shrunk = false;                 // a finished batched instance's store was compacted
   bool layer_used = false;             // layer ops ran: stores carry their staging
   bool layer_huge = false;             // buckets past a block's LDS run from HBM
@@ -716,6 +717,7 @@ int grow(pp_state* s) {
   if (cap < need + 1)
     return fail(PP_ECAPACITY, "term store would need " + std::to_string(need + 1) +
                                   " entries, limit " + std::to_string(s->max_terms));
+  if (s->txn && s->retired.empty()) s->txn_gen = d.gen;
   InstBuf nb;
   std::vector<void*> allocs;
   int rc = alloc_store(s, (uint32_t)cap, &nb, &allocs);
@@ -1730,9 +1732,20 @@ void txn_end(pp_state* s) {
 }
 
 // Restores the state of the call's start; returns `rc` (the call's error).
+// The gate table is not restored: the call may have entered the whole set and
+// its children under generations up to one past its last, and a generation
+// entered again call after call fills the table until lookups miss.  So the
+// state goes back with a generation no entry carries and the table marked
+// stale: the recount in front of the next gates enters the set afresh.  (An
+// error from before the first launch, with the program that the handle stands
+// in still attached, leaves the table valid for its gates.)
 int txn_rollback(pp_state* s, int rc) {
   const std::string msg = g_err;
+  const bool ran = s->batch_prog == nullptr;
+  bool ok = read_dyn(s) == PP_OK;
+  uint32_t gen = s->h_dyn->gen;
   if (s->buf.x[0] != s->txn_buf.x[0] && !s->retired.empty()) {
+    gen = s->txn_gen;
     free_store(s, s->store);                     // the grown store
     s->store = std::move(s->retired.front());
     s->retired.erase(s->retired.begin());
@@ -1741,8 +1754,8 @@ int txn_rollback(pp_state* s, int rc) {
   char* p = static_cast<char*>(s->txn_backup);
   const size_t cs = s->buf.f32 ? sizeof(float) : sizeof(double);
   const uint32_t M = s->txn_m;
-  bool ok = hipMemcpyAsync(s->d_buf, &s->buf, sizeof(InstBuf), hipMemcpyHostToDevice,
-                           s->stream) == hipSuccess;
+  ok = ok && hipMemcpyAsync(s->d_buf, &s->buf, sizeof(InstBuf), hipMemcpyHostToDevice,
+                            s->stream) == hipSuccess;
   ok = ok && hipMemcpyAsync(s->d_dyn, p, sizeof(InstDyn), hipMemcpyDeviceToDevice,
                             s->stream) == hipSuccess;
   p += sizeof(InstDyn);
@@ -1758,7 +1771,16 @@ int txn_rollback(pp_state* s, int rc) {
   }
   ok = ok && hipStreamSynchronize(s->stream) == hipSuccess;
   txn_end(s);
-  if (ok) (void)read_dyn(s);
+  ok = ok && read_dyn(s) == PP_OK;
+  if (ok && ran) {
+    s->h_dyn->gen = gen + 1;
+    s->h_dyn->gstale = 1;
+    ok = hipMemcpyAsync(&s->d_dyn->gen, &s->h_dyn->gen, sizeof(uint32_t), hipMemcpyHostToDevice,
+                        s->stream) == hipSuccess;
+    ok = ok && hipMemcpyAsync(&s->d_dyn->gstale, &s->h_dyn->gstale, sizeof(uint32_t),
+                              hipMemcpyHostToDevice, s->stream) == hipSuccess;
+    ok = ok && hipStreamSynchronize(s->stream) == hipSuccess;
+  }
   g_err = ok ? msg + " (the handle is as before the call)"
              : msg + " (restoring the handle's state also failed)";
   return ok ? rc : PP_EDEVICE;

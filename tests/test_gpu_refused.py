@@ -1,0 +1,78 @@
+"""Calls that a handle's limits or its allocator refuse leave the handle usable
+and exact: a refused call repeated without the store growing, a program stopped
+inside a sub-layer and resumed, memory that is not to be had for a layer op.
+What runs afterwards equals, bitwise, a handle that met no refusal."""
+import numpy as np
+import pytest
+
+from paper_2512_12094_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+CAPACITY, NOMEM = -4, -3
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2512_12094_amd import _lib
+    _lib.lib()
+    torch.cuda.set_device(0)
+    stream = torch.cuda.Stream()
+    return dict(torch=torch, stream=stream, handle=int(stream.cuda_stream),
+                alloc=_lib.TorchAllocator(0))
+
+
+def layer(gates, eps=0.0, wmax=-1):
+    from paper_2512_12094_amd import driver
+    prog = W.Program("layer", 20, "none", [], [W.SubLayer(gates, eps=eps, wmax=wmax)],
+                     W.ZERO_STATE, {})
+    return driver.heisenberg_layers(prog)[0]
+
+
+def strings(n, rows, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.permutation(1 << n)[:rows].astype(np.uint64).reshape(-1, 1)
+    z = rng.integers(0, 1 << n, size=(rows, 1), dtype=np.uint64)
+    return x, z, rng.normal(size=rows)
+
+
+@pytest.mark.parametrize("grow", [False, True])
+def test_refused_calls_leave_the_gate_table_usable(gpu, grow):
+    """A merge leaves the gate table to the next call's recount.  Calls that
+    are refused at the store limit (without a growth, or after one) enter the
+    set and give it back; after ten of them the table still finds every
+    string."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print(f"[case] refused calls, grow {grow}", flush=True)
+    x, z, c = strings(20, 1500, 3)
+    x[:, 0] &= np.uint64(0xFFFFF)
+    z[:, 0] &= np.uint64(0x7FFFF)                     # Z on qubit 19: few strings
+    z[:40, 0] |= np.uint64(1 << 19)
+    big = layer([W.Gate(1 << q, 0, 0.3) if q % 2 else W.Gate(0, 1 << q, 0.4)
+                 for q in range(10)] + [W.Gate(1 << q, 1 << q, 0.2) for q in range(10)])
+    fits = layer([W.Gate(1 << 19, 0, 0.3), W.Gate(1 << 19, 0, 0.5), W.Gate(1 << 19, 0, 0.7)])
+
+    def fresh():
+        ps = driver.PauliSet(20, "none", x, z, c, gpu["handle"], gpu["alloc"])
+        ps.merge()
+        return ps
+
+    ref, ps = fresh(), fresh()
+    L.pp_set_max_terms(ps.h, 16384 if grow else 4096)
+    before = (ps.as_dict(), ps.counters())
+    for _ in range(10):
+        with pytest.raises(L.PPError) as e:
+            ps.apply_layer(big)
+        assert e.value.code == CAPACITY and "as before the call" in str(e.value)
+    assert (ps.as_dict(), ps.counters()) == before
+    for s in (ref, ps):
+        s.apply_layer(fits)
+        s.apply_layer(fits)
+    assert ps.as_dict() == ref.as_dict()
+    assert ps.counters() == ref.counters()
+    ref.close()
+    ps.close()
