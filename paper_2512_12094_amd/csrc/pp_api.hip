@@ -177,6 +177,7 @@ struct pp_state {
   double m_growth = 2.0;   // records a merge took over the set size before it (last seen)
   unsigned long long* d_act = nullptr;   // run_wide's mask of rotations that act
   size_t act_cap = 0;                    // and its words
+  uint32_t wide_next = 0;  // rotations of the sub-layer at pc that a refused run_wide applied
   uint64_t m_prev_in = 0;  // merge_in and set size at the last read-back
   uint32_t m_prev = 0;
   int lx = 0;              // torus width (PP_GROUP_TORUS)
@@ -932,8 +933,9 @@ using TabRefs = std::vector<std::pair<size_t, size_t>>;   // (op index, table of
 
 int layer_failed(pp_state* s, const Op* ops, size_t len, bool grew = false);
 
+// *stopped: the op whose growth was refused (ops before it are applied).
 int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
-            const TabRefs& refs, bool nosync) {
+            const TabRefs& refs, bool nosync, size_t* stopped = nullptr) {
   if (ops.empty()) return PP_OK;
   int rc = ensure_ops(s, ops.size(), tab.size());
   if (rc) return rc;
@@ -992,6 +994,7 @@ int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
         (void)hipMemcpyAsync(&s->d_dyn->status, &s->h_dyn->status, sizeof(uint32_t),
                              hipMemcpyHostToDevice, s->stream);
         (void)hipStreamSynchronize(s->stream);
+        if (stopped) *stopped = at;
         g_err = msg + " (" + std::to_string(at) + " of " + std::to_string(ops.size()) +
                 " operations applied)";
         return rc;
@@ -2658,6 +2661,9 @@ void resume_window(pp_state* s, const Op* ops, size_t len, size_t pc) {
 // of gate launches of its own; the others count as tested (Op::idle).  The
 // first rotation always runs (it re-checks every term).  Nothing is in flight
 // when this is called and the device stands at w.from; it ends at w.to.
+// A growth that is refused leaves the device at w.from with the rotations that
+// are applied in wide_next: a batch that resumes the program there comes back
+// here for the others (the program's own launches would apply them all again).
 //
 // Only for sub-layers past kLayerMaxRot rotations (at least 22 launches of
 // ~7 us): the extra launch and two reads cost ~50 us.  All-to-all couplings
@@ -2685,7 +2691,7 @@ int run_wide(pp_state* s, const pp_program* p, const pp_program::Wide& w) {
                          s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
   std::vector<Op> ops(1, make_op(OP_COUNT));
-  for (uint32_t g = 0; g < nrot; ++g) {
+  for (uint32_t g = s->wide_next; g < nrot; ++g) {
     if (g == 0 || ((mask[g >> 6] >> (g & 63)) & 1ull))
       ops.push_back(w.gates[g]);
     else
@@ -2693,16 +2699,34 @@ int run_wide(pp_state* s, const pp_program* p, const pp_program::Wide& w) {
   }
   fuse_gates(ops, 1, s->W, w.fuse);
   set_next_gates(ops);
-  rc = run_ops(s, std::move(ops), {}, {}, false);
+  std::vector<uint32_t> applied;           // rotations applied in front of each op
+  uint32_t at = s->wide_next;
+  for (const Op& op : ops) {
+    applied.push_back(at);
+    at += op.nrot;                         // (0: the recount)
+    for (uint32_t r = 0; r < std::max<uint32_t>(op.nrot, 1); ++r) at += op.idle[r];
+  }
+  size_t stopped = applied.size();
+  rc = run_ops(s, std::move(ops), {}, {}, false, &stopped);
   s->buf.prog = p->d_ops;                  // back to the program
   s->buf.prog_len = (uint32_t)p->ops.size();
   s->batch_prog = p;
-  if (rc) return rc;
-  if ((rc = upload_buf(s))) return rc;
-  hipLaunchKernelGGL(k_set_pc, dim3(1), dim3(1), 0, s->stream, s->d_dyn, (uint32_t)w.to);
+  const bool refused = stopped < applied.size();
+  if (rc && !refused) return rc;
+  if (refused) s->wide_next = applied[stopped];
+  const std::string msg = g_err;
+  const uint32_t pc = (uint32_t)(refused ? w.from : w.to);
+  const int up = upload_buf(s);
+  hipLaunchKernelGGL(k_set_pc, dim3(1), dim3(1), 0, s->stream, s->d_dyn, pc);
   HIP_TRY(hipGetLastError());
-  s->h_dyn->pc = (uint32_t)w.to;
-  return PP_OK;
+  s->h_dyn->pc = pc;
+  if (rc) {
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    g_err = msg;
+    return rc;
+  }
+  s->wide_next = 0;
+  return up;
 }
 
 int solo_program(pp_state* s, const pp_program* p, double* expectation, bool resume = false) {
@@ -2716,7 +2740,10 @@ int solo_program(pp_state* s, const pp_program* p, double* expectation, bool res
   s->buf.nolayer = s->layer_off ? 1u : 0u;
   s->batch_prog = p;
   if ((rc = upload_buf(s))) return rc;
-  if (!resume) hipLaunchKernelGGL(k_set_pc, dim3(1), dim3(1), 0, st, s->d_dyn, 0u);
+  if (!resume) {
+    hipLaunchKernelGGL(k_set_pc, dim3(1), dim3(1), 0, st, s->d_dyn, 0u);
+    s->wide_next = 0;
+  }
   resume_window(s, ops, len, resume ? s->h_dyn->pc : 0);
   // chunk ends: after every kChunkSubs-th sub-layer (its MERGE and the TRUNC
   // that follows it), or the last op; the host reads the state once per chunk
@@ -2888,6 +2915,7 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
     if (s->batch_prog != programs[i]) {
       if (s->h_dyn->status & ST_FAILED) return fail(PP_EINVAL, "state failed in an earlier batch");
       s->shrunk = false;
+      s->wide_next = 0;
       s->buf.prog = programs[i]->d_ops;
       s->buf.prog_len = (uint32_t)programs[i]->ops.size();
       s->batch_prog = programs[i];
@@ -2899,6 +2927,11 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
       s->buf.nopart = 1;
       s->buf.nolayer = batch_layer(s, programs[i]) ? 0u : 1u;
       if ((rc = upload_buf(s))) return rc;
+    }
+    if (s->wide_next) {                    // the steps skip it; run_wide goes on with it
+      s->h_dyn->status |= ST_OVERFLOW;
+      HIP_TRY(hipMemcpyAsync(&s->d_dyn->status, &s->h_dyn->status, sizeof(uint32_t),
+                             hipMemcpyHostToDevice, stream));
     }
     b->h_bufp[i] = s->d_buf;
     b->h_dynp[i] = s->d_dyn;
@@ -2927,7 +2960,7 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
       if ((s->h_dyn->status & ST_OVERFLOW)) {
         // an instance that cannot grow stops (kernels keep skipping it);
         // the others go on
-        const int g = grow(s);
+        const int g = s->wide_next ? PP_OK : grow(s);
         s->h_dyn->status = g ? (s->h_dyn->status | ST_FAILED) : (s->h_dyn->status & ~ST_OVERFLOW);
         HIP_TRY(hipMemcpyAsync(&s->d_dyn->status, &s->h_dyn->status, sizeof(uint32_t),
                                hipMemcpyHostToDevice, stream));
@@ -2943,8 +2976,9 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
                                hipMemcpyHostToDevice, stream));
         continue;
       }
-      if (s->h_dyn->pc < s->buf.prog_len && s->h_dyn->peak >= kPromote) {
-        // a large instance: finish it alone, then put it back (finished)
+      if (s->h_dyn->pc < s->buf.prog_len && (s->h_dyn->peak >= kPromote || s->wide_next)) {
+        // a large instance (or one inside a wide sub-layer): finish it alone,
+        // then put it back (finished)
         const pp_program* prog = s->batch_prog;
         double e = 0.0;
         s->m_hint = s->h_dyn->M;

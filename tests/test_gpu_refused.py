@@ -76,3 +76,48 @@ def test_refused_calls_leave_the_gate_table_usable(gpu, grow):
     assert ps.counters() == ref.counters()
     ref.close()
     ps.close()
+
+
+def wide_program():
+    """120 commuting rotations on one string that 15 of them anticommute with
+    (2^15 strings), fields, then 120 more."""
+    pairs = lambda k, t: [W.Gate(*W.two_site(k, a, b), t) for a in range(16) for b in range(a)]
+    subs = [W.SubLayer(pairs("Z", 0.11), eps=2e-3, wmax=9),
+            W.SubLayer([W.Gate(0, 1 << q, 0.2) for q in range(16)], eps=1e-3),
+            W.SubLayer(pairs("X", 0.4), wmax=12)]      # applied last to first
+    return W.Program("wide16", 16, "none", [(0, 1, 1.0), (0, 0b10010, 0.5), (0b11, 0, 0.25)],
+                     subs, W.ZERO_STATE, {})
+
+
+@pytest.mark.parametrize("limit", [40, 700, 6000])
+@pytest.mark.parametrize("both", [False, True])
+def test_program_resumes_inside_a_wide_sublayer(gpu, limit, both):
+    """pp_batch_run is refused inside a sub-layer of more than 64 rotations;
+    the batched form then resumes the program, alone or beside another."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    prog = wide_program()
+    print(f"[case] resume in a wide sub-layer, limit {limit}, both {both}", flush=True)
+    dp = driver.DeviceProgram(prog)
+    make = lambda: driver.PauliSet.from_program(prog, None, gpu["handle"], gpu["alloc"])
+    ref, ps, other = make(), make(), make()
+    want = float(L.pp_batch_run([ref.h], [dp.h], gpu["handle"])[0])
+    L.pp_set_max_terms(ps.h, 4096 + limit)
+    with pytest.raises(L.PPError) as e:
+        L.pp_batch_run([ps.h], [dp.h], gpu["handle"])
+    assert e.value.code == CAPACITY
+    assert ps.num_terms() > 3                          # inside the sub-layer
+    L.pp_set_max_terms(ps.h, 0)
+    sets = [other, ps] if both else [ps]
+    for _ in range(200):
+        done, got = L.pp_batch_step([s.h for s in sets], [dp.h] * len(sets), gpu["handle"], 8)
+        assert (done >= 0).all()
+        if done.all():
+            break
+    assert done.all() and all(float(g) == want for g in got)
+    for s in sets:
+        assert s.as_dict() == ref.as_dict()
+        assert s.counters() == ref.counters()
+    for s in (ref, ps, other):
+        s.close()
+    dp.close()
