@@ -694,11 +694,11 @@ int items_of(int kind, bool big = false) {
   return kind == PP_K_GATE ? gate_items(big) : stream_items(big);
 }
 
-// Grows (or just compacts) the store so that the op that stopped fits:
+// The capacity grow() would give the store so that the op that stopped fits:
 // live + count entries for a gate, 2^(r-1) (live + count) for an op of r
 // rotations (each later rotation may append one string per term live
-// before it).
-int grow(pp_state* s) {
+// before it).  *need = the entries it must hold.
+uint64_t grow_cap(const pp_state* s, uint64_t* need_out) {
   const InstDyn& d = *s->h_dyn;
   const std::vector<Op>* ops = s->batch_prog ? &s->batch_prog->ops : s->run_ops_list;
   const uint32_t nrot =
@@ -715,6 +715,15 @@ int grow(pp_state* s) {
   uint64_t cap = std::max<uint64_t>({(uint64_t)s->buf.cap, head, 4096});
   if (cap > 0xFFFFFFF0ull) cap = 0xFFFFFFF0ull;
   if (s->max_terms && cap > s->max_terms) cap = s->max_terms;
+  *need_out = need;
+  return cap;
+}
+
+// Grows (or just compacts) the store.
+int grow(pp_state* s) {
+  const InstDyn& d = *s->h_dyn;
+  uint64_t need = 0;
+  const uint64_t cap = grow_cap(s, &need);
   if (cap < need + 1)
     return fail(PP_ECAPACITY, "term store would need " + std::to_string(need + 1) +
                                   " entries, limit " + std::to_string(s->max_terms));
@@ -2602,13 +2611,21 @@ int layer_failed(pp_state* s, const Op* ops, size_t len, bool grew) {
     // Z_32 ring, which needs that once)
     const bool exact = !ops[k].fail_test && (h.lwhy & 1u) && !s->layer_exact && h.lboost < 0;
     const bool enlarge = !ops[k].fail_test && !(h.lwhy & 1u) && !s->layer_big;
+    // a crowded store grows where that gives the buckets more staging slots: not
+    // at its limit, nor past 2^24 entries, where its headroom is no more than
+    // this asks for (run again in a store of the same size, the op would fail
+    // the same way without end)
+    uint64_t need = 0;
+    const uint64_t cap = grow_cap(s, &need);
+    const bool roomier = !ops[k].fail_test && (h.lwhy & 1u) &&
+                         (uint64_t)h.M * 3 > s->buf.cap && cap > s->buf.cap && cap > need;
     if (!ops[k].fail_test && (h.lwhy & 1u) && grew) {
       // the op ran in the store before the last growth: again, in the new one
     } else if (exact && ensure_exact(s)) {
       h.lboost = 0;                            // no bucket overflows its slots from here on
       HIP_TRY(hipMemcpyAsync(&s->d_dyn->lboost, &h.lboost, sizeof(int32_t),
                              hipMemcpyHostToDevice, s->stream));
-    } else if (!ops[k].fail_test && (h.lwhy & 1u) && (uint64_t)h.M * 3 > s->buf.cap) {
+    } else if (roomier) {
       if ((rc = grow(s))) return rc;           // more staging slots per bucket
     } else if (enlarge) {
       s->layer_big = true;                     // twice the strings per bucket, from here on

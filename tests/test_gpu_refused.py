@@ -121,3 +121,45 @@ def test_program_resumes_inside_a_wide_sublayer(gpu, limit, both):
     for s in (ref, ps, other):
         s.close()
     dp.close()
+
+
+def crowded_set():
+    """All 2^11 strings of one closed set, which no bucket's share of the
+    staging holds, and 511 strings that commute with everything: rotating them
+    makes no new string."""
+    k = 11
+    obs = [(s, (1 << k) - 1, 1.0 / (1 + s)) for s in range(1 << k)]
+    obs += [(s, 0, 0.5 + s / 1024) for s in range(1, 512)]
+    xs = [W.Gate(1 << q, 0, 0.3 + 0.01 * q) for q in range(k)]
+    return W.Program("crowded", 12, "none", obs, [W.SubLayer(xs), W.SubLayer(xs[::-1])],
+                     W.ZERO_STATE, {})
+
+
+@pytest.mark.parametrize("form", ["calls", "program"])
+def test_staging_overflow_at_the_store_limit(gpu, form):
+    """A layer op whose staging overflows in a store that may not grow goes on
+    to exact placement."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    prog = crowded_set()
+    print(f"[case] staging overflow at the limit, {form}", flush=True)
+    out = {}
+    for mode in (0, 1):
+        L.pp_set_layer_ops(mode)
+        try:
+            dp = driver.DeviceProgram(prog)
+            ps = driver.PauliSet.from_program(prog, None, gpu["handle"], gpu["alloc"])
+            if mode:
+                L.pp_set_max_terms(ps.h, 2 * len(prog.obs))      # the capacity it has
+            if form == "calls":
+                driver.run_layers(ps, driver.heisenberg_layers(prog))
+            else:
+                L.pp_batch_run([ps.h], [dp.h], gpu["handle"])
+            out[mode] = (ps.as_dict(), ps.counters())
+            st = L.pp_layer_stats(ps.h)
+            ps.close()
+            dp.close()
+        finally:
+            L.pp_set_layer_ops(1)
+    assert out[0] == out[1]
+    assert st["layer_ops"] == 2 and st["fallbacks"] == 0 and st["overflow_runs"] > 0, st
