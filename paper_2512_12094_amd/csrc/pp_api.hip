@@ -652,7 +652,6 @@ SoloFn layer_of(int kind, int n, int W, bool big) {
 // then with every store it grows into).
 int ensure_layer(pp_state* s) {
   if (s->buf.lcount && (s->buf.lbase || !s->layer_exact)) return PP_OK;
-  s->layer_used = true;
   InstBuf nb = s->buf;
   std::vector<void*> got;
   auto take = [&](size_t bytes) -> void* {
@@ -668,6 +667,7 @@ int ensure_layer(pp_state* s) {
   HIP_TRY(hipMemsetAsync(nb.lcount, 0, sizeof(uint32_t) << nb.lmaxbits, s->stream));
   // (a staging that is replaced is freed with the store)
   for (void* p : got) s->store.push_back(p);
+  s->layer_used = true;
   s->buf = nb;
   return upload_buf(s);
 }
@@ -863,19 +863,31 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
   hipEvent_t run_ev = nullptr;
   for (size_t k = from; k < to; ++k) {
     // a layer op's fallback copies run only after it failed (or with layer
-    // ops off for this handle, in place of it)
-    if (ops[k].type == OP_LAYER && s->buf.nolayer) continue;
+    // ops off for this handle, in place of it); without memory for the staging
+    // the gate launches, which need none, run from here to the end of the list
+    if (ops[k].type == OP_LAYER && !s->buf.nolayer) {
+      int rc = ensure_layer(s);
+      if (rc == PP_ENOMEM) {
+        s->buf.nolayer = 1;
+        rc = upload_buf(s);
+        hipLaunchKernelGGL(k_pass_op, dim3(1), dim3(1), 0, s->stream, s->d_dyn, (uint32_t)k);
+      }
+      if (rc) return rc;
+      if (s->layer_huge && ensure_huge(s) != PP_OK) s->layer_huge = false;
+    }
+    if (ops[k].type == OP_LAYER && s->buf.nolayer) {
+      // (the device passes layer ops that are off as it leaves the op in front,
+      // but a list that starts with one finds it standing there)
+      if (k == from)
+        hipLaunchKernelGGL(k_pass_op, dim3(1), dim3(1), 0, s->stream, s->d_dyn, (uint32_t)k);
+      continue;
+    }
     if (ops[k].fallback && !s->buf.nolayer && !(k >= s->fb_lo && k < s->fb_hi)) continue;
     kinds.clear();
     kinds_of(s, ops[k], &kinds);
     for (int kind : kinds) {
       if (small && is_part_kind(kind)) continue;
       const bool layer = kind == PP_K_LAYER_SCATTER || kind == PP_K_LAYER_APPLY;
-      if (layer) {
-        int rc = ensure_layer(s);
-        if (rc) return rc;
-        if (s->layer_huge && ensure_huge(s) != PP_OK) s->layer_huge = false;
-      }
       if (kind != run_kind) {
         if (run_kind >= 0) prof_end(s, run_kind, run_ev, run_len);
         run_kind = kind;

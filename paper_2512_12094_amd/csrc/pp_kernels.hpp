@@ -2644,6 +2644,11 @@ __global__ __launch_bounds__(kBlock) void k_grow(InstBuf src, InstBuf dst, InstD
 
 __global__ void k_set_pc(InstDyn* d, uint32_t pc) { d->pc = pc; }
 
+// Past op k if the instance stands there (a LAYER op that is not run).
+__global__ void k_pass_op(InstDyn* d, uint32_t k) {
+  if (d->pc == k) d->pc = k + 1;
+}
+
 // What a transaction may have to restore, into one backup area: the dynamic
 // state, the statistics lines, m coefficients (cw 4-byte words each) and m
 // liveness flags (one launch instead of four copies).

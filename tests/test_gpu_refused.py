@@ -25,6 +25,37 @@ def gpu():
                 alloc=_lib.TorchAllocator(0))
 
 
+class Refusing:
+    """A caller's allocator that refuses what `deny(bytes)` names; `held` is
+    what the library has from it."""
+
+    def __init__(self, inner, deny=lambda nbytes: False):
+        from paper_2512_12094_amd import _lib as L
+        self.inner, self.deny, self.held, self.refused = inner, deny, {}, 0
+
+        def alloc(nbytes, stream, ctx):
+            if self.deny(nbytes):
+                self.refused += 1
+                return None
+            p = inner._alloc(nbytes, stream, ctx)
+            if p:
+                self.held[p] = nbytes
+            return p
+
+        def free(p, stream, ctx):
+            self.held.pop(p, None)
+            inner._free(p, stream, ctx)
+
+        self._alloc, self._free = L.ALLOC_FN(alloc), L.FREE_FN(free)
+        self.struct = L.PPAllocator(self._alloc, self._free, None)
+
+
+def staging(nbytes):
+    """The layer op's staging arrays: 8 bytes for each of a power of two of slots
+    (a store is one allocation of another size)."""
+    return nbytes >= 1 << 16 and nbytes & (nbytes - 1) == 0
+
+
 def layer(gates, eps=0.0, wmax=-1):
     from paper_2512_12094_amd import driver
     prog = W.Program("layer", 20, "none", [], [W.SubLayer(gates, eps=eps, wmax=wmax)],
@@ -163,3 +194,45 @@ def test_staging_overflow_at_the_store_limit(gpu, form):
             L.pp_set_layer_ops(1)
     assert out[0] == out[1]
     assert st["layer_ops"] == 2 and st["fallbacks"] == 0 and st["overflow_runs"] > 0, st
+
+
+@pytest.mark.parametrize("form", ["calls", "program", "batch"])
+def test_no_memory_for_the_layer_staging(gpu, form):
+    """Without memory for a layer op's staging its gate launches run."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    prog = W.xxz_ring(16, 2, 0.3, 0.8, eps=1e-7, name="z16")
+    print(f"[case] no memory for the layer staging, {form}", flush=True)
+    dp = driver.DeviceProgram(prog)
+
+    def run(alloc, mode):
+        L.pp_set_layer_ops(mode)
+        try:
+            sets = [driver.PauliSet.from_program(prog, None, gpu["handle"], alloc)
+                    for _ in range(2 if form == "batch" else 1)]
+            if form == "calls":
+                driver.run_layers(sets[0], driver.heisenberg_layers(prog))
+            else:
+                L.pp_batch_run([s.h for s in sets], [dp.h] * len(sets), gpu["handle"])
+        finally:
+            L.pp_set_layer_ops(1)
+        out = [(s.as_dict(), s.counters(), L.pp_layer_stats(s.h)["layer_ops"]) for s in sets]
+        return sets, out
+
+    plain, want = run(gpu["alloc"], 0 if form == "calls" else 1)
+    short = Refusing(gpu["alloc"], staging)
+    tight, got = run(short, 1)
+    assert short.refused
+    for g, w in zip(got, want):
+        assert g[:2] == w[:2] and g[2] == 0
+    short.deny = lambda nbytes: False                  # memory again: layer ops again
+    if form == "calls":
+        la = driver.heisenberg_layers(prog)[0]
+        for s in (plain[0], tight[0]):
+            s.apply_layer(la)
+        assert L.pp_layer_stats(tight[0].h)["layer_ops"] == 1
+        assert tight[0].as_dict() == plain[0].as_dict()
+    for s in plain + tight:
+        s.close()
+    dp.close()
+    assert not short.held
