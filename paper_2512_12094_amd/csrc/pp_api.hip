@@ -409,16 +409,34 @@ void clear_layer(InstBuf& nb) {
   nb.lslots = nb.lmaxbits = nb.lexact = 0;
 }
 
-// The layer op's staging for nb's capacity, from take(bytes).
+void copy_layer(InstBuf& to, const InstBuf& from) {
+  to.lstx = from.lstx;
+  to.lstz = from.lstz;
+  to.lstc = from.lstc;
+  to.lsta = from.lsta;
+  to.lcount = from.lcount;
+  to.lslots = from.lslots;
+  to.lmaxbits = from.lmaxbits;
+  to.lpat = from.lpat;
+  to.lbk = from.lbk;
+  to.lrank = from.lrank;
+  to.lbase = from.lbase;
+}
+
+// The layer op's staging for nb's capacity, from take(bytes): the arrays that
+// nb lacks (exact placement adds four to a staging that is there).
 template <class Take>
 bool take_layer(InstBuf& nb, int W, bool exact, Take take) {
-  nb.lslots = layer_slots(nb.cap);
-  nb.lmaxbits = layer_max_bits(nb.lslots);
-  bool ok = (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots)) != nullptr;
-  ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
-  ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
-  ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
-  ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
+  bool ok = true;
+  if (!nb.lcount) {
+    nb.lslots = layer_slots(nb.cap);
+    nb.lmaxbits = layer_max_bits(nb.lslots);
+    ok = ok && (nb.lstx = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
+    ok = ok && (nb.lstz = (uint64_t*)take(sizeof(uint64_t) * W * nb.lslots));
+    ok = ok && (nb.lstc = (double*)take(sizeof(double) * nb.lslots));
+    ok = ok && (nb.lsta = (uint64_t*)take(sizeof(uint64_t) * nb.lslots));
+    ok = ok && (nb.lcount = (uint32_t*)take(sizeof(uint32_t) << nb.lmaxbits));
+  }
   if (exact) {
     ok = ok && (nb.lpat = (uint64_t*)take(sizeof(uint64_t) * nb.cap));
     ok = ok && (nb.lbk = (uint32_t*)take(sizeof(uint32_t) * nb.cap));
@@ -659,16 +677,18 @@ int ensure_layer(pp_state* s) {
     if (p) got.push_back(p);
     return p;
   };
-  clear_layer(nb);
+  const bool counts = nb.lcount == nullptr;  // (a staging's counts are zero between ops)
   if (!take_layer(nb, s->W, s->layer_exact, take)) {
     for (void* p : got) dev_free(s, p);
     return fail(PP_ENOMEM, "allocation of the layer staging failed");
   }
-  HIP_TRY(hipMemsetAsync(nb.lcount, 0, sizeof(uint32_t) << nb.lmaxbits, s->stream));
-  // (a staging that is replaced is freed with the store)
   for (void* p : got) s->store.push_back(p);
   s->layer_used = true;
   s->buf = nb;
+  // the store a call may roll back to is this one: it keeps the staging, which
+  // the store's allocations now hold
+  if (s->txn && s->txn_buf.x[0] == nb.x[0]) copy_layer(s->txn_buf, nb);
+  if (counts) HIP_TRY(hipMemsetAsync(nb.lcount, 0, sizeof(uint32_t) << nb.lmaxbits, s->stream));
   return upload_buf(s);
 }
 

@@ -236,3 +236,37 @@ def test_no_memory_for_the_layer_staging(gpu, form):
         s.close()
     dp.close()
     assert not short.held
+
+
+def test_refused_calls_keep_one_staging(gpu):
+    """Layer ops refused at the store limit, with and without exact placement,
+    hold one staging between them, whatever the number of calls."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print("[case] one staging", flush=True)
+    prog = crowded_set()
+    alloc = Refusing(gpu["alloc"])
+    ps = driver.PauliSet.from_program(prog, None, gpu["handle"], alloc)
+    plain = sum(alloc.held.values())
+    L.pp_set_max_terms(ps.h, 2 * len(prog.obs))
+    fields = layer([W.Gate(0, 1 << q, 0.3) for q in range(12)])       # outgrows the store
+    before = (ps.as_dict(), ps.counters())
+    held = []
+    for k in range(6):
+        with pytest.raises(L.PPError) as e:
+            ps.apply_layer(fields)
+        assert e.value.code == CAPACITY
+        held.append(sum(alloc.held.values()))
+    assert (ps.as_dict(), ps.counters()) == before
+    assert len(set(held[1:])) == 1, held
+    # exact placement adds 16 bytes an entry and the bucket bases to what is there
+    for la in driver.heisenberg_layers(prog):
+        ps.apply_layer(la)
+    cap, slots = 2 * len(prog.obs), 1 << 15            # 5118 entries: four times 2^13 slots
+    exact = 16 * cap + 4 * (slots >> 6)
+    stats = L.pp_layer_stats(ps.h)
+    assert stats["layer_ops"] == 2 and stats["fallbacks"] == 0, stats
+    assert held[-1] < sum(alloc.held.values()) <= held[-1] + exact + 4 * 256
+    assert held[-1] - plain < 33 * slots + (1 << 17)   # the staging and the call's backup
+    ps.close()
+    assert not alloc.held
