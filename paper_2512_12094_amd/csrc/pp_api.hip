@@ -751,6 +751,17 @@ int grow(pp_state* s) {
   InstBuf nb;
   std::vector<void*> allocs;
   int rc = alloc_store(s, (uint32_t)cap, &nb, &allocs);
+  // where memory is short: without what exact placement adds, then without the
+  // layer op's staging (the next layer op asks for it again)
+  if (rc == PP_ENOMEM && s->layer_used && s->layer_exact) {
+    s->layer_exact = false;
+    rc = alloc_store(s, (uint32_t)cap, &nb, &allocs);
+  }
+  if (rc == PP_ENOMEM && s->layer_used) {
+    s->layer_used = false;
+    rc = alloc_store(s, (uint32_t)cap, &nb, &allocs);
+    if (rc) s->layer_used = true;
+  }
   if (rc) return rc;
   nb.prog = s->buf.prog;
   nb.prog_len = s->buf.prog_len;
@@ -2657,8 +2668,8 @@ int layer_failed(pp_state* s, const Op* ops, size_t len, bool grew) {
       h.lboost = 0;                            // no bucket overflows its slots from here on
       HIP_TRY(hipMemcpyAsync(&s->d_dyn->lboost, &h.lboost, sizeof(int32_t),
                              hipMemcpyHostToDevice, s->stream));
-    } else if (roomier) {
-      if ((rc = grow(s))) return rc;           // more staging slots per bucket
+    } else if (roomier && (rc = grow(s)) != PP_ENOMEM) {
+      if (rc) return rc;                       // (done: more staging slots per bucket)
     } else if (enlarge) {
       s->layer_big = true;                     // twice the strings per bucket, from here on
     } else if (!ops[k].fail_test && (h.lwhy & 2u) && !s->layer_huge && ensure_huge(s) == PP_OK) {
@@ -2684,6 +2695,7 @@ int layer_failed(pp_state* s, const Op* ops, size_t len, bool grew) {
       }
     }
   }
+  h.status &= ~ST_LAYER;                       // (a growth reads the state again)
   HIP_TRY(hipMemcpyAsync(&s->d_dyn->status, &h.status, sizeof(uint32_t), hipMemcpyHostToDevice,
                          s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
@@ -3009,7 +3021,13 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
       if ((s->h_dyn->status & ST_OVERFLOW)) {
         // an instance that cannot grow stops (kernels keep skipping it);
         // the others go on
-        const int g = s->wide_next ? PP_OK : grow(s);
+        int g = s->wide_next ? PP_OK : grow(s);
+        if (!g && !s->buf.nolayer && !s->buf.lcount) {   // grown without staging
+          s->buf.nolayer = 1;
+          if ((rc = upload_buf(s))) return rc;
+          hipLaunchKernelGGL(k_pass_layers, dim3(1), dim3(1), 0, stream, s->d_buf, s->d_dyn);
+          g = read_dyn(s);
+        }
         s->h_dyn->status = g ? (s->h_dyn->status | ST_FAILED) : (s->h_dyn->status & ~ST_OVERFLOW);
         HIP_TRY(hipMemcpyAsync(&s->d_dyn->status, &s->h_dyn->status, sizeof(uint32_t),
                                hipMemcpyHostToDevice, stream));

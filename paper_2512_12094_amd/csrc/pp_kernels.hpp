@@ -2649,6 +2649,13 @@ __global__ void k_pass_op(InstDyn* d, uint32_t k) {
   if (d->pc == k) d->pc = k + 1;
 }
 
+// Past the LAYER ops the instance stands at, once they are off.
+__global__ void k_pass_layers(const InstBuf* b, InstDyn* d) {
+  uint32_t pc = d->pc;
+  while (pc < b->prog_len && b->prog[pc].type == OP_LAYER) ++pc;
+  d->pc = pc;
+}
+
 // What a transaction may have to restore, into one backup area: the dynamic
 // state, the statistics lines, m coefficients (cw 4-byte words each) and m
 // liveness flags (one launch instead of four copies).

@@ -270,3 +270,64 @@ def test_refused_calls_keep_one_staging(gpu):
     assert held[-1] - plain < 33 * slots + (1 << 17)   # the staging and the call's backup
     ps.close()
     assert not alloc.held
+
+
+@pytest.mark.parametrize("staged", [True, False])
+@pytest.mark.parametrize("form", ["calls", "program", "batch"])
+def test_growth_without_memory_for_the_staging(gpu, form, staged):
+    """A store that can be had only without the layer op's staging grows
+    without it; the staging is asked for again by the next layer op (`staged`:
+    and given)."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    prog = W.xxz_ring(16, 2, 0.3, 0.8, eps=1e-7, name="z16")
+    print(f"[case] growth without the staging, {form}, staged {staged}", flush=True)
+    dp = driver.DeviceProgram(prog)
+    short = Refusing(gpu["alloc"])
+
+    def run(alloc):
+        sets = [driver.PauliSet.from_program(prog, None, gpu["handle"], alloc)
+                for _ in range(2 if form == "batch" else 1)]
+        if alloc is short:
+            def deny(nbytes):                          # the first store it grows into
+                return (nbytes >= 1 << 20 and not short.refused) or \
+                    (short.refused > 0 and not staged and staging(nbytes))
+            short.deny = deny
+        if form == "calls":
+            driver.run_layers(sets[0], driver.heisenberg_layers(prog))
+        else:
+            L.pp_batch_run([s.h for s in sets], [dp.h] * len(sets), gpu["handle"])
+        return sets, [(s.as_dict(), s.counters()) for s in sets]
+
+    plain, want = run(gpu["alloc"])
+    tight, got = run(short)
+    assert short.refused and got == want
+    stats = L.pp_layer_stats(tight[0].h)
+    assert stats["layer_ops"] > 0 and stats["fallbacks"] == 0, stats
+    for s in plain + tight:
+        s.close()
+    dp.close()
+    assert not short.held
+
+
+def test_growth_without_memory_for_exact_placement(gpu):
+    """A store that can be had only without what exact placement adds."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print("[case] growth without exact placement", flush=True)
+    prog = crowded_set()
+    fields = layer([W.Gate(0, 1 << q, 0.3) for q in range(12)])
+    short = Refusing(gpu["alloc"])
+    sets = [driver.PauliSet.from_program(prog, None, gpu["handle"], a) for a in (gpu["alloc"], short)]
+    for s in sets:
+        L.pp_set_max_terms(s.h, 2 * len(prog.obs))
+        driver.run_layers(s, driver.heisenberg_layers(prog))       # exact from here on
+        L.pp_set_max_terms(s.h, 0)
+        short.deny = lambda nbytes: nbytes >= 1 << 20 and not short.refused
+        s.apply_layer(fields)
+    assert short.refused == 1
+    assert sets[0].as_dict() == sets[1].as_dict()
+    assert sets[0].counters() == sets[1].counters()
+    for s in sets:
+        s.close()
+    assert not short.held
