@@ -115,7 +115,7 @@ struct pp_state {
   HostBlock* host = nullptr;
   char* d_core = nullptr;              // one allocation: d_buf .. d_stats
   char* h_stage = nullptr;             // pinned, kStageBytes: uploads of create_handle
-  size_t txn_cap = 0;                  // bytes of txn_backup (kept between calls)
+  size_t txn_cap = 0;                  // bytes of txn_backup (kept between calls: kTxnKeep)
   int n = 0, W = 1, group = 0;
   hipStream_t stream = nullptr;
   pp_allocator alloc{};
@@ -1753,13 +1753,22 @@ size_t txn_bytes(const pp_state* s, uint32_t M) {
   return sizeof(InstDyn) + kStatBytes + (size_t)M * (cs + 1) + 64;
 }
 
+// A backup of at most kTxnKeep bytes stays with the handle for its next call,
+// with headroom where that is to be had; a larger one (10^6 terms and up, whose
+// calls take longer than an allocation) goes back when its call ends.
+constexpr size_t kTxnKeep = size_t(16) << 20;
+
 int txn_begin(pp_state* s) {
   const InstDyn& h = *s->h_dyn;
   const uint32_t M = h.M;
-  if (txn_bytes(s, M) > s->txn_cap) {      // kept between calls, sized with headroom
+  const size_t bytes = txn_bytes(s, M);
+  if (bytes > s->txn_cap) {
     dev_free(s, s->txn_backup);
-    s->txn_cap = 2 * txn_bytes(s, M);
+    s->txn_backup = nullptr;
+    s->txn_cap = 2 * bytes <= kTxnKeep ? 2 * bytes : bytes;
     s->txn_backup = dev_alloc(s, s->txn_cap);
+    if (!s->txn_backup && s->txn_cap > bytes)
+      s->txn_backup = dev_alloc(s, s->txn_cap = bytes);
     if (!s->txn_backup) {
       s->txn_cap = 0;
       return fail(PP_ENOMEM, "transaction backup allocation failed");
@@ -1784,6 +1793,11 @@ void txn_end(pp_state* s) {
   for (auto& st : s->retired) free_store(s, st);
   s->retired.clear();
   s->txn = false;
+  if (s->txn_cap > kTxnKeep) {
+    dev_free(s, s->txn_backup);
+    s->txn_backup = nullptr;
+    s->txn_cap = 0;
+  }
 }
 
 // Restores the state of the call's start; returns `rc` (the call's error).

@@ -331,3 +331,26 @@ def test_growth_without_memory_for_exact_placement(gpu):
     for s in sets:
         s.close()
     assert not short.held
+
+
+def test_call_backup_takes_what_there_is_and_goes_back(gpu):
+    """The copy a call may roll back to: without memory for its headroom the
+    bytes it needs do, and a large one is not kept between calls."""
+    from paper_2512_12094_amd import driver
+    print("[case] call backup", flush=True)
+    alloc = Refusing(gpu["alloc"])
+    x, z, c = strings(20, 1500, 5)
+    ps = driver.PauliSet(20, "none", x, z, c, gpu["handle"], alloc)
+    alloc.deny = lambda nbytes: nbytes > 2 * 9 * 1500 and not alloc.refused
+    ps.merge()
+    assert alloc.refused == 1 and ps.num_terms() == 1500
+    ps.close()
+    rows = 1 << 21
+    i = np.arange(rows, dtype=np.uint64).reshape(-1, 1)
+    ps = driver.PauliSet(24, "none", i, np.zeros_like(i), np.ones(rows), gpu["handle"], alloc)
+    before = sum(alloc.held.values())
+    ps.merge()
+    assert sum(alloc.held.values()) < before + (1 << 20)
+    assert ps.num_terms() == rows
+    ps.close()
+    assert not alloc.held
