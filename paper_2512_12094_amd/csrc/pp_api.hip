@@ -751,8 +751,15 @@ int grow(pp_state* s) {
   InstBuf nb;
   std::vector<void*> allocs;
   int rc = alloc_store(s, (uint32_t)cap, &nb, &allocs);
-  // where memory is short: without what exact placement adds, then without the
-  // layer op's staging (the next layer op asks for it again)
+  // where memory is short: without the workspace of buckets in HBM (nothing is
+  // in flight), without what exact placement adds, then without the layer op's
+  // staging (layer ops ask for each again)
+  if (rc == PP_ENOMEM && s->d_huge) {
+    dev_free(s, s->d_huge);
+    s->d_huge = nullptr;
+    s->layer_huge = false;
+    rc = alloc_store(s, (uint32_t)cap, &nb, &allocs);
+  }
   if (rc == PP_ENOMEM && s->layer_used && s->layer_exact) {
     s->layer_exact = false;
     rc = alloc_store(s, (uint32_t)cap, &nb, &allocs);

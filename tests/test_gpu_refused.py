@@ -354,3 +354,34 @@ def test_call_backup_takes_what_there_is_and_goes_back(gpu):
     assert ps.num_terms() == rows
     ps.close()
     assert not alloc.held
+
+
+def test_growth_gives_up_the_workspace_of_large_buckets(gpu):
+    """A store that cannot be had beside the workspace of buckets in HBM (which
+    a closed set of 2^13 strings asked for) is had without it."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print("[case] growth without the large buckets' workspace", flush=True)
+    k = 13
+    fields = [layer([W.Gate(x << q, z << q, 0.3 + 0.01 * q) for q in range(k)])
+              for x, z in ((1, 0), (0, 1))]
+    alloc = Refusing(gpu["alloc"])
+    sets = [driver.PauliSet(20, "none", [[0]], [[(1 << k) - 1]], [1.0], gpu["handle"], a)
+            for a in (gpu["alloc"], alloc)]
+    huge = lambda: [b for b in alloc.held.values() if (64 << 20) < b < (256 << 20)]
+    for s in sets:
+        s.apply_layer(fields[0])                       # 2^13 strings in one closed set
+        assert L.pp_layer_stats(s.h)["fallbacks"] == 0
+    assert huge()
+    more = layer([W.Gate(0, 1 << q, 0.1) for q in range(3)])       # gate launches
+    for s in sets:
+        alloc.deny = lambda nbytes: nbytes >= 1 << 20 and bool(huge())
+        for _ in range(4):
+            s.apply_layer(more)
+        s.apply_layer(layer([W.Gate(1 << 15, 1 << q, 0.2) for q in range(2)]))
+    assert alloc.refused and not huge()
+    assert sets[0].as_dict() == sets[1].as_dict()
+    assert sets[0].counters() == sets[1].counters()
+    for s in sets:
+        s.close()
+    assert not alloc.held
