@@ -1004,6 +1004,7 @@ int run_ops(pp_state* s, std::vector<Op> ops, const std::vector<double>& tab,
   s->buf.nopart = 0;
   s->buf.nolayer = s->layer_off ? 1u : 0u;
   s->fb_lo = s->fb_hi = 0;
+  s->layer_fail_pc = ~size_t(0);           // (an op of another list has its own retries)
   s->batch_prog = nullptr;
   s->run_ops_list = &ops;
   struct Reset {
@@ -2820,6 +2821,7 @@ int solo_program(pp_state* s, const pp_program* p, double* expectation, bool res
   s->buf.prog_len = (uint32_t)len;
   s->buf.nopart = 0;
   s->buf.nolayer = s->layer_off ? 1u : 0u;
+  s->layer_fail_pc = ~size_t(0);           // (an op of another list has its own retries)
   s->batch_prog = p;
   if ((rc = upload_buf(s))) return rc;
   if (!resume) {

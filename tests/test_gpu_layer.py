@@ -259,3 +259,24 @@ def test_closed_set_past_the_staging_slots(gpu, n, k):
     on = run(gpu, prog, 1)
     same(on, run(gpu, prog, 0), prog.name)
     assert on["stats"]["fallbacks"] == 0 and on["stats"]["overflow_runs"] > 0, on["stats"]
+
+
+def test_calls_retry_each_layer_op_as_a_program(gpu):
+    """A closed set of 2^16 strings fits no form of a layer op.  Two calls that
+    meet it try what two sub-layers of a program try: the second call does not
+    start with the retries of the first used up."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print("[case] retries by calls and in a program", flush=True)
+    k = 16
+    xs = [W.Gate(1 << q, 0, 0.3 + 0.01 * q) for q in range(k)]
+    prog = W.Program("field16x2", k, "none", [(0, (1 << k) - 1, 1.0)],
+                     [W.SubLayer(xs), W.SubLayer(xs[::-1])], W.ZERO_STATE, {})
+    want = run(gpu, prog, 1)
+    ps = driver.PauliSet.from_program(prog, None, gpu["handle"], gpu["alloc"])
+    driver.run_layers(ps, driver.heisenberg_layers(prog))
+    stats = L.pp_layer_stats(ps.h)
+    assert ps.as_dict() == want["terms"]
+    ps.close()
+    assert stats["fallbacks"] == want["stats"]["fallbacks"] == 2
+    assert stats["overflow_runs"] == want["stats"]["overflow_runs"], (stats, want["stats"])
