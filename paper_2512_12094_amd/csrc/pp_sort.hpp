@@ -13,7 +13,7 @@
 //
 // That takes five launches per 8 bits, 40 for a 32-qubit set, and most sets
 // are too small for any of them to run longer than it takes to launch.  Sets
-// of up to sample_max<NK>() strings are sorted by sampling instead, in five
+// of up to samp_max<NK>() strings are sorted by sampling instead, in five
 // launches whatever the width (two up to samp_cap<NK>() / 2 strings, which
 // one block sorts in less time than three launches take):
 //   k_samp_keys     the live strings' integers (NK words) and slots;
@@ -22,11 +22,13 @@
 //                   last block turns the counts into bucket bases;
 //   k_samp_place    strings to bucket order;
 //   k_samp_sort     one block per bucket sorts it in LDS (bitonic) and writes
-//                   the rows; a bucket that does not fit the LDS ranks each
-//                   string against the bucket.
+//                   the rows; a bucket that outgrows the LDS is sorted a chunk
+//                   at a time and each string ranked in the other chunks.
 // The strings are distinct, so eight samples per bucket keep the buckets near
-// their average of at most half the LDS.  Above, the radix passes move each
-// string a fixed number of times while a block could not sort the sample.
+// their average: 1024 buckets that average a quarter of the LDS (2^19 strings of
+// one or two key words) hardly ever hold one that outgrows it, at the half that
+// samp_max admits about ten do.  Above, the radix passes move each string a
+// fixed number of times while a block could not sort the sample.
 // Whole export, before -> after: 10^5 strings of 32 qubits 640 -> 360 us (the
 // rest is copies), 4349 strings 440 -> 186 us, 5 strings of 64 qubits 400 ->
 // 115 us, 5.8x10^5 strings of 48 qubits 1.92 -> 1.6 ms.
@@ -252,7 +254,7 @@ struct SampSort {
   const void* c;
   uint32_t cap, M, N;      // entries, live strings
   int W, n, f32;
-  uint32_t P, lgP;         // buckets (1: no splitters)
+  uint32_t P;              // buckets (1: no splitters)
   uint64_t* key;           // [NK][N] integers, then in bucket order (key2)
   uint64_t* key2;
   uint32_t* slot;          // [N]
@@ -443,30 +445,57 @@ __global__ __launch_bounds__(kSortBlock) void k_samp_sort(SampSort p) {
     }
     p.oc[r] = p.f32 ? (double)static_cast<const float*>(p.c)[i] : static_cast<const double*>(p.c)[i];
   };
-  if (b > CAP) {                                 // too large for the LDS (uniform)
-    for (uint32_t e = threadIdx.x; e < b; e += kSortBlock) {
-      uint64_t k[NK];
+  // strings [at, at + m) of the bucket into LDS, sorted
+  auto sort = [&](uint32_t at, uint32_t m) {
+    uint32_t sz = 2;
+    while (sz < m) sz <<= 1;
+    for (uint32_t t = threadIdx.x; t < sz; t += kSortBlock) {
 #pragma unroll
-      for (int w = 0; w < NK; ++w) k[w] = p.key2[(size_t)w * p.N + base + e];
-      uint32_t r = 0;
-      for (uint32_t q = 0; q < b; ++q) {
-        uint64_t m[NK];
-#pragma unroll
-        for (int w = 0; w < NK; ++w) m[w] = p.key2[(size_t)w * p.N + base + q];
-        r += samp_less<NK>(m, k) ? 1u : 0u;
-      }
-      row(base + r, p.slot2[base + e]);
+      for (int w = 0; w < NK; ++w)
+        key[w][t] = t < m ? p.key2[(size_t)w * p.N + base + at + t] : ~0ull;
+      id[t] = (uint16_t)t;
     }
+    __syncthreads();
+    samp_bitonic<NK, (int)CAP>(key, id, sz);
+  };
+  if (b <= CAP) {
+    sort(0, b);
+    for (uint32_t t = threadIdx.x; t < b; t += kSortBlock) row(base + t, p.slot2[base + id[t]]);
     return;
   }
-  uint32_t sz = 2;
-  while (sz < b) sz <<= 1;
-  for (uint32_t t = threadIdx.x; t < sz; t += kSortBlock) {
+  // past the LDS (uniform; P > 1): sorted chunks go to the bucket's part of the
+  // unplaced keys and slots, which are free by now.  Export of 2^20 strings of
+  // 32 qubits, about ten such buckets: 3.4 ms with every string compared to its
+  // whole bucket, 1.9 ms so (radix passes 2.2).
+  for (uint32_t at = 0; at < b; at += CAP) {
+    const uint32_t m = b - at < CAP ? b - at : CAP;
+    sort(at, m);
+    for (uint32_t t = threadIdx.x; t < m; t += kSortBlock) {
 #pragma unroll
-    for (int w = 0; w < NK; ++w) key[w][t] = t < b ? p.key2[(size_t)w * p.N + base + t] : ~0ull;
-    id[t] = (uint16_t)t;
+      for (int w = 0; w < NK; ++w) p.key[(size_t)w * p.N + base + at + t] = key[w][t];
+      p.slot[base + at + t] = p.slot2[base + at + id[t]];
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  samp_bitonic<NK, (int)CAP>(key, id, sz);
-  for (uint32_t t = threadIdx.x; t < b; t += kSortBlock) row(base + t, p.slot2[base + id[t]]);
+  for (uint32_t e = threadIdx.x; e < b; e += kSortBlock) {
+    uint64_t k[NK];
+#pragma unroll
+    for (int w = 0; w < NK; ++w) k[w] = p.key[(size_t)w * p.N + base + e];
+    const uint32_t own = e / CAP * CAP;
+    uint32_t r = e - own;
+    for (uint32_t at = 0; at < b; at += CAP) {   // plus the smaller strings of the others
+      if (at == own) continue;
+      uint32_t lo = 0, hi = b - at < CAP ? b - at : CAP;
+      while (lo < hi) {
+        const uint32_t q = (lo + hi) / 2;
+        uint64_t m[NK];
+#pragma unroll
+        for (int w = 0; w < NK; ++w) m[w] = p.key[(size_t)w * p.N + base + at + q];
+        if (samp_less<NK>(m, k)) lo = q + 1;
+        else hi = q;
+      }
+      r += lo;
+    }
+    row(base + r, p.slot[base + e]);
+  }
 }

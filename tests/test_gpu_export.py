@@ -222,3 +222,58 @@ def test_export_order_at_the_sort_sizes(gpu, n, rows):
     order = np.lexsort(keys)
     assert np.array_equal(ox, x[order]) and np.array_equal(oz, z[order])
     assert np.array_equal(oc, c[order])
+
+
+def _random_rows(n, rows, seed):
+    words = W.n_words(n)
+    rng = np.random.default_rng(seed)
+    mask = np.array([(1 << min(64, n - 64 * w)) - 1 for w in range(words)], dtype=np.uint64)
+    a = rng.integers(0, 1 << 64, size=(rows + rows // 64, 2 * words), dtype=np.uint64)
+    a = np.unique(a & np.concatenate([mask, mask]), axis=0)
+    a = a[rng.permutation(len(a))[:rows]]
+    assert len(a) == rows
+    return a[:, :words].copy(), a[:, words:].copy()
+
+
+def _export_time(ps, rows, words):
+    import ctypes
+    import time
+    from paper_2512_12094_amd import _lib as L
+    x, z = (np.zeros((rows, words), np.uint64) for _ in range(2))
+    c, got, best = np.zeros(rows), ctypes.c_size_t(), 1e9
+    ptr = lambda a, t: a.ctypes.data_as(t)
+    for _ in range(7):
+        t = time.perf_counter()
+        L._check(L.lib().pp_export_terms(ps.h, ptr(x, L._u64p), ptr(z, L._u64p),
+                                         ptr(c, L._f64p), rows, ctypes.byref(got)))
+        best = min(best, time.perf_counter() - t)
+    assert got.value == rows
+    return x, z, c, best
+
+
+@pytest.mark.parametrize("n,rows", [(32, 1 << 20), (48, (1 << 20) - 5), (128, 1 << 18)])
+def test_export_of_the_largest_sampled_sets(gpu, n, rows):
+    """At the most strings that are sorted by sampling some buckets outgrow a
+    block's LDS: the rows come in order, in about the time per string of a
+    set half as large, where none does (1.5 to 1.7 times as long measured,
+    2.9 and more with those buckets compared string by string)."""
+    from paper_2512_12094_amd import driver
+    print(f"[case] export of the largest sampled set, n {n}", flush=True)
+    words, times = W.n_words(n), []
+    for k in (rows, rows // 2):
+        x, z = _random_rows(n, k, k + n)
+        c = np.arange(1, k + 1, dtype=np.float64)
+        ps = driver.PauliSet(n, "none", x, z, c, gpu["handle"], gpu["alloc"])
+        ox, oz, oc, t = _export_time(ps, k, words)
+        ps.close()
+        times.append(t)
+        keys = []
+        for w in range(words):
+            for sh in (0, 32):
+                lo = np.uint64(0xFFFFFFFF)
+                zz, xx = (z[:, w] >> np.uint64(sh)) & lo, ((x ^ z)[:, w] >> np.uint64(sh)) & lo
+                keys.append((_spread(zz) << np.uint64(1)) | _spread(xx))
+        order = np.lexsort(keys)
+        assert np.array_equal(ox, x[order]) and np.array_equal(oz, z[order])
+        assert np.array_equal(oc, c[order])
+    assert times[0] < 2.4 * times[1], times
