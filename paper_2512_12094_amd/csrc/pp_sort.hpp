@@ -336,8 +336,11 @@ __device__ __forceinline__ void samp_bitonic(uint64_t (*key)[CAP], uint16_t* id,
 }
 
 // Eight samples per bucket (with four, one of 1024 buckets of a quarter of
-// the LDS overflows it every third time), at evenly spaced positions: the
-// store's order is that of hashes.
+// the LDS overflows it every third time), one at a hashed position in each of as
+// many even stretches of the store.  At evenly spaced positions they would meet
+// the store's own periods: 2^19 strings made by one rotation after another hold
+// the letters of the first rotations' qubits in the low bits of their index,
+// every 64th has the same, and all but 2^13 of them fell into one of 1024 buckets.
 template <int NK>
 __global__ __launch_bounds__(1024) void k_samp_split(SampSort p) {
   constexpr uint32_t S = samp_size<NK>();
@@ -345,7 +348,9 @@ __global__ __launch_bounds__(1024) void k_samp_split(SampSort p) {
   __shared__ uint16_t id[S];
   const uint32_t n = samp_n(p), sz = 8 * p.P;    // P <= S / 8
   for (uint32_t t = threadIdx.x; t < sz; t += blockDim.x) {
-    const uint32_t i = (uint32_t)((uint64_t)t * n / sz);
+    const uint32_t lo = (uint32_t)((uint64_t)t * n / sz);
+    const uint32_t len = (uint32_t)((uint64_t)(t + 1) * n / sz) - lo;
+    const uint32_t i = len ? lo + (uint32_t)(pp::mix64(t) % len) : lo;   // < n (n = 0: unused)
 #pragma unroll
     for (int w = 0; w < NK; ++w) key[w][t] = n ? p.key[(size_t)w * p.N + i] : 0ull;
     id[t] = (uint16_t)t;

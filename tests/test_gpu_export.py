@@ -277,3 +277,23 @@ def test_export_of_the_largest_sampled_sets(gpu, n, rows):
         assert np.array_equal(ox, x[order]) and np.array_equal(oz, z[order])
         assert np.array_equal(oc, c[order])
     assert times[0] < 2.4 * times[1], times
+
+
+def test_export_of_a_set_in_the_order_of_its_rotations(gpu):
+    """2^19 strings made by one rotation after another, the most significant
+    qubits first: the low bits of a string's place in the store are its most
+    significant letters, and evenly spaced places hold only some of them."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print("[case] export in the order of the rotations", flush=True)
+    k = 19
+    ps = driver.PauliSet(20, "none", [[0]], [[(1 << k) - 1]], [1.0], gpu["handle"], gpu["alloc"])
+    for q in range(k - 1, -1, -1):
+        L.pp_apply_layer(ps.h, [[1 << q]], [[0]], [0.3], 1)
+    rows = 1 << k
+    x, z, c, t = _export_time(ps, rows, 1)
+    ps.close()
+    assert np.all(z == np.uint64(rows - 1))
+    # Y (2) below Z (3) on every qubit: in the order of the integer x descends
+    assert np.array_equal(x[:, 0], np.arange(rows - 1, -1, -1, dtype=np.uint64))
+    assert t < 0.05, t
