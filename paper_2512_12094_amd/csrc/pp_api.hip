@@ -16,8 +16,6 @@
 #include <memory>
 #include <mutex>
 #include <string>
-#include <system_error>
-#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -25,6 +23,7 @@
 #include "pp_kernels.hpp"
 #include "pp_merge.hpp"
 #include "pp_layer.hpp"
+#include "pp_pages.hpp"
 #include "pp_sort.hpp"
 #include "pp_types.h"
 
@@ -2137,42 +2136,6 @@ int pp_counters(pp_state* s, uint64_t out[2]) {
   return PP_OK;
 }
 
-namespace {
-
-// Writes a zero into every page of some output arrays (which are overwritten
-// whole afterwards) from a few threads; joined before the arrays are used.
-struct Prefault {
-  static constexpr size_t kMin = size_t(2) << 20;    // below: the copies fault them in
-  static constexpr size_t kPage = 4096, kMaxThreads = 8;
-  std::vector<std::thread> th;
-  void start(std::vector<std::pair<void*, size_t>> parts) {
-    size_t total = 0;
-    for (const auto& p : parts) total += p.second;
-    if (total < kMin) return;
-    const size_t n = std::min<size_t>(kMaxThreads, total / (kMin / 2));
-    for (size_t t = 0; t < n; ++t) {
-      try {
-        th.emplace_back([parts, t, n] {
-          for (const auto& p : parts) {
-            volatile char* c = static_cast<volatile char*>(p.first);
-            const size_t lo = p.second / n * t, hi = t + 1 == n ? p.second : p.second / n * (t + 1);
-            for (size_t o = lo; o < hi; o += kPage) c[o] = 0;
-          }
-        });
-      } catch (const std::system_error&) {           // no thread to be had: the copies do it
-        return;
-      }
-    }
-  }
-  void join() {
-    for (auto& t : th) t.join();
-    th.clear();
-  }
-  ~Prefault() { join(); }
-};
-
-}  // namespace
-
 }  // extern "C"
 
 namespace {
@@ -2274,8 +2237,8 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
   auto* oz = static_cast<uint64_t*>(ws.get(rows));
   auto* oc = static_cast<double*>(ws.get(sizeof(double) * N));
   // The caller's arrays are often fresh pages, which the copies back would
-  // fault in one by one (2/3 of the call at 8x10^6 terms): threads write them
-  // while the sort runs.
+  // fault in one by one (2/3 of the call at 8x10^6 terms): threads map them
+  // while the sort runs.  Their contents stay until the copies.
   Prefault touch;
   touch.start({{x, rows}, {z, rows}, {coef, sizeof(double) * N}});
   auto copy_out = [&]() -> int {
@@ -2309,10 +2272,11 @@ int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef, size_t 
               : nk == 2 ? sample_sort<2>(s, p, area, found)
                         : sample_sort<4>(s, p, area, found)))
       return rc;
-    if ((rc = copy_out())) return rc;
+    HIP_TRY(hipStreamSynchronize(s->stream));
     if (*found != N)
       return fail(PP_EDEVICE, "live count mismatch: " + std::to_string(*found) + " flagged, " +
                                   std::to_string(N) + " counted");
+    if ((rc = copy_out())) return rc;
     *n_out = N;
     return PP_OK;
   }
