@@ -1113,10 +1113,12 @@ void append_rotation(std::vector<double>& tab, const Op& op) {
   tab.insert(tab.end(), rec, rec + kLayerRec);
 }
 
-// The one-rotation ops [from, to) commute pairwise.
+// The one-rotation ops [from, to) commute pairwise.  Commutation is bilinear in
+// the strings' bits, so they do where a basis of their span over GF(2) does: at
+// most n strings, whatever the number of rotations.
 bool all_commute(const std::vector<Op>& ops, size_t from, size_t to, int W) {
   // strings of one letter each (x or z absent, or equal) commute: the usual
-  // sub-layer, without the pairwise check
+  // sub-layer, without the elimination
   bool letter[3] = {true, true, true};
   for (size_t a = from; a < to; ++a) {
     if (ops[a].type != OP_GATE) return false;
@@ -1127,11 +1129,33 @@ bool all_commute(const std::vector<Op>& ops, size_t from, size_t to, int W) {
     }
   }
   if (letter[0] || letter[1] || letter[2]) return true;
-  for (size_t a = from; a < to; ++a)
-    for (size_t c = a + 1; c < to; ++c) {
+  using Key = std::array<uint64_t, 2 * kMaxW>;   // x words, z words
+  std::vector<Key> basis;
+  std::vector<int> lead(128 * W, -1);            // basis string with that highest bit
+  for (size_t a = from; a < to; ++a) {
+    Key k{};
+    for (int w = 0; w < W; ++w) {
+      k[w] = ops[a].px[w];
+      k[W + w] = ops[a].pz[w];
+    }
+    for (int w = 2 * W; w-- > 0;)
+      while (k[w]) {
+        int& at = lead[64 * w + 63 - __builtin_clzll(k[w])];
+        if (at < 0) {
+          at = (int)basis.size();
+          basis.push_back(k);
+          k = Key{};
+        } else {
+          for (int v = 0; v < 2 * W; ++v) k[v] ^= basis[at][v];
+        }
+      }
+  }
+  if (basis.size() > size_t(64) * W) return false;   // (n at most, if they commute)
+  for (size_t a = 0; a < basis.size(); ++a)
+    for (size_t c = a + 1; c < basis.size(); ++c) {
       int odd = 0;
       for (int w = 0; w < W; ++w)
-        odd += __builtin_popcountll((ops[a].px[w] & ops[c].pz[w]) ^ (ops[a].pz[w] & ops[c].px[w]));
+        odd += __builtin_popcountll((basis[a][w] & basis[c][W + w]) ^ (basis[a][W + w] & basis[c][w]));
       if (odd & 1) return false;
     }
   return true;

@@ -275,3 +275,33 @@ def test_wide_sublayer_runs_its_active_rotations(gpu, name):
     for s in sets:
         s.close()
     dp.close()
+
+
+def test_commutation_of_many_rotations_is_quick(gpu):
+    """A program's sub-layers past 64 rotations are looked over for commutation
+    when it is created: that grows with the rotations, not with their pairs,
+    and one clash anywhere counts."""
+    import time
+    from paper_2512_12094_amd import _lib as L
+    print("[case] commutation of many rotations", flush=True)
+    n, r = 128, 20000
+    rng = np.random.default_rng(1)
+    low = rng.integers(0, 1 << 64, size=r, dtype=np.uint64)
+    x, z = np.zeros((r, 2), np.uint64), np.zeros((r, 2), np.uint64)
+    x[: r // 2, 0] = low[: r // 2]                   # X strings on qubits 0..63
+    z[r // 2:, 1] = low[r // 2:]                     # Z strings on qubits 64..127
+    clash = z.copy()
+    clash[-1, 0] = 1                                 # one Z on qubit 0
+
+    def create(x, z):
+        t = time.perf_counter()
+        h = L.pp_program_create(n, [0, r], x, z, np.full(r, 0.1), [1e-4], [-1], [0.0], [0, 0, 1.0])
+        t = time.perf_counter() - t
+        L.pp_program_destroy(h)
+        return t
+
+    one = min(create(np.zeros_like(x), z) for _ in range(3))
+    mixed = min(create(x, z) for _ in range(3))
+    late = min(create(x, clash) for _ in range(3))
+    print(f"create: one letter {one:.3f} s, mixed {mixed:.3f} s, a late clash {late:.3f} s")
+    assert mixed < 3 * one + 0.1 and late < 3 * one + 0.1
