@@ -8,6 +8,7 @@ Trotter layer (the op's output then carries gate-table entries), after
 forced fallbacks to the gate launches, under store growth, and in the
 batched form (which runs the gate copies); and the oracle's results by the
 parity rules of tests/parity.py.  Algorithm 1 step 2a; Prop. 1."""
+import numpy as np
 import pytest
 
 from oracle import oracle as O
@@ -280,3 +281,42 @@ def test_calls_retry_each_layer_op_as_a_program(gpu):
     ps.close()
     assert stats["fallbacks"] == want["stats"]["fallbacks"] == 2
     assert stats["overflow_runs"] == want["stats"]["overflow_runs"], (stats, want["stats"])
+
+
+def test_more_large_buckets_than_the_list_holds(gpu):
+    """2^15 strings of 80 qubits, each of which becomes a closed set of 2^8, in
+    2^11 buckets of about 4096 strings: more buckets outgrow the largest block
+    (2048) than are listed for HBM (1024), and the op runs with more buckets.
+    Bitwise the gate launches."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print("[case] more large buckets than the list holds", flush=True)
+    n, k, rows = 80, 8, 1 << 15
+    rng = np.random.default_rng(11)
+    x, z = np.zeros((rows, 2), np.uint64), np.zeros((rows, 2), np.uint64)
+    x[:, 0] = rng.permutation(rows).astype(np.uint64) << np.uint64(20)   # distinct outside
+    z[:, 0] = (rng.integers(0, 1 << 40, size=rows, dtype=np.uint64) << np.uint64(20)) | \
+        np.uint64((1 << k) - 1)
+    z[:, 1] = rng.integers(0, 1 << 16, size=rows, dtype=np.uint64)
+    c = rng.normal(size=rows)
+    gx = np.zeros((k, 2), np.uint64)
+    gx[:, 0] = np.uint64(1) << np.arange(k, dtype=np.uint64)
+    out, before = {}, L.pp_get_layer_tuning()["bucket_log2"]
+    L.pp_set_layer_tuning(4, 0)
+    try:
+        for mode in (0, 1):
+            L.pp_set_layer_ops(mode)
+            ps = driver.PauliSet(n, "none", x, z, c, gpu["handle"], gpu["alloc"])
+            L.pp_apply_layer(ps.h, gx, np.zeros_like(gx), 0.2 + 0.05 * np.arange(k), 2)
+            stats = L.pp_layer_stats(ps.h)
+            out[mode] = (ps.counters(), ps.expectation([0.3, 0.5, 0.7]), *ps.export())
+            ps.close()
+    finally:
+        L.pp_set_layer_ops(1)
+        L.pp_set_layer_tuning(before, 0)
+    assert len(out[1][2]) == rows << k
+    assert stats["layer_ops"] == 1 and stats["fallbacks"] == 0, stats
+    assert stats["overflow_runs"] >= 3, stats          # larger blocks, HBM, more buckets
+    assert out[0][:2] == out[1][:2]
+    for a, b in zip(out[0][2:], out[1][2:]):
+        assert np.array_equal(a, b)

@@ -385,3 +385,47 @@ def test_growth_gives_up_the_workspace_of_large_buckets(gpu):
     for s in sets:
         s.close()
     assert not alloc.held
+
+
+@pytest.mark.parametrize("what", ["exact", "huge"])
+def test_no_memory_for_what_a_failing_layer_op_lacks(gpu, what):
+    """Exact placement, or the workspace of buckets in HBM, that cannot be had:
+    the op's gate launches run (and with memory again, exact placement)."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print(f"[case] no memory for {what}", flush=True)
+    if what == "exact":
+        prog = crowded_set()
+        size = 8 * 2 * len(prog.obs)                   # the patterns, one per entry
+        deny = lambda nbytes: size <= nbytes < size + 256
+    else:
+        xs = [W.Gate(1 << q, 0, 0.3 + 0.01 * q) for q in range(13)]
+        prog = W.Program("field13", 13, "none", [(0, (1 << 13) - 1, 1.0)],
+                         [W.SubLayer(xs), W.SubLayer(xs[::-1])], W.ZERO_STATE, {})
+        deny = lambda nbytes: (64 << 20) < nbytes < (256 << 20)
+    layers = driver.heisenberg_layers(prog)
+    alloc = Refusing(gpu["alloc"], deny)
+    sets = [driver.PauliSet.from_program(prog, None, gpu["handle"], a)
+            for a in (gpu["alloc"], alloc)]
+    if what == "exact":
+        L.pp_set_max_terms(sets[1].h, 2 * len(prog.obs))
+        L.pp_set_gate_fusion(1)                        # (fused launches ask for more room)
+    try:
+        for s in sets:
+            s.apply_layer(layers[0])
+    finally:
+        L.pp_set_gate_fusion(3)
+    stats = L.pp_layer_stats(sets[1].h)
+    assert alloc.refused and stats["fallbacks"] == 1 and stats["layer_ops"] == 0, stats
+    alloc.deny = lambda nbytes: False
+    L.pp_set_max_terms(sets[1].h, 0)
+    for s in sets:
+        s.apply_layer(layers[1])
+    if what == "exact":
+        stats = L.pp_layer_stats(sets[1].h)
+        assert stats["fallbacks"] == 1 and stats["layer_ops"] == 1, stats
+    assert sets[0].as_dict() == sets[1].as_dict()
+    assert sets[0].counters() == sets[1].counters()
+    for s in sets:
+        s.close()
+    assert not alloc.held
