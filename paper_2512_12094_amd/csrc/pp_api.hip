@@ -176,7 +176,8 @@ struct pp_state {
   double m_growth = 2.0;   // records a merge took over the set size before it (last seen)
   unsigned long long* d_act = nullptr;   // run_wide's mask of rotations that act
   size_t act_cap = 0;                    // and its words
-  uint32_t wide_next = 0;  // rotations of the sub-layer at pc that a refused run_wide applied
+  bool wide_stopped = false;   // run_wide was refused inside the sub-layer at pc
+  uint32_t wide_next = 0;      // with so many of its rotations applied
   uint64_t m_prev_in = 0;  // merge_in and set size at the last read-back
   uint32_t m_prev = 0;
   int lx = 0;              // torus width (PP_GROUP_TORUS)
@@ -2734,7 +2735,8 @@ void resume_window(pp_state* s, const Op* ops, size_t len, size_t pc) {
 // when this is called and the device stands at w.from; it ends at w.to.
 // A growth that is refused leaves the device at w.from with the rotations that
 // are applied in wide_next: a batch that resumes the program there comes back
-// here for the others (the program's own launches would apply them all again).
+// here for the others (the program's own launches would apply them all again, and
+// wait for a count of theirs that the list has overwritten).
 //
 // Only for sub-layers past kLayerMaxRot rotations (at least 22 launches of
 // ~7 us): the extra launch and two reads cost ~50 us.  All-to-all couplings
@@ -2784,7 +2786,8 @@ int run_wide(pp_state* s, const pp_program* p, const pp_program::Wide& w) {
   s->batch_prog = p;
   const bool refused = stopped < applied.size();
   if (rc && !refused) return rc;
-  if (refused) s->wide_next = applied[stopped];
+  s->wide_stopped = refused;
+  s->wide_next = refused ? applied[stopped] : 0;
   const std::string msg = g_err;
   const uint32_t pc = (uint32_t)(refused ? w.from : w.to);
   const int up = upload_buf(s);
@@ -2796,7 +2799,6 @@ int run_wide(pp_state* s, const pp_program* p, const pp_program::Wide& w) {
     g_err = msg;
     return rc;
   }
-  s->wide_next = 0;
   return up;
 }
 
@@ -2814,6 +2816,7 @@ int solo_program(pp_state* s, const pp_program* p, double* expectation, bool res
   if ((rc = upload_buf(s))) return rc;
   if (!resume) {
     hipLaunchKernelGGL(k_set_pc, dim3(1), dim3(1), 0, st, s->d_dyn, 0u);
+    s->wide_stopped = false;
     s->wide_next = 0;
   }
   resume_window(s, ops, len, resume ? s->h_dyn->pc : 0);
@@ -2987,6 +2990,7 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
     if (s->batch_prog != programs[i]) {
       if (s->h_dyn->status & ST_FAILED) return fail(PP_EINVAL, "state failed in an earlier batch");
       s->shrunk = false;
+      s->wide_stopped = false;
       s->wide_next = 0;
       s->buf.prog = programs[i]->d_ops;
       s->buf.prog_len = (uint32_t)programs[i]->ops.size();
@@ -3000,7 +3004,7 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
       s->buf.nolayer = batch_layer(s, programs[i]) ? 0u : 1u;
       if ((rc = upload_buf(s))) return rc;
     }
-    if (s->wide_next) {                    // the steps skip it; run_wide goes on with it
+    if (s->wide_stopped) {                 // the steps skip it; run_wide goes on with it
       s->h_dyn->status |= ST_OVERFLOW;
       HIP_TRY(hipMemcpyAsync(&s->d_dyn->status, &s->h_dyn->status, sizeof(uint32_t),
                              hipMemcpyHostToDevice, stream));
@@ -3032,7 +3036,7 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
       if ((s->h_dyn->status & ST_OVERFLOW)) {
         // an instance that cannot grow stops (kernels keep skipping it);
         // the others go on
-        int g = s->wide_next ? PP_OK : grow(s);
+        int g = s->wide_stopped ? PP_OK : grow(s);
         if (!g && !s->buf.nolayer && !s->buf.lcount) {   // grown without staging
           s->buf.nolayer = 1;
           if ((rc = upload_buf(s))) return rc;
@@ -3054,7 +3058,7 @@ int batch_common(pp_state* const* states, const pp_program* const* programs, siz
                                hipMemcpyHostToDevice, stream));
         continue;
       }
-      if (s->h_dyn->pc < s->buf.prog_len && (s->h_dyn->peak >= kPromote || s->wide_next)) {
+      if (s->h_dyn->pc < s->buf.prog_len && (s->h_dyn->peak >= kPromote || s->wide_stopped)) {
         // a large instance (or one inside a wide sub-layer): finish it alone,
         // then put it back (finished)
         const pp_program* prog = s->batch_prog;

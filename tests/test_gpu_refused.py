@@ -429,3 +429,39 @@ def test_no_memory_for_what_a_failing_layer_op_lacks(gpu, what):
     for s in sets:
         s.close()
     assert not alloc.held
+
+
+@pytest.mark.parametrize("both", [False, True])
+def test_program_resumes_at_the_start_of_a_wide_sublayer(gpu, both):
+    """The refusal meets the first rotations of the sub-layer, with none
+    applied: the batched form finishes the program all the same."""
+    from paper_2512_12094_amd import _lib as L
+    from paper_2512_12094_amd import driver
+    print(f"[case] resume at the start of a wide sub-layer, both {both}", flush=True)
+    x, z, c = strings(16, 2000, 9)
+    obs = [(int(a), int(b), float(v)) for a, b, v in zip(x[:, 0], z[:, 0], c)]
+    pairs = [W.Gate(*W.two_site("X", a, b), 0.2) for a in range(16) for b in range(a)]
+    prog = W.Program("start16", 16, "none", obs,
+                     [W.SubLayer([W.Gate(0, 1 << q, 0.2) for q in range(16)], eps=0.1),
+                      W.SubLayer(pairs, eps=0.3, wmax=13)], W.ZERO_STATE, {})
+    dp = driver.DeviceProgram(prog)
+    make = lambda: driver.PauliSet.from_program(prog, None, gpu["handle"], gpu["alloc"])
+    ref, ps, other = make(), make(), make()
+    want = float(L.pp_batch_run([ref.h], [dp.h], gpu["handle"])[0])
+    L.pp_set_max_terms(ps.h, 4096)
+    with pytest.raises(L.PPError) as e:
+        L.pp_batch_run([ps.h], [dp.h], gpu["handle"])
+    assert e.value.code == CAPACITY and ps.num_terms() == len(obs)
+    L.pp_set_max_terms(ps.h, 0)
+    sets = [other, ps] if both else [ps]
+    for _ in range(200):
+        done, got = L.pp_batch_step([s.h for s in sets], [dp.h] * len(sets), gpu["handle"], 8)
+        if done.all():
+            break
+    assert (done == 1).all() and all(float(g) == want for g in got)
+    for s in sets:
+        assert s.as_dict() == ref.as_dict()
+        assert s.counters() == ref.counters()
+    for s in (ref, ps, other):
+        s.close()
+    dp.close()
