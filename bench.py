@@ -326,8 +326,10 @@ def ising_family_leg(stream, alloc, ns=range(3, 21), max_layers=10, cap=1 << 26,
 def batched_leg(stream, alloc, count, cap_terms):
     """The batched ring workload at full depth (every instance's whole
     program).  A first pass runs every instance alone with a store limit of
-    `cap_terms` entries and keeps the instances that finish within it (the
-    others, listed, would need more); on those: one batched run (FP64), the
+    `cap_terms` entries and keeps the instances that finish within it and
+    whose finished sets take at most a fifth of the device between them (the
+    others, listed, would need more; which fit depends on the library too, so
+    runs compare only where the lists are equal); on those: one batched run (FP64), the
     same batched with FP32 coefficients (largest relative deviation of its
     expectations from FP64), and a loop of single-instance runs, all timed
     from creating each set from its observable."""
@@ -353,15 +355,16 @@ def batched_leg(stream, alloc, count, cap_terms):
     torch.cuda.empty_cache()
     # the finished sets of the batch together take at most a fifth of the
     # device (the largest are left out), beside the stores still growing
-    total, fit = 0, []
+    total, fit, large = 0, [], []
     for held, i, p in sorted(keep, key=lambda t: t[:2]):
         total += held
         if total <= 0.2 * torch.cuda.get_device_properties(0).total_memory:
             fit.append((i, p))
         else:
-            excluded.append(dict(name=p.name, n=p.n, sublayers=len(p.sublayers)))
+            large.append(dict(name=p.name, n=p.n, sublayers=len(p.sublayers)))
     keep = [p for _, p in sorted(fit, key=lambda t: t[0])]
-    print(f"[bench] batched: {len(keep)} of {len(allp)} instances fit {cap_terms} entries",
+    print(f"[bench] batched: {len(keep)} of {len(allp)} instances run, {len(excluded)} need more "
+          f"than {cap_terms} entries, {len(large)} left out for memory",
           file=sys.stderr, flush=True)
     dps = [driver.device_program(p) for p in keep]
 
@@ -406,7 +409,8 @@ def batched_leg(stream, alloc, count, cap_terms):
         abs(a - b) / p.n for a, b, p in zip(e32, e64, keep))
     out.update(instances=len(allp), full_depth_completed=len(keep),
                excluded_over_store_limit=len(excluded), store_limit_entries=cap_terms,
-               excluded_n=sorted({e["n"] for e in excluded}),
+               excluded_for_memory=[e["name"] for e in large],
+               excluded_n=sorted({e["n"] for e in excluded + large}),
                gates=sum(p.n_gates for p in keep),
                speedup=round(out["batched"]["value"] / out["per_instance"]["value"], 3),
                bitwise_equal_expectations=f"{same}/{len(keep)}",

@@ -241,9 +241,10 @@ int pp_peak_terms(pp_state* s, size_t* out);
 /*
  * Layer-op statistics of a handle (see pp_set_layer_ops): out[0] layer ops
  * completed, out[1] layer-op runs that reported a bucket that did not fit
- * (each was run again with more buckets or replaced by its gate launches),
- * out[2] layer ops replaced by their gate launches, out[3] 1 when the
- * handle runs the gate launches throughout.  Synchronises the handle's
+ * (each was run again in another form or replaced by its gate launches),
+ * out[2] layer ops replaced by their gate launches after such a run, out[3]
+ * 1 when the handle runs the gate launches throughout.  Ops whose staging
+ * cannot be allocated run as gate launches and are in none of the counts.  Synchronises the handle's
  * stream.
  */
 int pp_layer_stats(pp_state* s, uint64_t out[4]);
@@ -252,12 +253,17 @@ int pp_layer_stats(pp_state* s, uint64_t out[4]);
  * Device bytes of a term store of `cap` entries for a handle of n_qubits,
  * group and dtype (both halves, tables and the merge staging, as the
  * library would allocate them now; no allocation happens).  A handle that
- * has run a layer op (one-instance programs, see pp_set_layer_ops) also
- * carries its staging: 16W + 16 bytes per entry more (16W + 36 once closed
- * sets outgrew their shares, and then up to 125 MB of workspace).  A handle's
- * store grows to hold its largest set with headroom (4x below 2^24
- * entries, 2x below 2^27, 1.5x above), and the old store is freed only
- * after the new one is filled.  PP_EINVAL for a bad group or size.
+ * has run a layer op (see pp_set_layer_ops) also carries its staging: 16W + 16
+ * bytes per staging slot, of which there are the entries rounded up to a power
+ * of two (four times that in stores of at most 2^17 entries); 16 bytes per
+ * entry more once closed sets outgrew their shares of it, and up to 125 MB of
+ * workspace once one outgrew a block.  A store that cannot be allocated with
+ * these is allocated without.  A handle's store grows to hold its largest set
+ * with headroom (4x below 2^24 entries, 2x below 2^27, 1.5x above), and the
+ * old store is freed only after the new one is filled.  Calls that may roll
+ * back keep a copy of the coefficients and flags (9 bytes per entry) while
+ * they run, and up to 16 MB of it between calls.  PP_EINVAL for a bad group or
+ * size.
  */
 int pp_store_bytes(int n_qubits, int group, int dtype, size_t cap, size_t* out);
 
@@ -271,12 +277,15 @@ int pp_num_terms(pp_state* s, size_t* out);
  * the base-4 digit of weight 4^q, I, X, Y, Z = 0, 1, 2, 3), the integer
  * whose minimum picks a representative in Algorithms 2 and 3.  After a
  * symmetry merge that is one record per representative in key order.  The
- * sort runs on the device (radix passes over the store, 8 bits of the
+ * sort runs on the device (up to 2^20 strings, 2^18 beyond 64 qubits, by
+ * splitters from a sample; more by radix passes over the store, 8 bits of the
  * integer each) in workspace taken from the handle's allocator and freed
- * before the call returns; synchronises the handle's stream.  *n_out =
- * number written.  PP_EINVAL if cap is smaller than the number of live
- * terms or an array is NULL; PP_ENOMEM if the workspace cannot be had;
- * PP_EDEVICE if the liveness flags disagree with the term count.
+ * before the call returns; meanwhile threads map the pages of the output
+ * arrays, whose contents change only with the result.  Synchronises the
+ * handle's stream.  *n_out = number written.  PP_EINVAL if cap is smaller
+ * than the number of live terms or an array is NULL; PP_ENOMEM if the
+ * workspace cannot be had; PP_EDEVICE if the liveness flags disagree with the
+ * term count.
  */
 int pp_export_terms(pp_state* s, uint64_t* x, uint64_t* z, double* coef,
                     size_t cap, size_t* n_out);
@@ -388,9 +397,10 @@ void pp_program_destroy(pp_program* p);
 
 /*
  * Shape of a created program: out[0] = device operations, out[1] = apply
- * operations a one-instance run launches (a layer op, or a gate launch of
- * up to three fused rotations outside the fallback copies of layer ops),
- * out[2] = rotations, out[3] = layer ops (see pp_set_layer_ops).  NULL
+ * operations a one-instance run launches at most (a layer op, or a gate
+ * launch of up to three fused rotations outside the fallback copies of layer
+ * ops; of sub-layers of more than 64 commuting rotations only those that act
+ * are launched), out[2] = rotations, out[3] = layer ops (see pp_set_layer_ops).  NULL
  * arguments: PP_EINVAL.
  */
 int pp_program_info(const pp_program* p, uint64_t out[4]);
@@ -418,7 +428,8 @@ int pp_batch_run(pp_state* const* states, const pp_program* const* programs,
  * (allocator failure or pp_set_max_terms); a failed instance stops, the
  * others continue, and the call still returns PP_OK.  Instances may join or
  * leave between calls.  An instance promoted as in pp_batch_run finishes
- * within the call that promotes it.  A state starts its program at the first
+ * within the call that promotes it, as does one whose program pp_batch_run
+ * was refused inside a sub-layer of more than 64 commuting rotations.  A state starts its program at the first
  * pp_batch_step/pp_batch_run call that lists it with that program.
  * pp_batch_run returns the first failure's code instead.
  */
@@ -429,7 +440,8 @@ int pp_batch_step(pp_state* const* states, const pp_program* const* programs,
 /*
  * Launch tuning (process-wide; the autotuner picks it per workload class):
  * terms per thread of the gate kernel and of the streaming kernels (merge,
- * compaction, damping/truncation/expectation) in {1, 2, 4, 8}, the cap on
+ * damping/truncation/expectation, and in the batched form the collection and
+ * compaction of the output) in {1, 2, 4, 8}, the cap on
  * blocks per launch, the batched steps per captured graph, and the gate
  * launches per batched step (1..64).  A 0 keeps the current value.
  * pp_get_tuning returns the five current values in that order.
@@ -489,8 +501,8 @@ int pp_set_gate_fusion(int max_rotations, int lanes);
  * device memory, then as its fused gate launches; after three such
  * fallbacks a handle runs the gate launches throughout.  Programs built from
  * now on have them, and pp_apply_layer calls made from now on run them.  The
- * store then also carries (16W + 16) bytes of staging per entry (four times
- * that in stores of at most 2^17 entries).  mode 0: off,
+ * store then also carries staging (pp_store_bytes); without memory for it the
+ * gate launches run.  mode 0: off,
  * 1: on (default), 2: on, but every layer op reports a failure (tests of the
  * fallback path).  Other modes: PP_EINVAL.
  */
@@ -498,7 +510,7 @@ int pp_set_layer_ops(int mode);
 
 /*
  * Layer-op tuning knobs (process-wide, launches made afterwards):
- * bucket_log2 = log2 of the strings per bucket aimed at (4..10, default 7;
+ * bucket_log2 = log2 of the strings per bucket aimed at (4..11, default 8;
  * 0 keeps the current value), block = threads per bucket block (256 or 512,
  * default 512; 0 keeps).  Results do not depend on them.  Out of range:
  * PP_EINVAL.  pp_get_layer_tuning returns the two current values.

@@ -384,7 +384,7 @@ def pp_set_layer_ops(mode):
 
 
 def pp_set_layer_tuning(bucket_log2=0, block=0):
-    """Layer ops: log2 strings per bucket (4..10; 0 keeps) and threads per
+    """Layer ops: log2 strings per bucket (4..11; 0 keeps) and threads per
     bucket block (256 or 512; 0 keeps)."""
     _check(lib().pp_set_layer_tuning(int(bucket_log2), int(block)))
 

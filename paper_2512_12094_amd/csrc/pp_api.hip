@@ -940,10 +940,10 @@ int launch_range(pp_state* s, const Op* ops, size_t from, size_t to) {
                      ? std::min(launch_blocks(elems, kOutU), kOutBlocks)
                  : lane_it            ? launch_blocks(elems << nrot, lane_it)
                                       : launch_blocks(elems, items_of(kind, big));
-      if (kind == PP_K_LAYER_APPLY) {       // about two blocks per bucket of the last size seen
+      if (kind == PP_K_LAYER_APPLY) {       // one block per bucket of the last size seen
         const uint32_t bits = layer_bits(std::max<uint32_t>(s->m_hint, 1), s->h_dyn->lboost,
                                          s->buf.lmaxbits, s->buf.lshift);
-        grid = (int)std::min<uint32_t>(1u << bits, 8192u);   // one bucket per block
+        grid = (int)std::min<uint32_t>(1u << bits, 8192u);
       }
       const int block = kind == PP_K_PART_SCAN ? kPCBlock
                         : kind == PP_K_PART_AGG ? kPABlock
@@ -2388,7 +2388,7 @@ int pp_program_create(pp_program** out, int n_qubits, size_t n_sub, const size_t
   TabRefs refs;
   std::vector<Op>& ops = p->ops;
   ops.push_back(make_op(OP_COUNT));
-  bool table_ok = true;                    // the merge of the observable's rows made it
+  bool table_ok = true;                    // the recount in front makes it
   for (size_t j = 0; j < n_sub; ++j) {
     if (!(eps[j] >= 0.0) || !(depol_p[j] >= 0.0 && depol_p[j] <= 1.0))
       return fail(PP_EINVAL, "bad sub-layer parameters");

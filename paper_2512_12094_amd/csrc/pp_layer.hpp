@@ -41,10 +41,14 @@ __host__ __device__ __forceinline__ int layer_key_words(int n, int W) {
   return n <= 32 ? 1 : 2 * W;
 }
 
-// Strings per bucket in LDS: two blocks fit a CU's 160 KB, or one with twice
-// the room (`big`: for closed sets that do not fit the smaller form; also of
-// 512 threads, since with 1024 the kernel's registers spill to scratch memory,
-// which the runtime cannot get once a caller's allocator holds the device's).
+// Strings per bucket in LDS: half a CU's 160 KB, or all of it (`big`: for closed
+// sets that do not fit the smaller form).  One block of 512 threads runs per CU
+// in either form: the kernel takes 197 registers a thread, which leave two waves
+// a SIMD.  The rotations are not what takes them (66 to 89 by key width): it is
+// the unrolled fold of layer_end, whose one thread holds 112 sums at once.  For
+// the same reason the larger form keeps 512 threads: with 1024 that fold spills
+// to scratch memory, which the runtime cannot get once a caller's allocator
+// holds the device's.
 template <int KW, bool Big>
 constexpr int layer_cap() {
   constexpr int n = KW == 1 ? 2048 : KW == 2 ? 1792 : 1024;
