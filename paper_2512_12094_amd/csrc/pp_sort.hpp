@@ -264,6 +264,7 @@ struct SampSort {
   uint64_t* split;         // [NK][P]
   uint32_t* cnt;           // [1 + P] strings found, strings per bucket (cleared)
   uint32_t* base;          // [P]
+  uint32_t* found;         // pinned host memory: cnt[0] for the host
   uint32_t* sync;          // done counters (pp::last_block)
   uint64_t* ox;
   uint64_t* oz;
@@ -441,6 +442,7 @@ __global__ __launch_bounds__(kSortBlock) void k_samp_sort(SampSort p) {
   __shared__ uint64_t key[NK][CAP];
   __shared__ uint16_t id[CAP];
   const uint32_t n = samp_n(p);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *p.found = p.cnt[0];
   const uint32_t b = p.P == 1 ? n : p.cnt[1 + blockIdx.x];
   const uint32_t base = p.P == 1 ? 0u : p.base[blockIdx.x];
   auto row = [&](uint32_t r, uint32_t i) {
